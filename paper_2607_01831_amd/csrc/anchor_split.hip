@@ -6,36 +6,49 @@
 // a = c >> R and an R-bit residual (R = 8 - A, A in 2, 4, 6); before the
 // residual arrives the anchor alone stands for code 2^R a + (2^R - 1) / 2,
 // the middle of the codes it covers, so the cache reads
-//   k = z + (2^R a + (2^R - 1) / 2) s,
+//   k = z' + a s',  s' = 2^R s,  z' = z + (2^R - 1) / 2 s,
 // and one query per sequence attends it: o = softmax(q K^T / sqrt(128)) V.
 // Planes hold a token's 128 anchors as a little-endian bit string of 16 A
 // bytes (element e at bits e A .. e A + A - 1).
 //
-// The anchor value is a code dequantization with adjusted metadata:
-// k = z' + a s' with s' = 2^R s and z' = z + (2^R - 1) / 2 s, so the
-// attention is the code attention of the verification kernel over the
-// A-bit values a < 64: the K scale s' is folded into the query rows (fp16
-// hi + lo, exponent E per group and row), z' enters a per-(group, row) bias,
-// and the V scale s' rides on the softmax weight with a 2^-Ev factor that
-// keeps the fp16 weights at most 1.  The operands are the exact fp16 values
-// of a (the byte trick 1024 + a, then one packed fp16 subtraction of 1024 per
-// two values): with s' = 2^R s the fold's exponent grows by R, and an offset
-// of 1024 carried through the fp32 accumulation would cost 2^R times the
-// rounding of the code kernels in the scores.
+// Operands: a field is never unpacked to a value of its own.  Two fields 16
+// bits apart in a word are masked where they lie or after one shift, which is
+// a pair of fp16 subnormals a 2^(sh - 24) (sh the field's bit position in its
+// half): a v_and for two values and a shift for about every fourth.  The
+// matrix cores take subnormals exactly, but align a sum's terms by the
+// exponent a subnormal is written with, 2^-14: a field in the lowest bits
+// loses the bits it is below that (rms error of a sum of 2,048 products of
+// 2-bit values at bit 0, 4, 6, 8: 1.4e-5, 2.6e-7, 9.4e-8, 1.0e-7 of the sum's
+// spread; plain values 1.0e-7).  So every field's top bit is put at bit 7 or
+// above.  The position's factor 2^sh is a
+// constant of the dimension, so on the K side it is folded into the query
+// (y_d = q_d s_d 2^(-sh) 2^(-E), with the K scale; fp16 hi + lo, |y| < 2^15,
+// E per group and row), and on the V side into the output's scale at the end.
+// V is read transposed by bytes (ds_read_b64_tr_b8): a byte of the plane holds
+// the same 4 (A = 2) or 2 (A = 4) dimensions for every token.  For A = 6 a
+// byte holds the end of one field and the start of another, which part being
+// where a matter of its index mod 3; P V is linear in V, so the low and the
+// high part of each byte are multiplied on their own (12 products instead of
+// 8, masks per lane) and the parts of a field added at the end.
+// The first form (bytes built from the fields, fp16 values 1024 + a less
+// 1024) spent about 1,100 instructions on a 32-token tile: a paged batch of 16
+// sequences of 4K-32K tokens took 207 us with 2-bit anchors, six times the
+// time of its bytes; now 69 us (6-bit anchors, a batch of 16K-64K: 296 -> 187).
+// The V scale rides on the softmax weight, pw_t = p_t s_t 2^-Ev in fp16 (Ev
+// per wavefront from the largest V scale of its tokens), z' is summed in fp32.
 //
 // Work split: grid = (context split, kv head x chunk of 16 query heads,
-// sequence); 4 wavefronts per workgroup, wavefront w owning the split's
-// groups w, w + 4, ...  Per 32-token tile a wavefront loads (plain loads,
-// the next tile's issued before the current one is attended) its lanes'
-// K fields, unpacks them to bytes and straight into the MFMA operand
-// registers (lane (col, kg) takes dims 32 kg .. + 31 of token col of each
-// 16-token half: 4 A bytes), and unpacks the tile's V fields into byte rows
-// of a per-wavefront LDS tile, read back transposed (ds_read_b64_tr_b8) as
-// the P V operand.  The softmax keeps a running maximum (rescaling when a
-// tile raises it).  The four wavefronts merge through LDS into one partial
-// per split.  When the grid runs in one round the last workgroup of each
-// (sequence, kv head, row chunk) merges the splits in the same launch (as
-// the 4-bit decode does); otherwise the combine kernel merges them.
+// sequence), the kv head fastest for paged layouts; 4 wavefronts per
+// workgroup, two workgroups per CU, wavefront w owning the split's groups
+// w, w + 4, ... (2-bit anchors: three per CU, since a tile is little work for
+// its waits; the batch above 80 -> 69 us).  As in the 4-bit decode the 32-token tiles stream into a
+// private LDS ring by global-to-LDS copies, each with its V metadata, a group's
+// K metadata with its first tile; the softmax reference is the maximum of the
+// wavefront's first tile, and a wavefront whose sums leave the safe range
+// redoes its tiles with a running maximum.  The four wavefronts merge through
+// LDS into one partial per split.  When the grid runs in one round the last
+// workgroup of each (sequence, kv head, row chunk) merges the splits in the
+// same launch; otherwise the combine kernel merges them.
 #include "f16_ops.h"
 #include "lane_ops.h"
 #include "lynx_internal.h"
@@ -52,99 +65,93 @@ constexpr int kWaves = 4;
 constexpr int kTile = 32;
 constexpr int kRows = 16;  // query rows (heads) per workgroup
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kVTileBytes = kTile * kCodeRow;  // 32 V rows of 128 code bytes
-constexpr int kKMetaFloats = 2 * kHeadDim;     // s' [128] | z' [128] of a group
+constexpr int kKMetaBytes = 2 * kHeadDim * 4;  // K scales [128], zeros [128] of a group
 
-// Bits [p, p + 32) of a little-endian bit string held in words w[0 .. n).
-template <int N>
-__device__ __forceinline__ uint32_t bits32(const uint32_t (&w)[N], int p) {
-    const int i = p >> 5, sh = p & 31;
-    const uint32_t lo = w[i];
-    const uint32_t hi = i + 1 < N ? w[i + 1] : 0u;
-    return sh == 0 ? lo : (lo >> sh) | (hi << (32 - sh));
-}
-
-// 32 A-bit fields (the bit string w, field e at bits e A ..) -> 32 bytes
-// (8 words, byte e = field e).
-template <int A, int N>
-__device__ __forceinline__ void fields_to_bytes(const uint32_t (&w)[N], uint32_t (&b)[8]) {
-    constexpr uint32_t mask = (1u << A) - 1u;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint32_t x = bits32(w, 4 * A * j);  // fields 4 j .. 4 j + 3
-        b[j] = (x & mask) | (((x >> A) & mask) << 8) | (((x >> (2 * A)) & mask) << 16) |
-               (((x >> (3 * A)) & mask) << 24);
+// The K operand's place of each dimension.  A lane holds 32 dimensions of a
+// token in A words; operand kk (of 4) holds the pairs p = 0..3: dimensions
+// first(kk, p) and first(kk, p) + kApart, both at bit shift(kk, p) of a half.
+template <int A>
+struct KPlace {
+    static constexpr int kApart = A == 4 ? 4 : 8;
+    static constexpr int first(int kk, int p) { return A == 4 ? 8 * kk + p : 16 * (kk >> 1) + 4 * (kk & 1) + p; }
+    static constexpr int shift(int kk, int p) {
+        const int j = 4 * (kk & 1) + p;  // field of its half (A = 2), of its 48 bits (A = 6)
+        if (A == 2) return j == 2 || j == 4 || j == 6 || j == 7 ? 8 : 6;
+        if (A == 4) return 4;
+        return j == 1 || j == 4 || j >= 6 ? 4 : 2;
     }
-}
+};
 
-// Eight byte values a (two words, byte e = element e) -> eight exact fp16
-// values a in element order: 1024 + a by byte permutes, less 1024.
-__device__ __forceinline__ u32x4_t bytes_to_f16(uint32_t w0, uint32_t w1) {
-    const u32x4_t r = codes_to_f16(w0, w1);
-    const f16x2_t off = {(_Float16)-1024.0f, (_Float16)-1024.0f};
-    u32x4_t o;
+// The lane's 32 fields of A bits (words w) -> four operands of fp16 subnormal
+// pairs, placed as KPlace says.
+template <int A>
+__device__ __forceinline__ void k_operands(const uint32_t (&w)[A], u32x4_t (&av)[4]) {
+    if constexpr (A == 2) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        // through a scalar copy: a bit cast of the vector element itself
-        // compiles to element 0 for every i with this compiler
-        const uint32_t ri = r[i];
-        f16x2_t h;
-        __builtin_memcpy(&h, &ri, 4);
-        h = h + off;
-        uint32_t oi;
-        __builtin_memcpy(&oi, &h, 4);
-        o[i] = oi;
-    }
-    return o;
-}
-
-// Loads of n consecutive words from a 4-byte-aligned address.
-template <int N>
-__device__ __forceinline__ void load_words(const uint8_t *p, uint32_t (&w)[N]) {
-    const uint32_t *q = reinterpret_cast<const uint32_t *>(p);
-    if constexpr (N % 4 == 0 && N > 0) {
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t x = w[i], l4 = x << 4, r4 = x >> 4;
+            av[2 * i] = u32x4_t{(x << 6) & 0x00C000C0u, l4 & 0x00C000C0u, l4 & 0x03000300u, x & 0x00C000C0u};
+            av[2 * i + 1] = u32x4_t{x & 0x03000300u, r4 & 0x00C000C0u, r4 & 0x03000300u, (x >> 6) & 0x03000300u};
+        }
+    } else if constexpr (A == 4) {
 #pragma unroll
-        for (int i = 0; i < N; i += 4) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(q + i);
-            w[i] = v.x;
-            w[i + 1] = v.y;
-            w[i + 2] = v.z;
-            w[i + 3] = v.w;
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t x = w[i];
+            av[i] = u32x4_t{(x << 4) & 0x00F000F0u, x & 0x00F000F0u, (x >> 4) & 0x00F000F0u, (x >> 8) & 0x00F000F0u};
         }
     } else {
 #pragma unroll
-        for (int i = 0; i < N; i += 2) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(q + i);
-            w[i] = v.x;
-            w[i + 1] = v.y;
+        for (int i = 0; i < 2; ++i) {
+            // the first and the second 48 bits of 16 fields, a half of each per word
+            const uint32_t x0 = w[3 * i], x1 = w[3 * i + 1], x2 = w[3 * i + 2];
+            const uint32_t p0 = __builtin_amdgcn_perm(x1, x0, 0x07060100u);
+            const uint32_t p1 = __builtin_amdgcn_perm(x2, x0, 0x05040302u);
+            const uint32_t p2 = __builtin_amdgcn_perm(x2, x1, 0x07060100u);
+            av[2 * i] = u32x4_t{(p0 << 2) & 0x00FC00FCu, (p0 >> 2) & 0x03F003F0u,
+                                ((p0 >> 10) & 0x003C003Cu) | ((p1 & 0x00030003u) << 6), p1 & 0x00FC00FCu};
+            av[2 * i + 1] = u32x4_t{(p1 >> 4) & 0x03F003F0u,
+                                    ((p1 >> 12) & 0x000C000Cu) | ((p2 & 0x000F000Fu) << 4), p2 & 0x03F003F0u,
+                                    (p2 >> 6) & 0x03F003F0u};
         }
     }
 }
 
-// One tile's loads for one lane: K fields of tokens 16 r + col (r = 0, 1),
-// dims 32 kg .. + 31; V fields of token lane / 2, dims 64 (lane % 2) .. + 63;
-// V scale and zero of token lane % 32; with a group's first tile, K scale and
-// zero of dims 2 lane, 2 lane + 1.
+// A tile in the ring: K rows (32 x 16 A bytes), V rows, V scales [32] and
+// zeros [32].  Row t's 16-byte chunk q sits at chunk q ^ swizzle(t), so that
+// the lanes of one LDS read phase touch different banks.
 template <int A>
-struct TileRegs {
-    uint32_t k[2][A];
-    uint32_t v[2 * A];
-    float vs, vz;
-    float2 ks, kz;
+struct Ring {
+    // 2-bit tiles are small (2.25 KB): three in flight, one for the others
+    static constexpr int kDepth = A == 2 ? 4 : 2;
+    static constexpr int kRow = 16 * A;
+    static constexpr int kPlane = kTile * kRow;
+    static constexpr int kVMeta = 2 * kPlane;
+    static constexpr int kSlot = kVMeta + 2 * kTile * 4;
+    static constexpr int kCopies = kPlane / 1024;  // per plane and tile
+    static __device__ __forceinline__ int k_swizzle(int t) {
+        return A == 2 ? 0 : A == 4 ? (t >> 1) & 3 : (t >> 3) & 1;
+    }
+    static __device__ __forceinline__ int v_swizzle(int t) {
+        return A == 4 ? ((t >> 2) & 1) | ((t >> 4) & 1) << 1 : (t >> 4) & 1;
+    }
 };
 
-// LAYOUT 0: one block per sequence (contiguous); 1: any paging.
-// SG: 128-token groups per split (4, 8 or 16).
-template <int A, int LAYOUT, int SG>
-__global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_kernel(SplitDecodeArgs a) {
+// LAYOUT 0: one block per sequence (contiguous); 1: paged, block_tokens a
+// multiple of 16; 2: any other paging.
+template <int A, int LAYOUT>
+__global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_kernel(SplitDecodeArgs a) {
+    using RG = Ring<A>;
+    using KP = KPlace<A>;
     constexpr int R = 8 - A;
-    constexpr int kRowBytes = 16 * A;
-    constexpr int kMaxGroups = SG / kWaves;
-    static_assert(SG % kWaves == 0, "groups must split evenly over the wavefronts");
-    const float centre = (float)((1 << R) - 1) * 0.5f;
+    constexpr int kDepth = RG::kDepth;
+    constexpr int kChunks = A;                  // 16-byte chunks of a row
+    constexpr int kParts = A == 2 ? 4 : 2;      // parts a byte is multiplied in
+    constexpr int kAcc = kChunks * kParts;      // 8, 8 or 12 accumulators
+    constexpr int kCols = 16 * kAcc;            // output columns before parts are added
+    constexpr float centre = (float)((1 << R) - 1) * 0.5f;
     const int Hkv = a.geo.Hkv;
-    const int split = blockIdx.x;
-    const int hc = blockIdx.y;
+    const int split = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
     const int h = hc % Hkv;
     const int chunk = hc / Hkv;
     const int b = blockIdx.z;
@@ -154,6 +161,7 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_kernel(SplitD
     const int col = lane & 15;
     const int kg = lane >> 4;
     const int T = max(0, min(a.seq_lens[b], a.max_seq_len));
+    const int SG = a.groups_per_split;
     const int g0 = split * SG;
     const int n_groups = max(0, min(SG, (T - g0 * kKGroup + kKGroup - 1) / kKGroup));
     const int row_base = chunk * kRows;
@@ -175,35 +183,31 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_kernel(SplitD
             return;
         }
         // a split past the context: (max, sum) = (-inf, 0)
-        for (int r = tid; r < kRows; r += kThreads)
-            if (row_base + r < a.rows_total) a.ws_ml[partial_index(row_base + r)] = make_float2(-INFINITY, 0.0f);
+        if (tid < heads) a.ws_ml[partial_index(row_base + tid)] = make_float2(-INFINITY, 0.0f);
         return;
     }
 
-    // LDS: query rows; per wavefront its V byte tile, the tile's V scales
-    // and zeros, and its group's K scales and zeros; the epilogue reuses the
-    // V tiles and metadata
-    constexpr int kWaveBytes = kVTileBytes + 2 * kTile * 4 + kKMetaFloats * 4;
-    constexpr int kEpilogueBytes = (kWaves * kRows * (kHeadDim + 4)) * 4;
-    constexpr int kBufBytes = kWaves * kWaveBytes > kEpilogueBytes ? kWaves * kWaveBytes : kEpilogueBytes;
-    __shared__ __attribute__((aligned(16))) uint8_t s_buf[kBufBytes];
+    // LDS: 45-60 KB, two workgroups per CU; the epilogue reuses the ring
+    constexpr int kRingBytes = kWaves * kDepth * RG::kSlot;
+    __shared__ __attribute__((aligned(16))) uint8_t s_ring[kRingBytes];
+    __shared__ __attribute__((aligned(16))) uint8_t s_km[kWaves][kKMetaBytes];
     __shared__ __attribute__((aligned(16))) uint8_t s_q[kRows * kHeadDim * 2];
     __shared__ int s_ev[kWaves];
     __shared__ float s_ML[kRows][2];
-    uint8_t *s_vt = s_buf + (size_t)w * kWaveBytes;                           // V byte rows
-    float *s_vm = reinterpret_cast<float *>(s_vt + kVTileBytes);              // s' [32] | z' [32]
-    float *s_km = s_vm + 2 * kTile;                                           // s' [128] | z' [128]
+    static_assert((kWaves * kRows * kCols + 4 * kWaves * kRows) * 4 <= kRingBytes,
+                  "the epilogue's arrays must fit in the ring");
 
     bool bad = false;
     const int32_t *bt_row = a.block_table + (size_t)b * a.geo.max_blocks;
     const size_t vmeta = ((size_t)b * Hkv + h) * a.geo.max_tokens;
     const size_t kmeta = ((size_t)b * Hkv + h) * a.geo.n_groups * kHeadDim;
-    const int blk0 = LAYOUT == 0 ? min(max(bt_row[0], 0), a.geo.num_blocks - 1) : 0;
+    const size_t blk0_rows =
+        LAYOUT == 0 ? ((size_t)min(max(bt_row[0], 0), a.geo.num_blocks - 1) * Hkv + h) * a.geo.bt : 0;
     if (LAYOUT == 0 && (bt_row[0] < 0 || bt_row[0] >= a.geo.num_blocks)) bad = true;
     // plane row of token t (tokens past the context are clamped by the caller)
     auto row_of = [&](int t) -> size_t {
-        if (LAYOUT == 0) return ((size_t)blk0 * Hkv + h) * a.geo.bt + (size_t)t;
-        const int bi = t / a.geo.bt;
+        if (LAYOUT == 0) return blk0_rows + (size_t)t;
+        const int bi = a.bt_shift >= 0 ? (t >> a.bt_shift) : t / a.geo.bt;
         int blk = bt_row[bi];
         if (blk < 0 || blk >= a.geo.num_blocks) {
             bad = true;
@@ -215,240 +219,415 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_kernel(SplitD
     // this wavefront's tiles: tile j is tile j % 4 of its group j / 4, the
     // split's group w + 4 (j / 4)
     const int n_mine = n_groups > w ? (n_groups - w + kWaves - 1) / kWaves : 0;
-    const int n_tiles = 4 * n_mine;
     auto tile_t0 = [&](int j) { return (g0 + w + kWaves * (j >> 2)) * kKGroup + kTile * (j & 3); };
+    auto tile_valid = [&](int j) { return (j >> 2) < n_mine && tile_t0(j) < T; };
 
-    auto load_tile = [&](int j, TileRegs<A> &rg) {
-        const int t0 = tile_t0(j);
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int t = min(t0 + 16 * r + col, T - 1);
-            load_words(a.k_anc + row_of(t) * kRowBytes + 4 * A * kg, rg.k[r]);
-        }
-        {
-            const int t = min(t0 + (lane >> 1), T - 1);
-            load_words(a.v_anc + row_of(t) * kRowBytes + 8 * A * (lane & 1), rg.v);
-        }
-        {
-            const int t = min(t0 + (lane & 31), T - 1);
-            rg.vs = a.meta.v_scale[vmeta + t];
-            rg.vz = a.meta.v_zero[vmeta + t];
-        }
-        if ((j & 3) == 0) {
-            const int g = g0 + w + kWaves * (j >> 2);
-            rg.ks = reinterpret_cast<const float2 *>(a.meta.k_scale + kmeta + (size_t)g * kHeadDim)[lane];
-            rg.kz = reinterpret_cast<const float2 *>(a.meta.k_zero + kmeta + (size_t)g * kHeadDim)[lane];
-        }
-    };
-
-    // the first tile's loads, the query rows and the V scales go out together:
-    // one round trip before the loop
-    TileRegs<A> cur, nxt;
-    if (n_tiles > 0) load_tile(0, cur);
+    // ---- plain loads, all issued before the first copy ----
+    // The query rows (16 threads per 256-byte row; rows past the chunk's heads
+    // repeat the last), the V scales of the wavefront's tokens (for Ev) and,
+    // for LAYOUT 1, the block of every 16-token run the wavefront attends
+    // (lane 8 u + r: run r of its group u; at most 4 groups).
     uint4 q4;
     {
-        const int r = tid >> 4;  // 16 threads per 256-byte row (rows past the chunk's heads repeat the last)
-        const int hh = min(row_base + r, a.rows_total - 1);
+        const int hh = min(row_base + (tid >> 4), a.rows_total - 1);
         const size_t qrow = (size_t)b * a.Hq + (size_t)h * a.G + hh;
         q4 = reinterpret_cast<const uint4 *>(a.q + qrow * kHeadDim)[tid & 15];
     }
-    // ---- the largest adjusted V scale s' of the wavefront's tokens ----
-    int Ev = 0;
-    {
-        float vm = 0.0f;
+    int run_blk = 0;
+    if (LAYOUT == 1) {
+        const int u = min(lane >> 3, 3);
+        const int tr = (g0 + w + kWaves * u) * kKGroup + 16 * (lane & 7);
+        const int bi = a.bt_shift >= 0 ? (tr >> a.bt_shift) : tr / a.geo.bt;
+        run_blk = bt_row[min(bi, a.geo.max_blocks - 1)];
+    }
+    auto v_scale_at = [&](int u, int k) {
+        const int t = (g0 + w + kWaves * u) * kKGroup + 64 * k + lane;
+        return u < n_mine && t < T ? a.meta.v_scale[vmeta + t] : 0.0f;
+    };
+    float vmx[8];
 #pragma unroll
-        for (int u = 0; u < kMaxGroups; ++u) {
+    for (int i = 0; i < 8; ++i) vmx[i] = v_scale_at(i >> 1, i & 1);
+    float vm = 0.0f;
+    for (int u = 4; u < n_mine; ++u) vm = fmax2(vm, fmax2(v_scale_at(u, 0), v_scale_at(u, 1)));
+
+    // ---- copies into the ring ----
+    // Lane l of copy i fills 16-byte slot 64 i + l of the plane's tile: row
+    // slot / A, physical chunk slot % A.
+    const uint32_t ring = lds_addr(s_ring) + (uint32_t)w * kDepth * RG::kSlot;
+    const uint8_t *ring_p = s_ring + (size_t)w * kDepth * RG::kSlot;
+    const uint32_t km = lds_addr(&s_km[w][0]);
+    int crow[RG::kCopies];          // row of the tile
+    uint32_t kq[RG::kCopies], vq[RG::kCopies];  // byte offset of the logical chunk in its row
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int t = (g0 + w + kWaves * u) * kKGroup + 64 * k + lane;
-                if (u < n_mine && t < T) vm = fmax2(vm, a.meta.v_scale[vmeta + t]);
+    for (int i = 0; i < RG::kCopies; ++i) {
+        const int slot = 64 * i + lane;
+        crow[i] = slot / A;
+        const int pq = slot - crow[i] * A;
+        kq[i] = 16u * (uint32_t)(pq ^ RG::k_swizzle(crow[i]));
+        vq[i] = 16u * (uint32_t)(pq ^ RG::v_swizzle(crow[i]));
+    }
+
+    // Tile j of this wavefront into ring slot j % kDepth.
+    auto issue_tile = [&](int j) {
+        const int t0 = __builtin_amdgcn_readfirstlane(tile_t0(j));
+        const uint32_t slot = ring + (uint32_t)(j % kDepth) * RG::kSlot;
+        if (LAYOUT == 0 && t0 + kTile <= T) {
+            const size_t rb = (blk0_rows + (size_t)t0) * RG::kRow;
+#pragma unroll
+            for (int i = 0; i < RG::kCopies; ++i) {
+                const uint32_t off = (uint32_t)crow[i] * RG::kRow;
+                lds_copy16(a.k_anc + rb, off + kq[i], slot + 1024u * i);
+                lds_copy16(a.v_anc + rb, off + vq[i], slot + RG::kPlane + 1024u * i);
+            }
+        } else if (LAYOUT == 1 && t0 + kTile <= T) {
+            // two 16-token runs, each inside one block: byte offset of run r's
+            // row 0, less 16 r rows
+            size_t rb[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int tr = t0 + 16 * r;
+                const int bi = a.bt_shift >= 0 ? (tr >> a.bt_shift) : tr / a.geo.bt;
+                int blk = __builtin_amdgcn_readlane(run_blk, 8 * (j >> 2) + 2 * (j & 3) + r);
+                if (blk < 0 || blk >= a.geo.num_blocks) {
+                    bad = true;
+                    blk = 0;
+                }
+                rb[r] = (((size_t)blk * Hkv + h) * a.geo.bt + (size_t)(tr - bi * a.geo.bt)) * RG::kRow;
+            }
+#pragma unroll
+            for (int i = 0; i < RG::kCopies; ++i) {
+                const int r = crow[i] >> 4;
+                const size_t at = (r ? rb[1] : rb[0]) + (uint32_t)((crow[i] & 15) * RG::kRow);
+                lds_copy16(a.k_anc + at + kq[i], slot + 1024u * i);
+                lds_copy16(a.v_anc + at + vq[i], slot + RG::kPlane + 1024u * i);
+            }
+        } else {
+            // per-lane rows; rows past the context repeat the last token
+#pragma unroll
+            for (int i = 0; i < RG::kCopies; ++i) {
+                const size_t at = row_of(min(t0 + crow[i], T - 1)) * RG::kRow;
+                lds_copy16(a.k_anc + at + kq[i], slot + 1024u * i);
+                lds_copy16(a.v_anc + at + vq[i], slot + RG::kPlane + 1024u * i);
             }
         }
-        vm = max_kg(row16_max(vm)) * (float)(1 << R);
+        // V scale (lanes 0..31) and zero (lanes 32..63) of the tile's tokens;
+        // tokens past the context repeat the last one
+        {
+            const int t = min(t0 + (lane & 31), T - 1);
+            lds_copy4((lane < 32 ? a.meta.v_scale : a.meta.v_zero) + vmeta + t, slot + RG::kVMeta);
+        }
+        // K scale (lanes 0..31) and zero (lanes 32..63) of the group
+        if ((j & 3) == 0) {
+            const int g = g0 + min(w + kWaves * (j >> 2), n_groups - 1);
+            const float *src = (lane < 32 ? a.meta.k_scale : a.meta.k_zero) + kmeta + (size_t)g * kHeadDim;
+            lds_copy16(src + 4 * (lane & 31), km);
+        }
+    };
+    static_assert(kDepth - 1 < 4, "a group's K metadata may not arrive before the last group's fold");
+    auto issue_first = [&]() {
+        if (n_mine > 0) {
+#pragma unroll
+            for (int c = 0; c < kDepth - 1; ++c) issue_tile(c);  // all in the first group
+        }
+    };
+    // The block ids are needed first where there are any; elsewhere the first
+    // tiles go out before the plain loads above are waited for.
+    if (LAYOUT == 1)
+        asm volatile("" : "+v"(run_blk));
+    issue_first();
+
+    int Ev = 0;
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) vm = fmax2(vm, vmx[i]);
+        vm = max_kg(row16_max(vm));
         if (vm > 0.0f) frexpf(vm, &Ev);
         Ev = max(Ev, -100);
     }
-
     reinterpret_cast<uint4 *>(s_q)[tid] = q4;
     __syncthreads();  // the query rows are in
 
     // ---- per-wavefront online-softmax state: lane (col = query row, kg);
     // the reference carries the 2^-Ev factor of the V weights ----
     float m_run = -INFINITY, m_ref = -INFINITY, l_part = 0.0f, ob_part = 0.0f;
-    f32x4_t acc[8];
+    f32x4_t acc[kAcc];
+    auto reset_state = [&]() {
+        m_run = m_ref = -INFINITY;
+        l_part = ob_part = 0.0f;
 #pragma unroll
-    for (int n = 0; n < 8; ++n) acc[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    const bool row_live = row_base + col < a.rows_total;
-
-    // fold of a group from s' and z' in LDS: q''_d = q_d s'_d 2^-E as fp16
-    // hi + lo, score scale 2^E kscore, bias kscore sum_d q_d z'_d
+        for (int n = 0; n < kAcc; ++n) acc[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    };
+    reset_state();
+    // Rows past the chunk's heads repeat the last one; their results go nowhere.
+    // Fold of a group (K scales and zeros from the K-metadata buffer): the
+    // operands y_d, the score scale bsc = kscore 2^(24 + R + E) and the bias
+    // bb = kscore sum_d q_d z'_d.
     u32x4_t bq[8];
     float bsc = 0.0f, bb = 0.0f;
     auto fold = [&]() {
-        const float *ks = s_km + 32 * kg;
-        const float *kz = s_km + kHeadDim + 32 * kg;
+        const float *ks = reinterpret_cast<const float *>(&s_km[w][0]) + 32 * kg;
+        const float *kz = ks + kHeadDim;
         const uint4 *qp = reinterpret_cast<const uint4 *>(s_q + col * (kHeadDim * 2) + 64 * kg);
-        float mx = 0.0f, bias = 0.0f;
+        float qs[32];  // q_d s_d
+        float bias = 0.0f, mx = 0.0f;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const uint4 u = qp[k];
+            const float4 s0 = reinterpret_cast<const float4 *>(ks)[2 * k];
+            const float4 s1 = reinterpret_cast<const float4 *>(ks)[2 * k + 1];
+            const float4 z0 = reinterpret_cast<const float4 *>(kz)[2 * k];
+            const float4 z1 = reinterpret_cast<const float4 *>(kz)[2 * k + 1];
             const float qv[8] = {bf16_lo(u.x), bf16_hi(u.x), bf16_lo(u.y), bf16_hi(u.y),
                                  bf16_lo(u.z), bf16_hi(u.z), bf16_lo(u.w), bf16_hi(u.w)};
+            const float sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+            const float zv[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float sv = ks[8 * k + e], zv = kz[8 * k + e];
-                mx = fmax2(mx, fabsf(qv[e] * sv));
-                bias = fmaf(qv[e], zv, bias);
+                qs[8 * k + e] = qv[e] * sv[e];
+                bias = fmaf(qv[e], fmaf(centre, sv[e], zv[e]), bias);
+                mx = fmax2(mx, fabsf(qs[8 * k + e]));
             }
         }
         mx = max_kg(mx);
         bias = sum_kg(bias);
         int E = 0;
         if (mx > 0.0f) frexpf(mx, &E);
+        E -= 15;  // |y| < 2^15: the low halves stay clear of the fp16 floor
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            const uint4 u = qp[kk];
-            const float qv[8] = {bf16_lo(u.x), bf16_hi(u.x), bf16_lo(u.y), bf16_hi(u.y),
-                                 bf16_lo(u.z), bf16_hi(u.z), bf16_lo(u.w), bf16_hi(u.w)};
             u32x4_t hi, lo;
 #pragma unroll
-            for (int e = 0; e < 8; e += 2) {
-                const float y0 = row_live ? ldexpf(qv[e] * ks[8 * kk + e], -E) : 0.0f;
-                const float y1 = row_live ? ldexpf(qv[e + 1] * ks[8 * kk + e + 1], -E) : 0.0f;
+            for (int p = 0; p < 4; ++p) {
+                const int d = KP::first(kk, p), ex = -E - KP::shift(kk, p);
+                const float y0 = ldexpf(qs[d], ex), y1 = ldexpf(qs[d + KP::kApart], ex);
                 const uint32_t hp = pack_f16(y0, y1);
-                hi[e / 2] = hp;
-                lo[e / 2] = pack_f16(y0 - f16_lo(hp), y1 - f16_hi(hp));
+                hi[p] = hp;
+                lo[p] = pack_f16(less_f16_lo(y0, hp), less_f16_hi(y1, hp));  // exact differences
             }
             bq[2 * kk] = hi;
             bq[2 * kk + 1] = lo;
         }
-        bsc = ldexpf(kscore, E);
-        bb = row_live ? bias * kscore : 0.0f;
+        bsc = ldexpf(kscore, 24 + R + E);
+        bb = bias * kscore;
     };
 
-    const int tr = 16 * ((col >> 1) >> 2) + 4 * kg + ((col >> 1) & 3);
-    const int half = col & 1;
-
-    for (int j = 0; j < n_tiles; ++j) {
-        if (j + 1 < n_tiles) load_tile(j + 1, nxt);  // in flight while tile j is attended
+    // This lane's K words of a tile: dims 32 kg .. + 31 of token 16 r + col.
+    const uint32_t kswz = (uint32_t)RG::k_swizzle(col);
+    auto load_k = [&](const uint8_t *slot_p, int r, uint32_t (&kw)[A]) {
+        const uint8_t *row = slot_p + (16 * r + col) * RG::kRow;
+        if constexpr (A == 4) {
+            const uint4 u = *reinterpret_cast<const uint4 *>(row + 16 * ((uint32_t)kg ^ kswz));
+            kw[0] = u.x;
+            kw[1] = u.y;
+            kw[2] = u.z;
+            kw[3] = u.w;
+        } else {
+#pragma unroll
+            for (int i = 0; i < A / 2; ++i) {
+                const uint32_t unit = (uint32_t)(A / 2 * kg + i);  // 8-byte units
+                const uint2 u = *reinterpret_cast<const uint2 *>(row + 16 * ((unit >> 1) ^ kswz) + 8 * (unit & 1));
+                kw[2 * i] = u.x;
+                kw[2 * i + 1] = u.y;
+            }
+        }
+    };
+    // Products of tile j (scores are bsc times them, plus bb): lane (col, kg)
+    // gets token t0 + 16 r + 4 kg + i of query row col in x[4 r + i]; tokens
+    // past the context get -inf.
+    auto tile_products = [&](const uint8_t *slot_p, int j, float (&x)[8]) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            uint32_t kw[A];
+            load_k(slot_p, r, kw);
+            u32x4_t av[4];
+            k_operands<A>(kw, av);
+            f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                sc = mfma_f16(av[kk], bq[2 * kk + 0], sc);
+                sc = mfma_f16(av[kk], bq[2 * kk + 1], sc);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[4 * r + i] = sc[i];
+        }
         const int t0 = tile_t0(j);
-        // V fields -> byte rows of the LDS tile; s', z' of the tile's tokens;
-        // with a group's first tile its K s', z'
-        {
-            uint32_t bytes[2][8];
-            uint32_t wv[A];
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-#pragma unroll
-                for (int i = 0; i < A; ++i) wv[i] = cur.v[p * A + i];
-                fields_to_bytes<A>(wv, bytes[p]);
-            }
-            const int t = lane >> 1;
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int q2 = 0; q2 < 2; ++q2)
-                    *reinterpret_cast<uint4 *>(s_vt + v_slot(t, 4 * (lane & 1) + 2 * p + q2)) =
-                        make_uint4(bytes[p][4 * q2], bytes[p][4 * q2 + 1], bytes[p][4 * q2 + 2], bytes[p][4 * q2 + 3]);
-            // lane l < 32: s' of token l; lane l >= 32: z' of token l - 32
-            s_vm[lane] = lane < 32 ? ldexpf(cur.vs, R) : fmaf(centre, cur.vs, cur.vz);
-            if ((j & 3) == 0) {
-                s_km[2 * lane] = ldexpf(cur.ks.x, R);
-                s_km[2 * lane + 1] = ldexpf(cur.ks.y, R);
-                s_km[kHeadDim + 2 * lane] = fmaf(centre, cur.ks.x, cur.kz.x);
-                s_km[kHeadDim + 2 * lane + 1] = fmaf(centre, cur.ks.y, cur.kz.y);
-            }
-        }
-        asm volatile("" ::: "memory");  // the LDS writes above precede the reads below
-        if ((j & 3) == 0) fold();
-
-        // scores (log2 units): lane (col, kg) gets token t0 + 16 r + 4 kg + i
-        // of query row col in x[4 r + i]
-        float x[8];
-        {
-            f32x4_t sc[2];
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                uint32_t kb[8];
-                fields_to_bytes<A>(cur.k[r], kb);
-                sc[r] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    const u32x4_t av = bytes_to_f16(kb[2 * kk], kb[2 * kk + 1]);
-                    sc[r] = mfma_f16(av, bq[2 * kk + 0], sc[r]);
-                    sc[r] = mfma_f16(av, bq[2 * kk + 1], sc[r]);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) x[i] = fmaf(sc[i >> 2][i & 3], bsc, bb);
-            if (t0 + kTile > T) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int t = t0 + 16 * (i >> 2) + 4 * kg + (i & 3);
-                    x[i] = t < T ? x[i] : -INFINITY;
-                }
-            }
-        }
-        // running maximum per row; rescale when the tile raises it
-        {
-            const float mx = max_kg(fmax3(fmax3(x[0], x[1], x[2]), fmax3(x[3], x[4], x[5]), fmax2(x[6], x[7])));
-            if (__any(mx > m_run)) {
-                const float m_new = fmaxf(mx, m_run);
-                const float alpha = (m_run == -INFINITY) ? 0.0f : exp2f(m_run - m_new);
-                m_run = m_new;
-                m_ref = m_new + (float)Ev;
-                l_part *= alpha;
-                ob_part *= alpha;
-                float af[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) af[i] = __shfl(alpha, 4 * kg + i);
-#pragma unroll
-                for (int n = 0; n < 8; ++n)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[n][i] *= af[i];
-            }
-        }
-        // weights and P V
-        {
-            const float4 vs0 = *reinterpret_cast<const float4 *>(s_vm + 4 * kg);
-            const float4 vs1 = *reinterpret_cast<const float4 *>(s_vm + 16 + 4 * kg);
-            const float4 vz0 = *reinterpret_cast<const float4 *>(s_vm + kTile + 4 * kg);
-            const float4 vz1 = *reinterpret_cast<const float4 *>(s_vm + kTile + 16 + 4 * kg);
-            const float vsv[8] = {vs0.x, vs0.y, vs0.z, vs0.w, vs1.x, vs1.y, vs1.z, vs1.w};
-            const float vzv[8] = {vz0.x, vz0.y, vz0.z, vz0.w, vz1.x, vz1.y, vz1.z, vz1.w};
-            float pw[8];
+        if (t0 + kTile > T) {
+            asm volatile("" ::: "memory");  // keep the masking out of full tiles
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const float p = __builtin_amdgcn_exp2f(x[i] - m_ref);
-                l_part += p;
-                ob_part = fmaf(p, vzv[i], ob_part);
-                pw[i] = p * vsv[i];
-            }
-            u32x4_t pa;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) pa[e] = pack_f16_rne(pw[2 * e], pw[2 * e + 1]);
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const intx2_t vt = __builtin_amdgcn_ds_read_tr8_b64_v2i32(
-                    (__attribute__((address_space(3))) intx2_t *)(s_vt + v_slot(tr, c) + 8 * half));
-                acc[c] = mfma_f16(pa, bytes_to_f16((uint32_t)vt[0], (uint32_t)vt[1]), acc[c]);
+                const int t = t0 + 16 * (i >> 2) + 4 * kg + (i & 3);
+                x[i] = t < T ? x[i] : -INFINITY;
             }
         }
-        // the LDS tile and metadata are rewritten for the next tile: their
-        // reads must be done
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (j + 1 < n_tiles) cur = nxt;
+    };
+    // the row's largest score of a tile (bsc > 0)
+    auto tile_max = [&](const float (&x)[8]) {
+        return fmaf(max_kg(fmax3(fmax3(x[0], x[1], x[2]), fmax3(x[3], x[4], x[5]), fmax2(x[6], x[7]))), bsc, bb);
+    };
+
+    // Transposed V reads: lane (col, kg) names row tau(kg, col / 2) =
+    // 16 (col / 8) + 4 kg + (col / 2) % 4 and 8-byte half col % 2 of a chunk,
+    // and receives byte col of the chunk for the tokens tau(kg, 0..7).
+    uint32_t v_off[kChunks];
+    {
+        const int tr = 16 * (col >> 3) + 4 * kg + ((col >> 1) & 3);
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c)
+            v_off[c] = (uint32_t)(RG::kPlane + tr * RG::kRow + 16 * (c ^ RG::v_swizzle(tr)) + 8 * (col & 1));
     }
+    // A = 6: the low part of byte 16 c + col is 6, 4 or 2 bits by its index
+    // mod 3; it is moved up by 4, 4 or 6 and masked, the rest is masked in place.
+    uint32_t lowm[3] = {0, 0, 0}, highm[3] = {0, 0, 0}, up[3] = {0, 0, 0};
+    if (A == 6) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int m = (c + col) % 3;
+            lowm[c] = m == 0 ? 0x03F003F0u : m == 1 ? 0x00F000F0u : 0x00C000C0u;
+            highm[c] = m == 0 ? 0x00C000C0u : m == 1 ? 0x00F000F0u : 0x00FC00FCu;
+            up[c] = m == 2 ? 6 : 4;
+        }
+    }
+    // Part p of the bytes of four tokens (word v): pairs of tokens 0, 2 (e) and
+    // 1, 3 (o), both at the part's place in a half.
+    auto part_of = [&](uint32_t v, int c, int p, uint32_t &e, uint32_t &o) {
+        if constexpr (A == 2) {  // at bits 8, 6, 8, 6
+            const uint32_t m = p & 1 ? 0x00C000C0u : 0x03000300u;
+            e = (p == 0 ? v << 8 : p == 3 ? v : v << 4) & m;
+            o = (p == 0 ? v : p == 3 ? v >> 8 : v >> 4) & m;
+        } else if constexpr (A == 4) {  // at bit 4
+            e = (p == 0 ? v << 4 : v) & 0x00F000F0u;
+            o = (p == 0 ? v >> 4 : v >> 8) & 0x00F000F0u;
+        } else if (p == 0) {
+            e = (v << up[c % 3]) & lowm[c % 3];
+            o = (v >> (8 - up[c % 3])) & lowm[c % 3];
+        } else {
+            e = v & highm[c % 3];
+            o = (v >> 8) & highm[c % 3];
+        }
+    };
+    // Weights against m_ref, then P V for the tile.
+    auto tile_accumulate = [&](const uint8_t *slot_p, const float (&x)[8]) {
+        const float *vsm = reinterpret_cast<const float *>(slot_p + RG::kVMeta) + 4 * kg;
+        const float4 vs0 = *reinterpret_cast<const float4 *>(vsm);
+        const float4 vs1 = *reinterpret_cast<const float4 *>(vsm + 16);
+        const float4 vz0 = *reinterpret_cast<const float4 *>(vsm + kTile);
+        const float4 vz1 = *reinterpret_cast<const float4 *>(vsm + kTile + 16);
+        const float vsv[8] = {vs0.x, vs0.y, vs0.z, vs0.w, vs1.x, vs1.y, vs1.z, vs1.w};
+        const float vzv[8] = {vz0.x, vz0.y, vz0.z, vz0.w, vz1.x, vz1.y, vz1.z, vz1.w};
+        const float c0 = bb - m_ref;
+        float pw[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float p = __builtin_amdgcn_exp2f(fmaf(x[i], bsc, c0));
+            l_part += p;
+            ob_part = fmaf(p, fmaf(centre, vsv[i], vzv[i]), ob_part);
+            pw[i] = p * vsv[i];
+        }
+        // token pairs as the masks leave them: (0, 2), (1, 3), (4, 6), (5, 7)
+        const u32x4_t pa = {pack_f16_rne(pw[0], pw[2]), pack_f16_rne(pw[1], pw[3]), pack_f16_rne(pw[4], pw[6]),
+                            pack_f16_rne(pw[5], pw[7])};
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) {
+            const intx2_t vt = __builtin_amdgcn_ds_read_tr8_b64_v2i32(
+                (__attribute__((address_space(3))) intx2_t *)(slot_p + v_off[c]));
+            const uint32_t v0 = (uint32_t)vt[0], v1 = (uint32_t)vt[1];
+#pragma unroll
+            for (int p = 0; p < kParts; ++p) {
+                uint32_t e0, o0, e1, o1;
+                part_of(v0, c, p, e0, o0);
+                part_of(v1, c, p, e1, o1);
+                acc[kParts * c + p] = mfma_f16(pa, u32x4_t{e0, o0, e1, o1}, acc[kParts * c + p]);
+            }
+        }
+    };
+
+    // Fast path: a fixed softmax reference, the maximum of the wavefront's
+    // first tile; the next tiles are in flight while one is attended.
+    auto copies_at = [](int c) { return 2 * RG::kCopies + ((c & 3) == 0 ? 2 : 1); };
+    for (int u = 0; u < n_mine; ++u) {
+        const bool next_group = u + 1 < n_mine;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int j = 4 * u + c;
+            if (c + kDepth - 1 < 4 || next_group) issue_tile(j + kDepth - 1);
+            // tile j is in once only the later tiles' copies may remain in flight
+            int later_here = 0, later_next = 0;
+#pragma unroll
+            for (int k = 1; k < kDepth; ++k) {
+                later_next += copies_at(c + k);
+                if (c + k < 4) later_here += copies_at(c + k);
+            }
+            if (next_group) {
+                wait_vmcnt_folded(later_next);
+            } else {
+                wait_vmcnt_folded(later_here);
+            }
+            const uint8_t *slot_p = ring_p + (c % kDepth) * RG::kSlot;
+            if (c == 0) fold();
+            if (tile_valid(j)) {
+                float x[8];
+                tile_products(slot_p, j, x);
+                if (j == 0) {
+                    m_run = tile_max(x);
+                    m_ref = m_run + (float)Ev;
+                }
+                tile_accumulate(slot_p, x);
+            }
+            // the slot and the K-metadata buffer are rewritten by later
+            // copies: their reads must be done
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+    }
+    bool unsafe = !(l_part < 1e30f) || !(fabsf(ob_part) < 1e30f);
+#pragma unroll
+    for (int n = 0; n < kAcc; ++n)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) unsafe |= !(fabsf(acc[n][i]) < 1e30f);
+    if (__any(unsafe)) {
+        // Slow path (this wavefront only): running maximum with rescaling,
+        // one tile fetched and waited for at a time.
+        reset_state();
+        for (int j = 0; j < 4 * n_mine; ++j) {
+            issue_tile(j);
+            wait_vmcnt<0>();
+            const uint8_t *slot_p = ring_p + (j % kDepth) * RG::kSlot;
+            if ((j & 3) == 0) fold();
+            if (tile_valid(j)) {
+                float x[8];
+                tile_products(slot_p, j, x);
+                const float mx = tile_max(x);
+                if (__any(mx > m_run)) {
+                    const float m_new = fmaxf(mx, m_run);
+                    const float alpha = (m_run == -INFINITY) ? 0.0f : exp2f(m_run - m_new);
+                    m_run = m_new;
+                    m_ref = m_new + (float)Ev;
+                    l_part *= alpha;
+                    ob_part *= alpha;
+                    float af[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) af[i] = __shfl(alpha, 4 * kg + i);
+#pragma unroll
+                    for (int n = 0; n < kAcc; ++n)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[n][i] *= af[i];
+                }
+                tile_accumulate(slot_p, x);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+    }
+    wait_vmcnt<0>();  // no copy may land in the ring once it is reused below
 
     // ---- per-wavefront totals -> LDS (still scaled by 2^-Ev) ----
-    __syncthreads();  // every wavefront is done with its LDS tile
-    float *s_o = reinterpret_cast<float *>(s_buf);
-    float(*s_m)[kRows] = reinterpret_cast<float(*)[kRows]>(s_o + kWaves * kRows * kHeadDim);
+    __syncthreads();  // every wavefront is done with its ring
+    // ring reused: o [wave][row][kCols] (A = 2, 4: dims in order; A = 6: the
+    // low parts of bytes 0..95, then their high parts), then max, sum,
+    // sum p z' and merge factors [wave][row]
+    float *s_o = reinterpret_cast<float *>(s_ring);
+    float(*s_m)[kRows] = reinterpret_cast<float(*)[kRows]>(s_o + kWaves * kRows * kCols);
     float(*s_l)[kRows] = s_m + kWaves;
     float(*s_ob)[kRows] = s_l + kWaves;
     float(*s_f)[kRows] = s_ob + kWaves;
-    static_assert((kWaves * kRows * kHeadDim + 4 * kWaves * kRows) * 4 <= kBufBytes,
-                  "the epilogue's arrays must fit");
     {
         const float l = sum_kg(l_part);
         const float ob = sum_kg(ob_part);
@@ -457,15 +636,31 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_kernel(SplitD
             s_l[w][col] = l;
             s_ob[w][col] = ob;
         }
+        constexpr float kUnit = (float)(1u << 24) * (float)(1 << R);  // the operand's 2^-24, s' = 2^R s
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i) {
+            if (4 * kg + i < heads) {
+                float *o = s_o + (w * kRows + 4 * kg + i) * kCols;
 #pragma unroll
-            for (int c = 0; c < 8; ++c)
-                s_o[(w * kRows + 4 * kg + i) * kHeadDim + 16 * c + col] = acc[c][i];
+                for (int c = 0; c < kChunks; ++c) {
+                    if constexpr (A == 2) {
+                        *reinterpret_cast<float4 *>(o + 4 * (16 * c + col)) =
+                            make_float4(acc[4 * c][i] * (kUnit / 256.0f), acc[4 * c + 1][i] * (kUnit / 64.0f),
+                                        acc[4 * c + 2][i] * (kUnit / 256.0f), acc[4 * c + 3][i] * (kUnit / 64.0f));
+                    } else if constexpr (A == 4) {
+                        *reinterpret_cast<float2 *>(o + 2 * (16 * c + col)) =
+                            make_float2(acc[2 * c][i] * (kUnit / 16.0f), acc[2 * c + 1][i] * (kUnit / 16.0f));
+                    } else {
+                        o[16 * c + col] = acc[2 * c][i] * (kUnit / 16.0f);  // a byte's third kind: at 64
+                        o[96 + 16 * c + col] = acc[2 * c + 1][i] * kUnit;
+                    }
+                }
+            }
+        }
     }
     if (lane == 0) s_ev[w] = Ev;
     const bool any_bad = __syncthreads_or(bad);
-    if (tid < kRows) {
+    if (tid < heads) {
         float M = -INFINITY;
 #pragma unroll
         for (int ww = 0; ww < kWaves; ++ww) M = fmaxf(M, s_m[ww][tid]);
@@ -487,17 +682,27 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_kernel(SplitD
     const __amdgpu_buffer_rsrc_t pair_o =
         buffer_rsrc(a.ws_o + prow0 * a.ws_splits * kHeadDim, (uint32_t)heads * a.ws_splits * kHeadDim * 4);
     const __amdgpu_buffer_rsrc_t pair_ml = buffer_rsrc(a.ws_ml + prow0 * a.ws_splits, (uint32_t)heads * a.ws_splits * 8);
-    for (int idx = tid; idx < kRows * (kHeadDim / 4); idx += kThreads) {
+    for (int idx = tid; idx < heads * (kHeadDim / 4); idx += kThreads) {
         const int rr = idx / (kHeadDim / 4);
         const int d4 = idx % (kHeadDim / 4);
-        const int row = row_base + rr;
-        if (row >= a.rows_total) continue;
         float4 O = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int ww = 0; ww < kWaves; ++ww) {
             const float f = s_f[ww][rr];
             const float ob = s_ob[ww][rr];
-            const float4 o = reinterpret_cast<const float4 *>(s_o + (ww * kRows + rr) * kHeadDim)[d4];
+            const float *row = s_o + (ww * kRows + rr) * kCols;
+            float4 o;
+            if constexpr (A == 6) {
+                // dims 4 d4 .. + 3 lie in bytes 3 d4 .. + 2: field 0 is byte 0's
+                // low six bits; field 1 byte 0's top two (at bit 6) and byte 1's
+                // low four; field 2 byte 1's top four (at bit 4) and byte 2's low
+                // two; field 3 byte 2's top six (at bit 2)
+                const float *lo = row + 3 * d4, *hi = row + 96 + 3 * d4;
+                o = make_float4(lo[0], fmaf(hi[0], 1.0f / 64.0f, 4.0f * lo[1]),
+                                fmaf(hi[1], 1.0f / 16.0f, 4.0f * lo[2]), 0.25f * hi[2]);
+            } else {
+                o = reinterpret_cast<const float4 *>(row)[d4];
+            }
             O.x = fmaf(o.x + ob, f, O.x);
             O.y = fmaf(o.y + ob, f, O.y);
             O.z = fmaf(o.z + ob, f, O.z);
@@ -509,7 +714,7 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_kernel(SplitD
             store16_agent(pair_o, (sp * kHeadDim + 4 * d4) * 4, O);
             if (d4 == 0) store8_agent(pair_ml, sp * 8, make_float2(s_ML[rr][0], s_ML[rr][1]));
         } else {
-            const size_t pi = partial_index(row);
+            const size_t pi = partial_index(row_base + rr);
             reinterpret_cast<float4 *>(a.ws_o + pi * kHeadDim)[d4] = O;
             if (d4 == 0) a.ws_ml[pi] = make_float2(s_ML[rr][0], s_ML[rr][1]);
         }
@@ -522,56 +727,46 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_kernel(SplitD
     if (!last_to_arrive(ctr, live, &s_last)) return;
     const size_t orow0 = (size_t)b * a.Hq + (size_t)h * a.G + row_base;
     if (heads <= 4)
-        merge_pair<4>(a, pair_o, pair_ml, orow0, heads, live, s_buf);
+        merge_pair<4>(a, pair_o, pair_ml, orow0, heads, live, s_ring);
     else if (heads <= 8)
-        merge_pair<8>(a, pair_o, pair_ml, orow0, heads, live, s_buf);
+        merge_pair<8>(a, pair_o, pair_ml, orow0, heads, live, s_ring);
     else
-        merge_pair<16>(a, pair_o, pair_ml, orow0, heads, live, s_buf);
-}
-
-template <int A, int LAYOUT>
-hipError_t launch_sg(const SplitDecodeArgs &args, dim3 grid, hipStream_t stream) {
-    switch (args.groups_per_split) {
-        case 4:
-            hipLaunchKernelGGL((anchor_split_decode_kernel<A, LAYOUT, 4>), grid, dim3(kThreads), 0, stream, args);
-            break;
-        case 8:
-            hipLaunchKernelGGL((anchor_split_decode_kernel<A, LAYOUT, 8>), grid, dim3(kThreads), 0, stream, args);
-            break;
-        case 16:
-            hipLaunchKernelGGL((anchor_split_decode_kernel<A, LAYOUT, 16>), grid, dim3(kThreads), 0, stream, args);
-            break;
-        default:
-            return hipErrorInvalidValue;
-    }
-    return hipSuccess;
+        merge_pair<16>(a, pair_o, pair_ml, orow0, heads, live, s_ring);
 }
 
 template <int A>
-hipError_t launch_a(const SplitDecodeArgs &args, dim3 grid, hipStream_t stream) {
-    return args.geo.max_blocks == 1 ? launch_sg<A, 0>(args, grid, stream) : launch_sg<A, 1>(args, grid, stream);
+void launch_a(const SplitDecodeArgs &args, dim3 grid, hipStream_t stream) {
+    if (args.geo.max_blocks == 1)
+        hipLaunchKernelGGL((anchor_split_decode_kernel<A, 0>), grid, dim3(kThreads), 0, stream, args);
+    else if (args.geo.bt % 16 == 0)
+        hipLaunchKernelGGL((anchor_split_decode_kernel<A, 1>), grid, dim3(kThreads), 0, stream, args);
+    else
+        hipLaunchKernelGGL((anchor_split_decode_kernel<A, 2>), grid, dim3(kThreads), 0, stream, args);
 }
 
 }  // namespace
 
 hipError_t launch_anchor_split_decode(const SplitDecodeArgs &args, hipStream_t stream) {
-    const int chunks = (args.rows_total + kRows - 1) / kRows;
-    const dim3 grid(args.n_splits, (unsigned)(args.geo.Hkv * chunks), args.B);
-    hipError_t e;
+    // a wavefront keeps the block ids of at most 4 groups (paged layouts)
+    const bool paged = args.geo.max_blocks != 1;
+    if (args.groups_per_split < 1 || (paged && args.groups_per_split > 4 * kWaves)) return hipErrorInvalidValue;
+    if (paged && args.n_splits > 65535) return hipErrorInvalidValue;
+    const unsigned hc = (unsigned)(args.geo.Hkv * ((args.rows_total + kRows - 1) / kRows));
+    // kv head fastest for paged layouts (the kernel reads the grid the same way)
+    const dim3 grid = paged ? dim3(hc, args.n_splits, args.B) : dim3(args.n_splits, hc, args.B);
     switch (args.anchor_bits) {
         case 2:
-            e = launch_a<2>(args, grid, stream);
+            launch_a<2>(args, grid, stream);
             break;
         case 4:
-            e = launch_a<4>(args, grid, stream);
+            launch_a<4>(args, grid, stream);
             break;
         case 6:
-            e = launch_a<6>(args, grid, stream);
+            launch_a<6>(args, grid, stream);
             break;
         default:
             return hipErrorInvalidValue;
     }
-    if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 

@@ -409,6 +409,9 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
         d.anchor_bits = anchor_bits;
         d.n_splits = plan.n_ctx_splits;
         d.groups_per_split = plan.split_tokens / kKGroup;
+        d.bt_shift = -1;
+        for (int sh = 0; sh < 31; ++sh)
+            if ((1 << sh) == g.bt) d.bt_shift = sh;
         d.rows_total = plan.rows_total;
         d.ws_splits = plan.n_splits;
         d.seq_lens = seq_lens;

@@ -177,7 +177,8 @@ struct SplitDecodeArgs {
     int B, Hq, G, max_seq_len;
     int anchor_bits;      // A: 2, 4 or 6
     int n_splits;         // grid.x
-    int groups_per_split; // 4, 8 or 16
+    int groups_per_split; // 128-token groups per split; at most 16 when paged
+    int bt_shift;         // log2(block_tokens) when it is a power of two, else -1
     int rows_total;       // G query rows per (sequence, kv head)
     int ws_splits;        // partial-row stride
     const int32_t *seq_lens;

@@ -177,3 +177,39 @@ def test_split_decode_calls_share_one_workspace():
             assert np.array_equal(out.float().cpu().numpy(), fresh), (A, lens, rep)
             assert np.array_equal(lse.cpu().numpy(), fresh_lse), (A, lens, rep)
     assert int(shared[:lynx.ATTN_COUNTER_BYTES].count_nonzero()) == 0
+
+
+@pytest.mark.parametrize("A", [2, 4, 6])
+def test_split_decode_long_splits(A):
+    """A contiguous batch whose plan takes splits longer than 2048 tokens (more
+    than 512 workgroups of 2048 tokens, at most 512 of 4096): every wavefront
+    attends 8 groups and the last split is ragged.  Two (sequence, kv head) units against the oracle."""
+    lens, Hkv, G = [70001, 69000], 8, 1
+    kv = [random_kv(T, Hkv, seed=4700 + T) for T in lens]
+    lens, L, OL, table, planes, meta, op, om = encode(A, [k for k, _ in kv], [v for _, v in kv], Hkv)
+    q = random_bf16((2, Hkv * G, 128), seed=4701)
+    out, lse = decode(A, lens, L, table, planes, meta, q)
+    assert np.isfinite(out).all() and np.isfinite(lse).all()
+    mask = np.zeros((2, Hkv), np.uint8)
+    mask[0, 7] = mask[1, 2] = 1
+    check(A, lens, OL, table, op, om, q, out, lse, unit_mask=mask, what=f"A={A} long splits")
+
+
+@pytest.mark.parametrize("A", [2, 4, 6])
+@pytest.mark.parametrize("scale", [1e-30, 1e30])
+def test_split_decode_extreme_scales(A, scale):
+    """Values far from 1 (K 1e-3, V 1e30 or 1e-30, with a block of zero V rows first): the exponents that the
+    fold and the weights carry keep the fp16 operands in range.  The outputs scale with V, so the tolerance
+    does too."""
+    T, Hkv, G = 700, 2, 4
+    k, v = random_kv(T, Hkv, seed=4800)
+    v = (v.float() * scale).to(torch.bfloat16)
+    v[:40] = 0
+    k = (k.float() * 1e-3).to(torch.bfloat16)
+    lens, L, OL, table, planes, meta, op, om = encode(A, [k], [v], Hkv)
+    q = random_bf16((1, Hkv * G, 128), seed=4801)
+    out, lse = decode(A, lens, L, table, planes, meta, q)
+    ref, ref_lse = oracle.anchor_decode_split(A, OL, Hkv * G, np.array(lens, np.int32), table.numpy(), op["k_anc"],
+                                              op["v_anc"], om, bits(q))
+    assert_close(out.astype(np.float64) / scale, ref.astype(np.float64) / scale, what=f"A={A} V x{scale}")
+    np.testing.assert_allclose(lse, ref_lse, rtol=LSE_RTOL, atol=LSE_ATOL)
