@@ -547,6 +547,46 @@ def test_spec_accept_greedy(B, k, V):
     assert np.array_equal(ref_acc, cut)
 
 
+@pytest.mark.parametrize("V", [1, 3, 255, 4095, 4096, 4097, 8196])
+def test_spec_accept_greedy_edges(V):
+    """The ends of the 4096-entry chunks and of a thread's 16 scores, bit-exact:
+    the best score first, last, at a chunk's edge, tied with another chunk's
+    (the lower index wins), zeros of both signs (equal scores), minus infinity
+    beside it, and NaN, which never wins; up to 64 drafts kept."""
+    B, k = 6, 64
+    g = torch.Generator().manual_seed(V)
+    lg = torch.randn(B, k + 1, V, generator=g).clamp(-3, 3)
+    for b in range(B):
+        for i in range(k + 1):
+            spots = [0, V - 1, min(4095, V - 1), min(4096, V - 1), V // 2]
+            lg[b, i, spots[(b + i) % 5]] = 9.0
+            if b == 1:
+                lg[b, i, spots[i % 3]] = 9.0
+            if b == 2:
+                lg[b, i] = 0.0
+                lg[b, i, :: 2] = -0.0
+            if b == 3 and V > 2:
+                lg[b, i, V // 3] = float("nan")
+                lg[b, i, spots[i % 5]] = 10.0
+            if b == 4:
+                lg[b, i] = float("-inf")
+                lg[b, i, V // 2] = -50.0
+    lgn = lg.numpy()
+    lgn = np.where(np.isnan(lgn), -np.inf, lgn)  # the oracle's scores: a NaN never wins
+    drafts = lgn.argmax(axis=2)[:, :k].astype(np.int32)
+    for b in range(B):
+        if b % 2:
+            drafts[b, 7 * b % k] += 1
+    acc = torch.empty(B, dtype=torch.int32, device="cuda")
+    nxt = torch.empty(B, dtype=torch.int32, device="cuda")
+    note(f"spec_accept_greedy edges V={V}")
+    lynx.lynx_spec_accept_greedy(lg.cuda(), torch.from_numpy(drafts).cuda(), acc, nxt)
+    torch.cuda.synchronize()
+    ref_acc, ref_nxt = oracle.accept_greedy(lgn, drafts)
+    assert np.array_equal(acc.cpu().numpy(), ref_acc)
+    assert np.array_equal(nxt.cpu().numpy(), ref_nxt)
+
+
 def _sample_inputs(B, k, V, seed):
     """Target / draft distributions with drafts drawn from q, the uniforms,
     and planted edge cases: drafts outside the vocabulary, p = q rows (no
