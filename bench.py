@@ -72,7 +72,7 @@ WORKLOAD = "llama3-8b-32k"
 COPY_CALIBRATION_BYTES = 640 << 20
 TRAFFIC_SUMMARY = ROOT / "profiles" / "anchor_decode_llama3-8b-32k_traffic.md"
 # sources whose kernels make up one anchor-decode call
-DECODE_SOURCES = ["anchor_decode.hip", "split_merge.h", "attention.hip", "lynx_internal.h", "lane_ops.h"]
+DECODE_SOURCES = ["anchor_decode.hip", "work_list.h", "split_merge.h", "attention.hip", "lynx_internal.h", "lane_ops.h"]
 
 # algorithmic bytes per unit
 ENC_BYTES_PER_ELEM = 2.0 + 0.5 + 0.5 + 0.0625   # read BF16, write 2 nibbles, metadata
@@ -196,6 +196,9 @@ def _csv(dirname, suffix):
 
 
 def _short(name: str) -> str:
+    # the kernels of a batch, of a long sequence and of rows that share a
+    # workgroup, with the plain ones
+    name = name.replace("_batch_kernel", "_kernel").replace("_long_kernel", "_kernel").replace("_rows_kernel", "_kernel")
     for key in ("anchor_split_decode_kernel", "anchor_decode_kernel", "attn_combine_kernel", "verify_kernel", "encode_kernel",
                 "merge_kernel", "copyBuffer", "hencode_kernel", "hdequant_kernel",
                 "deserialize_anchor_kernel", "deserialize_residual_kernel", "merge_split_kernel",
@@ -210,8 +213,8 @@ def _short(name: str) -> str:
 
 def _variant(name: str) -> str:
     """A library kernel with its template arguments (the decode of a 32K layer,
-    anchor_decode_kernel<4, 0, 4>, and the 70B-shaped one-round decode,
-    anchor_decode_kernel<8, 0, 64>, launch the same number of work-items);
+    anchor_decode_kernel<4, 0, 4>, and the 70B-shaped one,
+    anchor_decode_batch_kernel<8, 0, 4>, launch the same number of work-items);
     any other kernel by its short name."""
     m = re.search(r"(\w+_kernel)(<[^()]*>)\(", name)
     if m and "lynx::" in name:

@@ -180,9 +180,7 @@ size_t lynx_attn_workspace_bytes(const lynx_layout *L, int32_t B, int32_t Hq,
     if (B < 0 || Hq < 1 || Hq % g.Hkv != 0 || num_queries < 1 || num_queries > 64 ||
         max_seq_len < 0)
         return 0;
-    // sized for the larger plan, the one with a draft-tail split
-    const lynx::AttnPlan p = lynx::plan_attention(g, B, Hq, num_queries, max_seq_len, true);
-    return p.workspace_bytes();
+    return lynx::attention_workspace_bound(g, B, Hq, num_queries, max_seq_len);
 }
 
 int lynx_attn_anchor_decode(const lynx_layout *L, int32_t B, int32_t Hq, int32_t max_seq_len,
@@ -197,8 +195,9 @@ int lynx_attn_anchor_decode(const lynx_layout *L, int32_t B, int32_t Hq, int32_t
     if (rc != LYNX_OK) return rc;
     if (B == 0) return LYNX_OK;
     if (lse && !aligned16(lse)) return LYNX_EINVAL;
-    const lynx::AttnPlan p = lynx::plan_attention(g, B, Hq, 1, max_seq_len, false);
-    if (!workspace || !aligned16(workspace) || workspace_bytes < p.workspace_bytes())
+    const lynx::AttnPlan p = lynx::plan_attention(lynx::KvMode::kAnchor, g, B, Hq, 1, max_seq_len);
+    if (!workspace || !aligned16(workspace) ||
+        workspace_bytes < lynx::attention_workspace_bound(g, B, Hq, 1, max_seq_len))
         return LYNX_EWORKSPACE;
     hipError_t e = lynx::launch_attention(
         lynx::KvMode::kAnchor, g, p, B, Hq, 1, max_seq_len, seq_lens, block_table, k_anc, v_anc,
@@ -221,8 +220,9 @@ int lynx_attn_anchor_decode_split(int32_t anchor_bits, const lynx_layout *L, int
     if (rc != LYNX_OK) return rc;
     if (B == 0) return LYNX_OK;
     if (lse && !aligned16(lse)) return LYNX_EINVAL;
-    const lynx::AttnPlan p = lynx::plan_attention(g, B, Hq, 1, max_seq_len, false);
-    if (!workspace || !aligned16(workspace) || workspace_bytes < p.workspace_bytes())
+    const lynx::AttnPlan p = lynx::plan_attention(lynx::KvMode::kAnchorSplit, g, B, Hq, 1, max_seq_len);
+    if (!workspace || !aligned16(workspace) ||
+        workspace_bytes < lynx::attention_workspace_bound(g, B, Hq, 1, max_seq_len))
         return LYNX_EWORKSPACE;
     hipError_t e = lynx::launch_attention(
         lynx::KvMode::kAnchorSplit, g, p, B, Hq, 1, max_seq_len, seq_lens, block_table, k_anc,
@@ -276,8 +276,9 @@ int lynx_attn_anchor_decode_noalloc(const lynx_layout *L, int32_t B, int32_t Hq,
     if (rc != LYNX_OK) return rc;
     if (B == 0) return LYNX_OK;
     if (lse && !aligned16(lse)) return LYNX_EINVAL;
-    const lynx::AttnPlan p = lynx::plan_attention(g, B, Hq, 1, max_seq_len, false);
-    if (p.workspace_bytes() > kScratchBytes) return LYNX_EWORKSPACE;
+    const lynx::AttnPlan p = lynx::plan_attention(lynx::KvMode::kAnchor, g, B, Hq, 1, max_seq_len, kScratchBytes);
+    if (lynx::decode_over_scratch(g, B, Hq, max_seq_len, kScratchBytes) || p.workspace_bytes() > kScratchBytes)
+        return LYNX_EWORKSPACE;
     void *ws = scratch_on_current_device();
     if (!ws) return LYNX_EHIP;
     hipError_t e = lynx::launch_attention(
@@ -304,8 +305,9 @@ int lynx_attn_anchor_decode_tail(const lynx_layout *L, int32_t B, int32_t Hq,
         return LYNX_EINVAL;
     if (B == 0) return LYNX_OK;
     if (lse && !aligned16(lse)) return LYNX_EINVAL;
-    const lynx::AttnPlan p = lynx::plan_attention(g, B, Hq, 1, max_seq_len, false);
-    if (!workspace || !aligned16(workspace) || workspace_bytes < p.workspace_bytes())
+    const lynx::AttnPlan p = lynx::plan_attention(lynx::KvMode::kAnchor, g, B, Hq, 1, max_seq_len);
+    if (!workspace || !aligned16(workspace) ||
+        workspace_bytes < lynx::attention_workspace_bound(g, B, Hq, 1, max_seq_len))
         return LYNX_EWORKSPACE;
     hipError_t e = lynx::launch_attention(
         lynx::KvMode::kAnchor, g, p, B, Hq, 1, max_seq_len, seq_lens, block_table, k_anc, v_anc,
@@ -330,9 +332,9 @@ int lynx_attn_verify(const lynx_layout *L, int32_t B, int32_t Hq, int32_t k,
     if ((k_new == nullptr) != (v_new == nullptr)) return LYNX_EINVAL;
     if (k_new && (!aligned16(k_new) || !aligned16(v_new))) return LYNX_EINVAL;
     if (B == 0) return LYNX_OK;
-    const bool tail = k_new != nullptr;
-    const lynx::AttnPlan p = lynx::plan_attention(g, B, Hq, k, max_seq_len, tail);
-    if (!workspace || !aligned16(workspace) || workspace_bytes < p.workspace_bytes())
+    const lynx::AttnPlan p = lynx::plan_attention(lynx::KvMode::kCodes, g, B, Hq, k, max_seq_len);
+    if (!workspace || !aligned16(workspace) ||
+        workspace_bytes < lynx::attention_workspace_bound(g, B, Hq, k, max_seq_len))
         return LYNX_EWORKSPACE;
     hipError_t e = lynx::launch_attention(
         lynx::KvMode::kCodes, g, p, B, Hq, k, max_seq_len, seq_lens, block_table, k_codes, v_codes,

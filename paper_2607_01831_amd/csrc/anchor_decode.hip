@@ -24,9 +24,11 @@
 //    the zero/centre term sum_t p_t (z_t + 7.5 s_t) is a per-head scalar and
 //    the 128 offset is measured by one extra MFMA against a constant operand.
 //
-// Work split: grid = (context split of NG 128-token groups, kv head x head
-// chunk, sequence); 4 wavefronts per workgroup, two workgroups per CU.
-// Wavefront w owns the groups w, w + 4, ... of the split: it folds each
+// Work split: grid = (worker, kv head x head chunk), as many workers as the
+// chip holds at once (two workgroups of 4 wavefronts per CU), each with an
+// equal share of the batch's 512-token units (work_list.h), a segment per
+// sequence it touches.  Wavefront w owns the groups w, w + 4, ... of a
+// segment: it folds each
 // group's K scales into its own MFMA operand lanes of the query (registers)
 // and attends the group's four 32-token tiles with its own online softmax,
 // so the loop has no barrier.  Tiles stream into a private 2-slot LDS ring
@@ -35,16 +37,18 @@
 // metadata rides with its first tile.  At the end the wavefronts are merged
 // through LDS into one partial (max, sum, output) per head.
 //
-// Split merge in the same launch: each workgroup stores its partial with
-// agent-coherent stores, waits for them and counts in on its (sequence, kv
-// head, head chunk) counter; the last to arrive merges the splits' partials,
-// writes the output and lse, and resets the counter.  A second, dependent
-// launch costs 4 us on this part (8 us while a copy engine streams the
-// residual).  With a BF16 tail the combine kernel of attention.hip merges
-// instead.
+// Split merge in the same launch: a sequence that one worker covers is written
+// by it; otherwise each workgroup stores its partial with agent-coherent
+// stores, waits for them and counts in on its (sequence, kv head, head chunk)
+// counter; the last to arrive merges the segments' partials, writes the
+// output and lse, and resets the counter.  A second, dependent launch costs
+// 4 us on this part (8 us while a copy engine streams the residual).  With a
+// BF16 tail, or more sequences than counters, the combine kernel of
+// attention.hip merges instead.
 #include "lane_ops.h"
 #include "split_merge.h"
 #include "lynx_internal.h"
+#include "work_list.h"
 
 #include <float.h>
 #include <math.h>
@@ -110,61 +114,48 @@ __device__ __forceinline__ uint32_t k_slot(int t, int q) {
 // LAYOUT 0: one block per sequence (contiguous cache, max_blocks_per_seq == 1)
 // LAYOUT 1: paged, block_tokens a multiple of 16 (a 16-token run is in one block)
 // LAYOUT 2: any other paging (per-token block lookups)
-// GP: heads per chunk, padded (4, 8 or 16); NG: 128-token groups per split.
-template <int GP, int LAYOUT, int NG>
-__global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a) {
-    constexpr int kMaxGroups = NG / kWaves;  // groups per wavefront
-    static_assert(NG % kWaves == 0, "groups must split evenly over the wavefronts");
+// GP: heads per chunk, padded (4, 8 or 16); UNIT: 128-token groups per unit of
+// the work list.
+// One segment of a worker's share, for kv head h and a chunk of query heads.
+// ONE: the segment is a single unit, a group per wavefront.
+template <int GP, int LAYOUT, int UNIT, bool ONE>
+__device__ __forceinline__ void attend_segment(const DecodeArgs &a, const Segment<UNIT> &seg, int h, int chunk,
+                                               const int tid) {
+    static_assert(UNIT == kWaves, "a group per wavefront and unit");
     const int Hkv = a.geo.Hkv;
-    // Grid (split, kv head x chunk, sequence) for the contiguous layout.  A
-    // paged block holds the rows of every kv head for its tokens side by side,
-    // so paged layouts make the kv head the fastest grid index: workgroups
-    // reading the same blocks run together and share DRAM pages.
-    const int split = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
-    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
-    const int h = hc % Hkv;
-    const int chunk = hc / Hkv;
-    const int b = blockIdx.z;
-    const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = tid >> 6;
     const int col = lane & 15;  // MFMA column (head) / 16-lane row index
     const int kg = lane >> 4;   // MFMA row group
     const int heads = min(a.chunk_heads, a.G - chunk * a.chunk_heads);
-    const int T = max(0, min(a.seq_lens[b], a.max_seq_len));
-    const int g0 = split * NG;
-    // groups of this split that hold tokens (uniform across the workgroup)
-    const int n_groups = max(0, min(NG, (T - g0 * kKGroup + kKGroup - 1) / kKGroup));
+    const int b = seg.b, T = seg.T, g0 = seg.g0, n_groups = seg.n_groups, live = seg.live;
     const size_t q_row0 = (size_t)b * a.Hq + (size_t)h * a.G + (size_t)chunk * a.chunk_heads;
-
-    // splits holding tokens (one for an empty sequence)
-    const int live = max(1, (T + NG * kKGroup - 1) / (NG * kKGroup));
-    if (a.fused && split >= live) return;  // nothing to attend, nothing to merge
-    if (n_groups == 0 && a.fused) {
-        // split 0 of an empty sequence: zero output, lse -inf
-        const size_t orow0 = (size_t)b * a.Hq + (size_t)h * a.G + (size_t)chunk * a.chunk_heads;
-        for (int idx = tid; idx < heads * (kHeadDim / 4); idx += kThreads)
-            *reinterpret_cast<uint2 *>(a.out + (orow0 + idx / (kHeadDim / 4)) * kHeadDim +
-                                       4 * (idx % (kHeadDim / 4))) = make_uint2(0u, 0u);
-        if (a.lse && tid < heads) a.lse[orow0 + tid] = -INFINITY;
-        return;
-    }
+    // the chunk's partials: rows chunk * chunk_heads .. of kv head h, segments
+    // seg.number0 .. + live - 1 of sequence b
+    const size_t prow0 = (size_t)h * a.rows_total + (size_t)chunk * a.chunk_heads;
     if (n_groups == 0) {
-        // a split past the context: (max, sum) = (-inf, 0), no output
-        for (int hh = tid; hh < heads; hh += kThreads) {
-            const size_t pi =
-                (((size_t)b * Hkv + h) * a.rows_total + chunk * a.chunk_heads + hh) * a.ws_splits + split;
-            a.ws_ml[pi] = make_float2(-INFINITY, 0.0f);
+        // an empty sequence: zero output, lse -inf; or, for the combine kernel,
+        // (max, sum) = (-inf, 0)
+        if (a.fused) {
+            for (int idx = tid; idx < heads * (kHeadDim / 4); idx += kThreads)
+                *reinterpret_cast<uint2 *>(a.out + (q_row0 + idx / (kHeadDim / 4)) * kHeadDim +
+                                           4 * (idx % (kHeadDim / 4))) = make_uint2(0u, 0u);
+            if (a.lse && tid < heads) a.lse[q_row0 + tid] = -INFINITY;
+        } else if (tid < heads) {
+            a.ws_ml[(prow0 + tid) * a.n_seg + seg.number] = make_float2(-INFINITY, 0.0f);
         }
         return;
     }
 
-    // LDS: 39-43 KB, two workgroups per CU; the epilogue reuses the ring
+    // LDS: 40-44 KB, two workgroups per CU; the epilogue reuses the ring
     __shared__ __attribute__((aligned(16))) uint8_t s_ring[kWaves * kDepth * kSlotBytes];
     __shared__ __attribute__((aligned(16))) uint8_t s_km[kWaves][kKMetaBytes];
     __shared__ __attribute__((aligned(16))) uint8_t s_q[GP * kHeadDim * 2];  // BF16 query rows
     static_assert((kWaves * GP * (kHeadDim + 4) + 2 * GP) * 4 <= kWaves * kDepth * kSlotBytes,
                   "the epilogue's arrays must fit in the ring");
+    // LAYOUT 1: the blocks of a group's eight 16-token runs, for two groups
+    __shared__ int32_t s_ids[LAYOUT == 1 ? kWaves : 1][2][8];
+    __shared__ int s_last;
 
     bool bad = false;
     const int32_t *bt_row = a.block_table + (size_t)b * a.geo.max_blocks;
@@ -188,7 +179,7 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a
 
     // This wavefront's tiles: tile j is tile j % 4 of its group j / 4, the
     // split's group w + 4 (j / 4).
-    const int n_mine = n_groups > w ? (n_groups - w + kWaves - 1) / kWaves : 0;
+    const int n_mine = ONE ? (n_groups > w ? 1 : 0) : n_groups > w ? (n_groups - w + kWaves - 1) / kWaves : 0;
     auto tile_t0 = [&](int j) { return (g0 + w + kWaves * (j >> 2)) * kKGroup + kTile * (j & 3); };
     auto tile_valid = [&](int j) { return (j >> 2) < n_mine && tile_t0(j) < T; };
 
@@ -202,30 +193,26 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a
     const uint32_t ring = lds_addr(s_ring) + (uint32_t)w * kDepth * kSlotBytes;
     const uint8_t *ring_p = s_ring + (size_t)w * kDepth * kSlotBytes;
     const uint32_t km = lds_addr(&s_km[w][0]);
-    // copies per tile: 2 K + 2 V + 1 V metadata, + 1 K metadata (into the
-    // wavefront's K-metadata buffer) for a group's first tile
+    // copies per tile: 2 K + 2 V + 1 V metadata; with a group's first tile
+    // also its K metadata (into the wavefront's K-metadata buffer) and, for
+    // LAYOUT 1, the next group's block ids
 
-    // LAYOUT 1: the block of every 16-token run the wavefront attends (lane
-    // 8 u + r: run r of its group u), looked up once before any copy is in
-    // flight; a full tile's copies then take their blocks by readlane
-    // instead of waiting on a block-table load each.  Lanes past the
-    // wavefront's groups read a clamped, unused entry.
-    int run_blk = 0;
-    if (LAYOUT == 1) {
-        const int u = lane >> 3;
-        if (u < kMaxGroups) {
-            const int tr = (g0 + w + kWaves * u) * kKGroup + 16 * (lane & 7);
-            const int bi = a.bt_shift >= 0 ? (tr >> a.bt_shift) : tr / a.geo.bt;
-            run_blk = bt_row[min(bi, a.geo.max_blocks - 1)];
-        }
-        // the compiler places its wait for the load before this use: ahead of
-        // every copy, whose waits it does not see
-        asm volatile("" : "+v"(run_blk));
-    }
+    // LAYOUT 1: the blocks of the wavefront's group u, run r in lane r, into
+    // s_ids, one group ahead of its tiles, whose copies then take them by readlane
+    // instead of waiting on a block-table load each.  Past the
+    // wavefront's groups the entries are clamped and unused.
+    auto issue_ids = [&](int u) {
+        if (LAYOUT != 1) return;
+        const int tr = (g0 + w + kWaves * u) * kKGroup + 16 * lane;
+        const int bi = a.bt_shift >= 0 ? (tr >> a.bt_shift) : tr / a.geo.bt;
+        if (lane < 8) lds_copy4(bt_row + min(bi, a.geo.max_blocks - 1), lds_addr(&s_ids[LAYOUT == 1 ? w : 0][u & 1][0]));
+    };
 
     // Tile j of this wavefront into ring slot j % kDepth.
+    int ids = 0;  // LAYOUT 1: block ids of the group being issued, run r in lane r
     auto issue_tile = [&](int j) {
         const int t0 = __builtin_amdgcn_readfirstlane(tile_t0(j));
+        if (LAYOUT == 1 && (j & 3) == 0) ids = s_ids[LAYOUT == 1 ? w : 0][(j >> 2) & 1][lane & 7];
         const uint32_t slot = ring + (uint32_t)(j % kDepth) * kSlotBytes;
         if (LAYOUT != 2 && t0 + kTile <= T) {
             // two 16-token runs, each inside one block
@@ -238,7 +225,7 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a
                     const int tr = t0 + 16 * i;
                     const int bi = a.bt_shift >= 0 ? (tr >> a.bt_shift) : tr / a.geo.bt;
                     // run 2 (j % 4) + i of the wavefront's group j / 4
-                    int blk = __builtin_amdgcn_readlane(run_blk, 8 * (j >> 2) + 2 * (j & 3) + i);
+                    int blk = __builtin_amdgcn_readlane(ids, 2 * (j & 3) + i);
                     if (blk < 0 || blk >= a.geo.num_blocks) {
                         bad = true;
                         blk = 0;
@@ -271,6 +258,7 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a
             const int g = g0 + min(w + kWaves * (j >> 2), n_groups - 1);
             const float *src = (lane < 32 ? a.meta.k_scale : a.meta.k_zero) + kmeta + (size_t)g * kHeadDim;
             lds_copy16(src + 4 * (lane & 31), km);
+            if (!ONE && n_mine > 1) issue_ids((j >> 2) + 1);  // (a wavefront's only group has no next)
         }
     };
 
@@ -434,14 +422,18 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a
     // Weights of later, larger scores exceed 1; if any sum leaves the safe
     // range the wavefront redoes its tiles below with a running maximum.
     // The next tile is in flight while one is attended; no barriers.
-    // copies of a tile at position c of its group: 5, and 6 for a group's first
-    auto copies_at = [](int c) { return (c & 3) == 0 ? 6 : 5; };
+    // copies of a tile at position c of its group
+    auto copies_at = [](int c) { return (c & 3) == 0 ? (LAYOUT == 1 ? 7 : 6) : 5; };
     static_assert(kDepth - 1 <= 4, "the ring reaches at most into the next group");
+    if (LAYOUT == 1) {
+        issue_ids(0);
+        wait_vmcnt<0>();
+    }
     if (n_mine > 0) {
 #pragma unroll
         for (int c = 0; c < kDepth - 1; ++c) issue_tile(c);  // all in the first group
     }
-    if (w == 0) {
+    if (LAYOUT != 1 && w == 0) {  // LAYOUT 1 waited for everything above
         // the query rows are in once only the first tiles' copies remain
         int later = 0;
 #pragma unroll
@@ -450,9 +442,8 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a
     }
     __syncthreads();  // the query rows are visible to every wavefront
     load_query();
-    for (int u = 0; u < kMaxGroups; ++u) {
-        if (u >= n_mine) break;  // wavefront-uniform
-        const bool next_group = u + 1 < n_mine;
+    for (int u = 0; u < (ONE ? min(n_mine, 1) : n_mine); ++u) {
+        const bool next_group = !ONE && u + 1 < n_mine;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int j = 4 * u + c;
@@ -495,6 +486,8 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a
         // Slow path (this wavefront only): running maximum with rescaling,
         // one tile fetched and waited for at a time.
         reset_state();
+        issue_ids(0);
+        wait_vmcnt<0>();
         for (int j = 0; j < 4 * n_mine; ++j) {
             issue_tile(j);
             wait_vmcnt<0>();
@@ -575,11 +568,11 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a
         s_ML[hh][1] = any_bad ? NAN : L;
     }
     __syncthreads();
-    // the pair's partials: rows chunk * chunk_heads .. + heads - 1 of (b, h)
-    const size_t prow0 = ((size_t)b * Hkv + h) * a.rows_total + (size_t)chunk * a.chunk_heads;
-    const __amdgpu_buffer_rsrc_t pair_o =
-        buffer_rsrc(a.ws_o + prow0 * a.ws_splits * kHeadDim, (uint32_t)heads * a.ws_splits * kHeadDim * 4);
-    const __amdgpu_buffer_rsrc_t pair_ml = buffer_rsrc(a.ws_ml + prow0 * a.ws_splits, (uint32_t)heads * a.ws_splits * 8);
+    const size_t pseg0 = prow0 * a.n_seg + seg.number0;
+    const uint32_t prows = (uint32_t)(heads - 1) * a.n_seg + live;  // from the first row's first segment
+    const __amdgpu_buffer_rsrc_t pair_o = buffer_rsrc(a.ws_o + pseg0 * kHeadDim, prows * kHeadDim * 4);
+    const __amdgpu_buffer_rsrc_t pair_ml = buffer_rsrc(a.ws_ml + pseg0, prows * 8);
+    const bool merge = a.fused && live > 1;
     for (int idx = tid; idx < heads * (kHeadDim / 4); idx += kThreads) {
         const int hh = idx / (kHeadDim / 4);
         const int d4 = idx % (kHeadDim / 4);
@@ -595,77 +588,109 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a
             O.w = fmaf(o.w + ob, f, O.w);
         }
         if (any_bad) O = make_float4(NAN, NAN, NAN, NAN);
-        const int gr = chunk * a.chunk_heads + hh;  // row = head within the kv group
-        const size_t pi = (((size_t)b * Hkv + h) * a.rows_total + gr) * a.ws_splits + split;
-        if (a.fused) {
-            const uint32_t sp = (uint32_t)hh * a.ws_splits + split;  // within the pair's rows
+        if (merge) {
+            const uint32_t sp = (uint32_t)hh * a.n_seg + (seg.number - seg.number0);
             store16_agent(pair_o, (sp * kHeadDim + 4 * d4) * 4, O);
             if (d4 == 0) store8_agent(pair_ml, sp * 8, make_float2(s_ML[hh][0], s_ML[hh][1]));
+        } else if (a.fused) {  // the whole sequence is this worker's
+            write_row4(a.out, a.lse, q_row0 + hh, d4, O, s_ML[hh][0], s_ML[hh][1]);
         } else {
+            const size_t pi = (prow0 + hh) * a.n_seg + seg.number;
             reinterpret_cast<float4 *>(a.ws_o + pi * kHeadDim)[d4] = O;
             if (d4 == 0) a.ws_ml[pi] = make_float2(s_ML[hh][0], s_ML[hh][1]);
         }
     }
-    if (!a.fused) return;
+    if (!merge) return;
 
     // ---- fused merge: count in; the pair's last workgroup merges ----
-    __shared__ int s_last;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's partial stores are done
-    __syncthreads();                                    // ... and every other thread's
     unsigned *ctr = a.counters + (((size_t)b * Hkv + h) * a.row_chunks + chunk) * kCounterStride;
-    if (tid == 0)
-        s_last = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                 (unsigned)(live - 1);
-    __syncthreads();
-    if (!s_last) return;
-    if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const size_t orow0 = (size_t)b * a.Hq + (size_t)h * a.G + (size_t)chunk * a.chunk_heads;
-    merge_pair<GP>(a, pair_o, pair_ml, orow0, heads, live, s_ring);
+    if (last_to_arrive(ctr, live, &s_last)) merge_pair<GP>(a, pair_o, pair_ml, q_row0, heads, live, s_ring);
 }
 
-template <int LAYOUT, int NG>
+// Grid (worker, kv head x chunk) for the contiguous layout.  A paged block
+// holds the rows of every kv head for its tokens side by side, so paged
+// layouts make the kv head the fastest grid index: workgroups reading the
+// same blocks run together and share DRAM pages.
+template <int GP, int LAYOUT, int UNIT>
+__global__ __launch_bounds__(kThreads, 2) void anchor_decode_batch_kernel(DecodeArgs a) {
+    const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
+    const WorkList<UNIT, true> list(a.seq_lens, a.B, a.max_seq_len, a.workers);
+    if (worker >= list.workers) return;
+    Segment<UNIT> seg;
+    seg.start(list, worker);
+    for (;;) {
+        attend_segment<GP, LAYOUT, UNIT, false>(a, seg, fresh_uniform(hc % a.geo.Hkv), fresh_uniform(hc / a.geo.Hkv), fresh_tid());
+        if (!seg.next(list, worker)) return;
+        __syncthreads();  // the segment's LDS is free again
+    }
+}
+
+// A single sequence: one segment per worker, no walk.
+template <int GP, int LAYOUT, int UNIT>
+__global__ __launch_bounds__(kThreads, 2) void anchor_decode_long_kernel(DecodeArgs a) {
+    const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
+    const WorkList<UNIT, false> list(a.seq_lens, 1, a.max_seq_len, a.workers);
+    if (worker >= list.workers) return;
+    Segment<UNIT> seg;
+    seg.start(list, worker);
+    attend_segment<GP, LAYOUT, UNIT, false>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
+}
+
+// A single sequence of no more units than workers: unit p is worker p's.  The
+// short call is all latency (32K layer: 14.0 us, 14.3 through the long kernel,
+// 14.7 through the batch's, whose start waits for its arguments in turn).
+template <int GP, int LAYOUT, int UNIT>
+__global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a) {
+    const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
+    const WorkList<UNIT, false> list(a.seq_lens, 1, a.max_seq_len, a.workers);
+    if (worker >= list.total) return;
+    Segment<UNIT> seg;
+    seg.b = 0;
+    seg.T = list.only;
+    seg.g0 = worker * UNIT;
+    seg.n_groups = max(0, min(UNIT, (seg.T + kKGroup - 1) / kKGroup - seg.g0));
+    seg.number = worker;
+    seg.number0 = 0;
+    seg.live = list.total;
+    attend_segment<GP, LAYOUT, UNIT, true>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
+}
+
+template <int GP, int LAYOUT>
+void launch_gp(const DecodeArgs &args, dim3 grid, hipStream_t stream) {
+    if (args.B > 1)
+        hipLaunchKernelGGL((anchor_decode_batch_kernel<GP, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+    else if ((long long)args.workers * kWorkUnit * kKGroup < args.max_seq_len)
+        hipLaunchKernelGGL((anchor_decode_long_kernel<GP, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+    else
+        hipLaunchKernelGGL((anchor_decode_kernel<GP, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+}
+
+template <int GP>
 void launch_layout(const DecodeArgs &args, dim3 grid, hipStream_t stream) {
-    if (args.chunk_heads <= 4) {
-        hipLaunchKernelGGL((anchor_decode_kernel<4, LAYOUT, NG>), grid, dim3(kThreads), 0, stream, args);
-    } else if (args.chunk_heads <= 8) {
-        hipLaunchKernelGGL((anchor_decode_kernel<8, LAYOUT, NG>), grid, dim3(kThreads), 0, stream, args);
-    } else {
-        hipLaunchKernelGGL((anchor_decode_kernel<16, LAYOUT, NG>), grid, dim3(kThreads), 0, stream, args);
-    }
-}
-
-template <int NG>
-void launch_groups(const DecodeArgs &args, dim3 grid, hipStream_t stream) {
-    if (args.geo.max_blocks == 1) {
-        launch_layout<0, NG>(args, grid, stream);
-    } else if (args.geo.bt % 16 == 0) {
-        launch_layout<1, NG>(args, grid, stream);
-    } else {
-        launch_layout<2, NG>(args, grid, stream);
-    }
+    if (args.geo.max_blocks == 1)
+        launch_gp<GP, 0>(args, grid, stream);
+    else if (args.geo.bt % 16 == 0)
+        launch_gp<GP, 1>(args, grid, stream);
+    else
+        launch_gp<GP, 2>(args, grid, stream);
 }
 
 }  // namespace
 
 hipError_t launch_anchor_decode_mfma(const DecodeArgs &args, int chunks, hipStream_t stream) {
     // kv head fastest for paged layouts (the kernel reads the grid the same way)
-    if (args.geo.max_blocks != 1 && args.n_splits > 65535) return hipErrorInvalidValue;
+    if (args.workers < 1 || args.workers > 65535) return hipErrorInvalidValue;
     const unsigned hc = (unsigned)(args.geo.Hkv * chunks);
-    const dim3 grid = args.geo.max_blocks == 1 ? dim3(args.n_splits, hc, args.B) : dim3(hc, args.n_splits, args.B);
-    if (args.groups_per_split == 4) {
-        launch_groups<4>(args, grid, stream);
-    } else if (args.groups_per_split == 8) {
-        launch_groups<8>(args, grid, stream);
-    } else if (args.groups_per_split == 16) {
-        launch_groups<16>(args, grid, stream);
-    } else if (args.groups_per_split == 32 && args.geo.max_blocks == 1) {
-        // the long splits of one-round contiguous batches (plan_attention)
-        launch_layout<0, 32>(args, grid, stream);
-    } else if (args.groups_per_split == 64 && args.geo.max_blocks == 1) {
-        launch_layout<0, 64>(args, grid, stream);
-    } else {
-        return hipErrorInvalidValue;
-    }
+    const dim3 grid = args.geo.max_blocks == 1 ? dim3(args.workers, hc) : dim3(hc, args.workers);
+    if (args.chunk_heads <= 4)
+        launch_layout<4>(args, grid, stream);
+    else if (args.chunk_heads <= 8)
+        launch_layout<8>(args, grid, stream);
+    else
+        launch_layout<16>(args, grid, stream);
     return hipGetLastError();
 }
 

@@ -22,8 +22,8 @@
 // spread; plain values 1.0e-7).  So every field's top bit is put at bit 7 or
 // above.  The position's factor 2^sh is a
 // constant of the dimension, so on the K side it is folded into the query
-// (y_d = q_d s_d 2^(-sh) 2^(-E), with the K scale; fp16 hi + lo, |y| < 2^15,
-// E per group and row), and on the V side into the output's scale at the end.
+// (y_d = q'_d s_d 2^(15 - Es - sh), with the K scale; fp16 hi + lo, |y| < 2^15,
+// Es the exponent of the group's largest scale), and on the V side into the output's scale at the end.
 // V is read transposed by bytes (ds_read_b64_tr_b8): a byte of the plane holds
 // the same 4 (A = 2) or 2 (A = 4) dimensions for every token.  For A = 6 a
 // byte holds the end of one field and the start of another, which part being
@@ -33,26 +33,27 @@
 // The first form (bytes built from the fields, fp16 values 1024 + a less
 // 1024) spent about 1,100 instructions on a 32-token tile: a paged batch of 16
 // sequences of 4K-32K tokens took 207 us with 2-bit anchors, six times the
-// time of its bytes; now 69 us (6-bit anchors, a batch of 16K-64K: 296 -> 187).
+// time of its bytes; now 65 us (6-bit anchors, a batch of 16K-64K: 296 -> 178).
 // The V scale rides on the softmax weight, pw_t = p_t s_t 2^-Ev in fp16 (Ev
 // per wavefront from the largest V scale of its tokens), z' is summed in fp32.
 //
-// Work split: grid = (context split, kv head x chunk of 16 query heads,
-// sequence), the kv head fastest for paged layouts; 4 wavefronts per
-// workgroup, two workgroups per CU, wavefront w owning the split's groups
-// w, w + 4, ... (2-bit anchors: three per CU, since a tile is little work for
-// its waits; the batch above 80 -> 69 us).  As in the 4-bit decode the 32-token tiles stream into a
-// private LDS ring by global-to-LDS copies, each with its V metadata, a group's
-// K metadata with its first tile; the softmax reference is the maximum of the
+// Work split: as in the 4-bit decode, grid = (worker, kv head x chunk of 16
+// query heads), the kv head fastest for paged layouts, each worker with an
+// equal share of the batch's 512-token units (work_list.h); 4 wavefronts per
+// workgroup, two workgroups per CU, wavefront w owning a segment's groups w,
+// w + 4, ...  The 32-token tiles stream into a private
+// LDS ring by global-to-LDS copies, each with its V metadata, a group's K
+// metadata with its first tile; the softmax reference is the maximum of the
 // wavefront's first tile, and a wavefront whose sums leave the safe range
 // redoes its tiles with a running maximum.  The four wavefronts merge through
-// LDS into one partial per split.  When the grid runs in one round the last
-// workgroup of each (sequence, kv head, row chunk) merges the splits in the
-// same launch; otherwise the combine kernel merges them.
+// LDS into one partial per segment, and the last workgroup of a (sequence, kv
+// head, row chunk) merges those in the same launch; the combine kernel where
+// there are more sequences than counters.
 #include "f16_ops.h"
 #include "lane_ops.h"
 #include "lynx_internal.h"
 #include "split_merge.h"
+#include "work_list.h"
 
 #include <math.h>
 
@@ -74,6 +75,12 @@ template <int A>
 struct KPlace {
     static constexpr int kApart = A == 4 ? 4 : 8;
     static constexpr int first(int kk, int p) { return A == 4 ? 8 * kk + p : 16 * (kk >> 1) + 4 * (kk & 1) + p; }
+    static constexpr int shift_of(int d) {  // of dimension d
+        for (int kk = 0; kk < 4; ++kk)
+            for (int p = 0; p < 4; ++p)
+                if (first(kk, p) == d || first(kk, p) + kApart == d) return shift(kk, p);
+        return 0;
+    }
     static constexpr int shift(int kk, int p) {
         const int j = 4 * (kk & 1) + p;  // field of its half (A = 2), of its 48 bits (A = 6)
         if (A == 2) return j == 2 || j == 4 || j == 6 || j == 7 ? 8 : 6;
@@ -138,8 +145,11 @@ struct Ring {
 
 // LAYOUT 0: one block per sequence (contiguous); 1: paged, block_tokens a
 // multiple of 16; 2: any other paging.
-template <int A, int LAYOUT>
-__global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_kernel(SplitDecodeArgs a) {
+// One segment of a worker's share, for kv head h and a chunk of 16 query rows.
+template <int A, int LAYOUT, int UNIT>
+__device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const Segment<UNIT> &seg, int h, int chunk,
+                                               const int tid) {
+    static_assert(UNIT == kWaves, "a group per wavefront and unit");
     using RG = Ring<A>;
     using KP = KPlace<A>;
     constexpr int R = 8 - A;
@@ -150,40 +160,27 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
     constexpr int kCols = 16 * kAcc;            // output columns before parts are added
     constexpr float centre = (float)((1 << R) - 1) * 0.5f;
     const int Hkv = a.geo.Hkv;
-    const int split = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
-    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
-    const int h = hc % Hkv;
-    const int chunk = hc / Hkv;
-    const int b = blockIdx.z;
-    const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = tid >> 6;
     const int col = lane & 15;
     const int kg = lane >> 4;
-    const int T = max(0, min(a.seq_lens[b], a.max_seq_len));
-    const int SG = a.groups_per_split;
-    const int g0 = split * SG;
-    const int n_groups = max(0, min(SG, (T - g0 * kKGroup + kKGroup - 1) / kKGroup));
+    const int b = seg.b, T = seg.T, g0 = seg.g0, n_groups = seg.n_groups, live = seg.live;
     const int row_base = chunk * kRows;
     const float kscore = kLog2e * rsqrtf((float)kHeadDim);
-    auto partial_index = [&](int r) {
-        return (((size_t)b * Hkv + h) * a.rows_total + r) * a.ws_splits + split;
-    };
     const int heads = min(kRows, a.rows_total - row_base);  // live query rows of the chunk
-    // splits holding tokens (one for an empty sequence)
-    const int live = max(1, (T + SG * kKGroup - 1) / (SG * kKGroup));
-    if (a.fused && split >= live) return;  // nothing to attend, nothing to merge
+    const size_t orow0 = (size_t)b * a.Hq + (size_t)h * a.G + row_base;
+    const size_t prow0 = (size_t)h * a.rows_total + row_base;
     if (n_groups == 0) {
-        if (a.fused) {  // split 0 of an empty sequence: zero output, lse -inf
-            const size_t orow0 = (size_t)b * a.Hq + (size_t)h * a.G + row_base;
+        // an empty sequence: zero output, lse -inf; or, for the combine kernel,
+        // (max, sum) = (-inf, 0)
+        if (a.fused) {
             for (int idx = tid; idx < heads * (kHeadDim / 4); idx += kThreads)
                 *reinterpret_cast<uint2 *>(a.out + (orow0 + idx / (kHeadDim / 4)) * kHeadDim +
                                            4 * (idx % (kHeadDim / 4))) = make_uint2(0u, 0u);
             if (a.lse && tid < heads) a.lse[orow0 + tid] = -INFINITY;
-            return;
+        } else if (tid < heads) {
+            a.ws_ml[(prow0 + tid) * a.n_seg + seg.number] = make_float2(-INFINITY, 0.0f);
         }
-        // a split past the context: (max, sum) = (-inf, 0)
-        if (tid < heads) a.ws_ml[partial_index(row_base + tid)] = make_float2(-INFINITY, 0.0f);
         return;
     }
 
@@ -191,11 +188,15 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
     constexpr int kRingBytes = kWaves * kDepth * RG::kSlot;
     __shared__ __attribute__((aligned(16))) uint8_t s_ring[kRingBytes];
     __shared__ __attribute__((aligned(16))) uint8_t s_km[kWaves][kKMetaBytes];
-    __shared__ __attribute__((aligned(16))) uint8_t s_q[kRows * kHeadDim * 2];
+    __shared__ __attribute__((aligned(16))) uint8_t s_q[kRows * kHeadDim * 2];  // fp16 rows q'
+    __shared__ int s_eq[kRows];                                                 // and their exponents Eq
     __shared__ int s_ev[kWaves];
     __shared__ float s_ML[kRows][2];
     static_assert((kWaves * kRows * kCols + 4 * kWaves * kRows) * 4 <= kRingBytes,
                   "the epilogue's arrays must fit in the ring");
+    // LAYOUT 1: the blocks of a group's eight 16-token runs, for two groups
+    __shared__ int32_t s_ids[LAYOUT == 1 ? kWaves : 1][2][8];
+    __shared__ int s_last;
 
     bool bad = false;
     const int32_t *bt_row = a.block_table + (size_t)b * a.geo.max_blocks;
@@ -222,33 +223,20 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
     auto tile_t0 = [&](int j) { return (g0 + w + kWaves * (j >> 2)) * kKGroup + kTile * (j & 3); };
     auto tile_valid = [&](int j) { return (j >> 2) < n_mine && tile_t0(j) < T; };
 
-    // ---- plain loads, all issued before the first copy ----
-    // The query rows (16 threads per 256-byte row; rows past the chunk's heads
-    // repeat the last), the V scales of the wavefront's tokens (for Ev) and,
-    // for LAYOUT 1, the block of every 16-token run the wavefront attends
-    // (lane 8 u + r: run r of its group u; at most 4 groups).
+    // ---- plain loads, all issued before the first copy: the query rows (16
+    // threads per 256-byte row; rows past the chunk's heads repeat the last)
+    // and the V scales of the wavefront's first group, for Ev ----
     uint4 q4;
     {
         const int hh = min(row_base + (tid >> 4), a.rows_total - 1);
         const size_t qrow = (size_t)b * a.Hq + (size_t)h * a.G + hh;
         q4 = reinterpret_cast<const uint4 *>(a.q + qrow * kHeadDim)[tid & 15];
     }
-    int run_blk = 0;
-    if (LAYOUT == 1) {
-        const int u = min(lane >> 3, 3);
-        const int tr = (g0 + w + kWaves * u) * kKGroup + 16 * (lane & 7);
-        const int bi = a.bt_shift >= 0 ? (tr >> a.bt_shift) : tr / a.geo.bt;
-        run_blk = bt_row[min(bi, a.geo.max_blocks - 1)];
-    }
     auto v_scale_at = [&](int u, int k) {
         const int t = (g0 + w + kWaves * u) * kKGroup + 64 * k + lane;
         return u < n_mine && t < T ? a.meta.v_scale[vmeta + t] : 0.0f;
     };
-    float vmx[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) vmx[i] = v_scale_at(i >> 1, i & 1);
-    float vm = 0.0f;
-    for (int u = 4; u < n_mine; ++u) vm = fmax2(vm, fmax2(v_scale_at(u, 0), v_scale_at(u, 1)));
+    const float vs_first[2] = {v_scale_at(0, 0), v_scale_at(0, 1)};
 
     // ---- copies into the ring ----
     // Lane l of copy i fills 16-byte slot 64 i + l of the plane's tile: row
@@ -267,9 +255,20 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
         vq[i] = 16u * (uint32_t)(pq ^ RG::v_swizzle(crow[i]));
     }
 
+    // LAYOUT 1: the blocks of the wavefront's group u, run r in lane r, into
+    // s_ids, one group ahead of its tiles.  Past the wavefront's groups the
+    // entries are clamped and unused.
+    auto issue_ids = [&](int u) {
+        if (LAYOUT != 1) return;
+        const int tr = (g0 + w + kWaves * u) * kKGroup + 16 * lane;
+        const int bi = a.bt_shift >= 0 ? (tr >> a.bt_shift) : tr / a.geo.bt;
+        if (lane < 8) lds_copy4(bt_row + min(bi, a.geo.max_blocks - 1), lds_addr(&s_ids[LAYOUT == 1 ? w : 0][u & 1][0]));
+    };
     // Tile j of this wavefront into ring slot j % kDepth.
+    int ids = 0;  // LAYOUT 1: block ids of the group being issued, run r in lane r
     auto issue_tile = [&](int j) {
         const int t0 = __builtin_amdgcn_readfirstlane(tile_t0(j));
+        if (LAYOUT == 1 && (j & 3) == 0) ids = s_ids[LAYOUT == 1 ? w : 0][(j >> 2) & 1][lane & 7];
         const uint32_t slot = ring + (uint32_t)(j % kDepth) * RG::kSlot;
         if (LAYOUT == 0 && t0 + kTile <= T) {
             const size_t rb = (blk0_rows + (size_t)t0) * RG::kRow;
@@ -287,7 +286,7 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
             for (int r = 0; r < 2; ++r) {
                 const int tr = t0 + 16 * r;
                 const int bi = a.bt_shift >= 0 ? (tr >> a.bt_shift) : tr / a.geo.bt;
-                int blk = __builtin_amdgcn_readlane(run_blk, 8 * (j >> 2) + 2 * (j & 3) + r);
+                int blk = __builtin_amdgcn_readlane(ids, 2 * (j & 3) + r);
                 if (blk < 0 || blk >= a.geo.num_blocks) {
                     bad = true;
                     blk = 0;
@@ -321,6 +320,7 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
             const int g = g0 + min(w + kWaves * (j >> 2), n_groups - 1);
             const float *src = (lane < 32 ? a.meta.k_scale : a.meta.k_zero) + kmeta + (size_t)g * kHeadDim;
             lds_copy16(src + 4 * (lane & 31), km);
+            if (n_mine > 1) issue_ids((j >> 2) + 1);  // (a wavefront's only group has no next)
         }
     };
     static_assert(kDepth - 1 < 4, "a group's K metadata may not arrive before the last group's fold");
@@ -330,22 +330,40 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
             for (int c = 0; c < kDepth - 1; ++c) issue_tile(c);  // all in the first group
         }
     };
-    // The block ids are needed first where there are any; elsewhere the first
-    // tiles go out before the plain loads above are waited for.
-    if (LAYOUT == 1)
-        asm volatile("" : "+v"(run_blk));
+    // The first group's block ids are needed before its tiles; elsewhere the
+    // first tiles go out before the plain loads above are waited for.
+    if (LAYOUT == 1) {
+        issue_ids(0);
+        wait_vmcnt<0>();
+    }
     issue_first();
 
+    // The exponent of the largest V scale, from the wavefront's first group: a
+    // later, larger one gives weights above 1, and past the fp16 range an
+    // infinity that sends the wavefront to the slow path, which looks at all
+    // of its scales, as does a first group without any.
     int Ev = 0;
-    {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) vm = fmax2(vm, vmx[i]);
+    auto set_ev = [&](float vm) {
         vm = max_kg(row16_max(vm));
+        Ev = 0;
         if (vm > 0.0f) frexpf(vm, &Ev);
         Ev = max(Ev, -100);
+        return vm > 0.0f;
+    };
+    auto set_ev_all = [&]() {
+        float vm = 0.0f;
+        for (int u = 0; u < n_mine; ++u) vm = fmax2(vm, fmax2(v_scale_at(u, 0), v_scale_at(u, 1)));
+        set_ev(vm);
+    };
+    if (!set_ev(fmax2(vs_first[0], vs_first[1]))) set_ev_all();
+    // The query rows as fp16, q = 2^Eq q' with |q'| < 1 (8 bits of a BF16 value
+    // fit; a value below 2^-16 of its row's largest rounds at 2^-25 of that).
+    {
+        int eq;
+        reinterpret_cast<uint4 *>(s_q)[tid] = rows_to_f16(q4, eq);
+        if ((tid & 15) == 0) s_eq[tid >> 4] = eq;
     }
-    reinterpret_cast<uint4 *>(s_q)[tid] = q4;
-    __syncthreads();  // the query rows are in
+    __syncthreads();
 
     // ---- per-wavefront online-softmax state: lane (col = query row, kg);
     // the reference carries the 2^-Ev factor of the V weights ----
@@ -359,47 +377,53 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
     };
     reset_state();
     // Rows past the chunk's heads repeat the last one; their results go nowhere.
-    // Fold of a group (K scales and zeros from the K-metadata buffer): the
-    // operands y_d, the score scale bsc = kscore 2^(24 + R + E) and the bias
-    // bb = kscore sum_d q_d z'_d.
+    // Fold of a group (K scales and zeros from the K-metadata buffer, query
+    // rows q' from LDS): the operands y_d, hi and lo, the products' scale
+    // bsc = kscore 2^(24 + R + Eq + Es - 15) and the bias
+    // bb = kscore 2^Eq sum_d q'_d z'_d.
     u32x4_t bq[8];
     float bsc = 0.0f, bb = 0.0f;
     auto fold = [&]() {
-        const float *ks = reinterpret_cast<const float *>(&s_km[w][0]) + 32 * kg;
-        const float *kz = ks + kHeadDim;
+        const float4 *ks = reinterpret_cast<const float4 *>(&s_km[w][0]) + 8 * kg;
+        const float4 *kz = ks + kHeadDim / 4;
+        float mx = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const float4 u = ks[k];
+            mx = fmax3(mx, fmax2(u.x, u.y), fmax2(u.z, u.w));
+        }
+        mx = max_kg(mx);
+        int Es = 0;
+        if (mx > 0.0f) frexpf(mx, &Es);
         const uint4 *qp = reinterpret_cast<const uint4 *>(s_q + col * (kHeadDim * 2) + 64 * kg);
-        float qs[32];  // q_d s_d
-        float bias = 0.0f, mx = 0.0f;
+        float y[32];
+        float bias = 0.0f;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const uint4 u = qp[k];
-            const float4 s0 = reinterpret_cast<const float4 *>(ks)[2 * k];
-            const float4 s1 = reinterpret_cast<const float4 *>(ks)[2 * k + 1];
-            const float4 z0 = reinterpret_cast<const float4 *>(kz)[2 * k];
-            const float4 z1 = reinterpret_cast<const float4 *>(kz)[2 * k + 1];
-            const float qv[8] = {bf16_lo(u.x), bf16_hi(u.x), bf16_lo(u.y), bf16_hi(u.y),
-                                 bf16_lo(u.z), bf16_hi(u.z), bf16_lo(u.w), bf16_hi(u.w)};
+            const float4 s0 = ks[2 * k], s1 = ks[2 * k + 1], z0 = kz[2 * k], z1 = kz[2 * k + 1];
+            const uint32_t qw[4] = {u.x, u.y, u.z, u.w};
             const float sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
             const float zv[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                qs[8 * k + e] = qv[e] * sv[e];
-                bias = fmaf(qv[e], fmaf(centre, sv[e], zv[e]), bias);
-                mx = fmax2(mx, fabsf(qs[8 * k + e]));
+                const int ex = 15 - Es - KP::shift_of(8 * k + e);
+                const float zc = fmaf(centre, sv[e], zv[e]);
+                if (e & 1) {
+                    y[8 * k + e] = fma_f16_hi(qw[e / 2], ldexpf(sv[e], ex), 0.0f);
+                    bias = fma_f16_hi(qw[e / 2], zc, bias);
+                } else {
+                    y[8 * k + e] = fma_f16_lo(qw[e / 2], ldexpf(sv[e], ex), 0.0f);
+                    bias = fma_f16_lo(qw[e / 2], zc, bias);
+                }
             }
         }
-        mx = max_kg(mx);
-        bias = sum_kg(bias);
-        int E = 0;
-        if (mx > 0.0f) frexpf(mx, &E);
-        E -= 15;  // |y| < 2^15: the low halves stay clear of the fp16 floor
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
             u32x4_t hi, lo;
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
-                const int d = KP::first(kk, p), ex = -E - KP::shift(kk, p);
-                const float y0 = ldexpf(qs[d], ex), y1 = ldexpf(qs[d + KP::kApart], ex);
+                const float y0 = y[KP::first(kk, p)], y1 = y[KP::first(kk, p) + KP::kApart];
                 const uint32_t hp = pack_f16(y0, y1);
                 hi[p] = hp;
                 lo[p] = pack_f16(less_f16_lo(y0, hp), less_f16_hi(y1, hp));  // exact differences
@@ -407,8 +431,9 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
             bq[2 * kk] = hi;
             bq[2 * kk + 1] = lo;
         }
-        bsc = ldexpf(kscore, 24 + R + E);
-        bb = bias * kscore;
+        const int eq = s_eq[col];
+        bsc = ldexpf(kscore, 9 + R + eq + Es);
+        bb = ldexpf(kscore * sum_kg(bias), eq);
     };
 
     // This lane's K words of a tile: dims 32 kg .. + 31 of token 16 r + col.
@@ -543,7 +568,7 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
 
     // Fast path: a fixed softmax reference, the maximum of the wavefront's
     // first tile; the next tiles are in flight while one is attended.
-    auto copies_at = [](int c) { return 2 * RG::kCopies + ((c & 3) == 0 ? 2 : 1); };
+    auto copies_at = [](int c) { return 2 * RG::kCopies + ((c & 3) == 0 ? (LAYOUT == 1 ? 3 : 2) : 1); };
     for (int u = 0; u < n_mine; ++u) {
         const bool next_group = u + 1 < n_mine;
 #pragma unroll
@@ -587,6 +612,9 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
         // Slow path (this wavefront only): running maximum with rescaling,
         // one tile fetched and waited for at a time.
         reset_state();
+        set_ev_all();
+        issue_ids(0);
+        wait_vmcnt<0>();
         for (int j = 0; j < 4 * n_mine; ++j) {
             issue_tile(j);
             wait_vmcnt<0>();
@@ -677,11 +705,12 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
         s_ML[tid][1] = any_bad ? NAN : L;
     }
     __syncthreads();
-    // the chunk's partials: rows row_base .. + heads - 1 of (b, h)
-    const size_t prow0 = ((size_t)b * Hkv + h) * a.rows_total + row_base;
-    const __amdgpu_buffer_rsrc_t pair_o =
-        buffer_rsrc(a.ws_o + prow0 * a.ws_splits * kHeadDim, (uint32_t)heads * a.ws_splits * kHeadDim * 4);
-    const __amdgpu_buffer_rsrc_t pair_ml = buffer_rsrc(a.ws_ml + prow0 * a.ws_splits, (uint32_t)heads * a.ws_splits * 8);
+    // the sequence's partials, from its first on, rows n_seg partials apart
+    const size_t pseg0 = prow0 * a.n_seg + seg.number0;
+    const uint32_t prows = (uint32_t)(heads - 1) * a.n_seg + live;
+    const __amdgpu_buffer_rsrc_t pair_o = buffer_rsrc(a.ws_o + pseg0 * kHeadDim, prows * kHeadDim * 4);
+    const __amdgpu_buffer_rsrc_t pair_ml = buffer_rsrc(a.ws_ml + pseg0, prows * 8);
+    const bool merge = a.fused && live > 1;
     for (int idx = tid; idx < heads * (kHeadDim / 4); idx += kThreads) {
         const int rr = idx / (kHeadDim / 4);
         const int d4 = idx % (kHeadDim / 4);
@@ -709,23 +738,23 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
             O.w = fmaf(o.w + ob, f, O.w);
         }
         if (any_bad) O = make_float4(NAN, NAN, NAN, NAN);
-        if (a.fused) {
-            const uint32_t sp = (uint32_t)rr * a.ws_splits + split;  // within the chunk's rows
+        if (merge) {
+            const uint32_t sp = (uint32_t)rr * a.n_seg + (seg.number - seg.number0);
             store16_agent(pair_o, (sp * kHeadDim + 4 * d4) * 4, O);
             if (d4 == 0) store8_agent(pair_ml, sp * 8, make_float2(s_ML[rr][0], s_ML[rr][1]));
+        } else if (a.fused) {  // the whole sequence is this worker's
+            write_row4(a.out, a.lse, orow0 + rr, d4, O, s_ML[rr][0], s_ML[rr][1]);
         } else {
-            const size_t pi = partial_index(row_base + rr);
+            const size_t pi = (prow0 + rr) * a.n_seg + seg.number;
             reinterpret_cast<float4 *>(a.ws_o + pi * kHeadDim)[d4] = O;
             if (d4 == 0) a.ws_ml[pi] = make_float2(s_ML[rr][0], s_ML[rr][1]);
         }
     }
-    if (!a.fused) return;
+    if (!merge) return;
 
     // ---- split merge: count in; the chunk's last workgroup merges ----
-    __shared__ int s_last;
     unsigned *ctr = a.counters + (((size_t)b * Hkv + h) * a.row_chunks + chunk) * kCounterStride;
     if (!last_to_arrive(ctr, live, &s_last)) return;
-    const size_t orow0 = (size_t)b * a.Hq + (size_t)h * a.G + row_base;
     if (heads <= 4)
         merge_pair<4>(a, pair_o, pair_ml, orow0, heads, live, s_ring);
     else if (heads <= 8)
@@ -734,26 +763,60 @@ __global__ __launch_bounds__(kThreads, A == 2 ? 3 : 2) void anchor_split_decode_
         merge_pair<16>(a, pair_o, pair_ml, orow0, heads, live, s_ring);
 }
 
+template <int A, int LAYOUT, int UNIT>
+__global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_batch_kernel(SplitDecodeArgs a) {
+    const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
+    const WorkList<UNIT, true> list(a.seq_lens, a.B, a.max_seq_len, a.workers);
+    if (worker >= list.workers) return;
+    Segment<UNIT> seg;
+    seg.start(list, worker);
+    for (;;) {
+        attend_segment<A, LAYOUT, UNIT>(a, seg, fresh_uniform(hc % a.geo.Hkv), fresh_uniform(hc / a.geo.Hkv), fresh_tid());
+        if (!seg.next(list, worker)) return;
+        __syncthreads();  // the segment's LDS is free again
+    }
+}
+
+// A single sequence: one segment per worker, no walk.
+template <int A, int LAYOUT, int UNIT>
+__global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_kernel(SplitDecodeArgs a) {
+    const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
+    const WorkList<UNIT, false> list(a.seq_lens, 1, a.max_seq_len, a.workers);
+    if (worker >= list.workers) return;
+    Segment<UNIT> seg;
+    seg.start(list, worker);
+    attend_segment<A, LAYOUT, UNIT>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
+}
+
+template <int A, int LAYOUT>
+void launch_layout(const SplitDecodeArgs &args, dim3 grid, hipStream_t stream) {
+    if (args.B == 1)
+        hipLaunchKernelGGL((anchor_split_decode_kernel<A, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+    else
+        hipLaunchKernelGGL((anchor_split_decode_batch_kernel<A, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream,
+                           args);
+}
+
 template <int A>
 void launch_a(const SplitDecodeArgs &args, dim3 grid, hipStream_t stream) {
     if (args.geo.max_blocks == 1)
-        hipLaunchKernelGGL((anchor_split_decode_kernel<A, 0>), grid, dim3(kThreads), 0, stream, args);
+        launch_layout<A, 0>(args, grid, stream);
     else if (args.geo.bt % 16 == 0)
-        hipLaunchKernelGGL((anchor_split_decode_kernel<A, 1>), grid, dim3(kThreads), 0, stream, args);
+        launch_layout<A, 1>(args, grid, stream);
     else
-        hipLaunchKernelGGL((anchor_split_decode_kernel<A, 2>), grid, dim3(kThreads), 0, stream, args);
+        launch_layout<A, 2>(args, grid, stream);
 }
 
 }  // namespace
 
 hipError_t launch_anchor_split_decode(const SplitDecodeArgs &args, hipStream_t stream) {
-    // a wavefront keeps the block ids of at most 4 groups (paged layouts)
     const bool paged = args.geo.max_blocks != 1;
-    if (args.groups_per_split < 1 || (paged && args.groups_per_split > 4 * kWaves)) return hipErrorInvalidValue;
-    if (paged && args.n_splits > 65535) return hipErrorInvalidValue;
+    if (args.workers < 1 || args.workers > 65535) return hipErrorInvalidValue;
     const unsigned hc = (unsigned)(args.geo.Hkv * ((args.rows_total + kRows - 1) / kRows));
     // kv head fastest for paged layouts (the kernel reads the grid the same way)
-    const dim3 grid = paged ? dim3(hc, args.n_splits, args.B) : dim3(args.n_splits, hc, args.B);
+    const dim3 grid = paged ? dim3(hc, args.workers) : dim3(args.workers, hc);
     switch (args.anchor_bits) {
         case 2:
             launch_a<2>(args, grid, stream);

@@ -1,11 +1,14 @@
 // Attention over the split-stream KV cache for gfx950: planning and launch of
 // the anchor-only decode (Sec. 4.2 Anchor phase; anchor_decode.hip) and of
 // the verification pass over the merged 8-bit cache (Sec. 4.3; verify.hip),
-// both O = softmax(q K^T / sqrt(128)) V (Sec. 2) split along the context,
-// and the combine kernel that merges their per-split partials (max, sum,
+// both O = softmax(q K^T / sqrt(128)) V (Sec. 2) cut along the context,
+// and the combine kernel that merges their partials (max, sum,
 // unnormalised output) and attends the BF16 tail: the drafts, causal among
 // themselves, in verification, and the generated tokens in decode.
+#include "lane_ops.h"
 #include "lynx_internal.h"
+#include "split_merge.h"
+#include "work_list.h"
 
 #include <float.h>
 #include <math.h>
@@ -15,16 +18,13 @@
 namespace lynx {
 namespace {
 
-constexpr int kWaves = 4;  // wavefronts per decode / verification workgroup
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 
 struct AttnArgs {
     Geometry geo;
     int B, Hq, nq, G, max_seq_len;
-    int rows_total, n_ctx_splits, n_splits, split_tokens;
-    int split_base;  // split index of blockIdx.x == 0
-    int tail_in_combine;  // the combine kernel attends the BF16 tail itself
+    int rows_total, workers, n_seg, max_live;
+    int tail;             // attend the BF16 tail
     int tail_count;       // tokens of the tail every query sees; -1: query i sees i + 1 (drafts)
     int tail_stride;      // tail tokens stored per sequence in k_new / v_new
     const int32_t *seq_lens;
@@ -35,8 +35,8 @@ struct AttnArgs {
     const uint16_t *q;
     const uint16_t *k_new;
     const uint16_t *v_new;
-    float *ws_o;    // [B][Hkv][rows_total][n_splits][128]
-    float2 *ws_ml;  // [B][Hkv][rows_total][n_splits]
+    float *ws_o;    // [Hkv][rows_total][n_seg][128]
+    float2 *ws_ml;  // [Hkv][rows_total][n_seg]
 };
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -49,18 +49,10 @@ __device__ __forceinline__ void unpack8_bf16(const uint4 &u, float *x) {
     x[6] = bf16_lo(u.w); x[7] = bf16_hi(u.w);
 }
 
-// fp32 -> BF16 bits, round to nearest even (NaN -> a quiet NaN).
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;  // NaN
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
 constexpr int kCombineThreads = 256;
 
-// One workgroup per (row, kv head, sequence): merge the partials of all
-// splits and the BF16 tail tokens, normalise, round to BF16, write lse.
+// One workgroup per (row, kv head, sequence): merge the sequence's partials
+// ("splits") and the BF16 tail tokens, normalise, round to BF16, write lse.
 // Thread (split group sg, float4 column d4) folds every 8th split into a
 // running (max, sum, output), loading kBatch splits' partial outputs and
 // (max, sum) pairs together (8 when 64 splits or fewer, so no load is a
@@ -78,10 +70,6 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
     const int b = blockIdx.z;
     const int tid = threadIdx.x;
     const int Hkv = a.geo.Hkv;
-    const size_t base = (((size_t)b * Hkv + h) * a.rows_total + gr) * a.n_splits;
-    // splits with partials: every split, or the context ones when this kernel
-    // attends the tail itself
-    const int n = a.tail_in_combine ? a.n_ctx_splits : a.n_splits;
     constexpr int kGroups = kCombineThreads / (kHeadDim / 4);  // 8 split groups
     constexpr int kTailMax = 64;                   // tail tokens attended at most
     constexpr int kTailPer = kTailMax / kGroups;   // per split group
@@ -95,25 +83,10 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
     const int qi = gr / a.G;
     const int qg = gr % a.G;
     const size_t qrow = ((size_t)b * a.nq + qi) * a.Hq + (size_t)h * a.G + qg;
-    const int n_tail = a.tail_in_combine ? (a.tail_count < 0 ? qi + 1 : a.tail_count) : 0;
+    const int n_tail = a.tail ? (a.tail_count < 0 ? qi + 1 : a.tail_count) : 0;
 
     const int d4 = tid % (kHeadDim / 4);
     const int sg = tid / (kHeadDim / 4);
-    const float4 *o4 = reinterpret_cast<const float4 *>(a.ws_o) + base * (kHeadDim / 4) + d4;
-    // a batch of partials: splits s0, s0 + 8, ... (clamped to the last split)
-    float4 v[kBatch];
-    float2 ml[kBatch];
-    bool live[kBatch];
-    auto load_batch = [&](int s0) {
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int s = min(s0 + kGroups * u, n - 1);
-            v[u] = o4[(size_t)s * (kHeadDim / 4)];
-            ml[u] = a.ws_ml[base + s];
-            live[u] = s0 + kGroups * u < n;
-        }
-    };
-    load_batch(sg);
     // this thread's tail values: tokens sg, sg + 8, ... (dims 4 d4 .. + 3)
     uint2 tvw[kTailPer];
     if (n_tail > 0) {
@@ -124,6 +97,31 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
                 a.v_new + (((size_t)b * a.tail_stride + j) * Hkv + h) * kHeadDim + 4 * d4);
         }
     }
+    // The sequence's partials stand from the row's first on (work_list.h).  The
+    // first batch is loaded, up to the most there can be, before the
+    // sequence's length is in.
+    const size_t base = ((size_t)h * a.rows_total + gr) * a.n_seg;
+    int n = a.max_live;
+    // a batch of partials: splits s0, s0 + 8, ... (clamped to the last split)
+    float4 v[kBatch];
+    float2 ml[kBatch];
+    bool live[kBatch];
+    auto load_batch = [&](int s0) {
+        const float4 *o4 = reinterpret_cast<const float4 *>(a.ws_o) + base * (kHeadDim / 4) + d4;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int s = min(s0 + kGroups * u, n - 1);
+            v[u] = o4[(size_t)s * (kHeadDim / 4)];
+            ml[u] = a.ws_ml[base + s];
+        }
+    };
+    auto set_live = [&](int s0) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) live[u] = s0 + kGroups * u < n;
+    };
+    load_batch(sg);
+    n = WorkList<kWorkUnit, false>(a.seq_lens, 1, a.max_seq_len, a.workers).workers;
+    set_live(sg);
     if (n_tail > 0) {
         // tail scores, 16 tokens per pass: thread (token tid / 16, dims
         // 8 (tid % 16) .. + 7), summed over the 16 lanes of a token
@@ -186,7 +184,10 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
         m_t = mb;
     };
     for (int s0 = sg; s0 < n; s0 += kGroups * kBatch) {
-        if (s0 != sg) load_batch(s0);
+        if (s0 != sg) {
+            load_batch(s0);
+            set_live(s0);
+        }
         fold(v, ml, live);
     }
     // the tail tokens: partials (score, 1, value)
@@ -225,16 +226,168 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
             any_nan |= isnan(s_l[g][d4]);
             L = fmaf(s_l[g][d4], f, L);
         }
-        float r[4] = {O.x, O.y, O.z, O.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = any_nan ? NAN : (L > 0.0f ? r[i] / L : 0.0f);
-        const size_t row = qrow;
-        const uint32_t lo = f32_to_bf16_rne(r[0]) | ((uint32_t)f32_to_bf16_rne(r[1]) << 16);
-        const uint32_t hi = f32_to_bf16_rne(r[2]) | ((uint32_t)f32_to_bf16_rne(r[3]) << 16);
-        *reinterpret_cast<uint2 *>(out + row * kHeadDim + 4 * d4) = make_uint2(lo, hi);
-        if (lse && d4 == 0)
-            lse[row] = any_nan ? NAN : (L > 0.0f ? (M + log2f(L)) * kLn2 : -INFINITY);
+        write_row4(out, lse, qrow, d4, O, M, any_nan ? NAN : L);
     }
+}
+
+// The same for batches, and wherever a sequence has few partials: one workgroup
+// per (ROWS rows, kv head, sequence), a row per 32 threads.  Thread (row r,
+// float4 column d4) folds all of the row's partials, 8 loaded at a time, so
+// nothing meets in LDS but the tail, whose keys and values the rows share: a
+// thread holds a quarter of a token's key against every row's query, and the
+// values are staged once.  A workgroup per row reads the tail once a row, and
+// spends a third of its time on its first wait (verification of 5 drafts for 16
+// paged sequences: 17.1 -> 8.1 us).
+template <int ROWS>
+__global__ __launch_bounds__(32 * ROWS) void attn_combine_rows_kernel(AttnArgs a, uint16_t *out, float *lse) {
+    constexpr int kThreads = 32 * ROWS;
+    constexpr int kTailMax = 64;
+    constexpr int kTokens = kThreads / 4;  // tail tokens scored per pass, four threads each
+    constexpr int kPasses = kTailMax / kTokens;
+    constexpr int kValues = kTailMax * (kHeadDim / 8) / kThreads;  // 16-byte value pieces per thread
+    constexpr int kBatch = 8;
+    const int h = blockIdx.y;
+    const int b = blockIdx.z;
+    const int tid = threadIdx.x;
+    const int Hkv = a.geo.Hkv;
+    const int d4 = tid % 32;
+    const int r = tid / 32;
+    const int row0 = blockIdx.x * ROWS;
+    const bool row_live = row0 + r < a.rows_total;
+    const int gr = min(row0 + r, a.rows_total - 1);
+    const int qi = gr / a.G;
+    const size_t qrow = ((size_t)b * a.nq + qi) * a.Hq + (size_t)h * a.G + gr % a.G;
+    // tail tokens of this row, and of any row of the workgroup
+    const int n_tail = a.tail ? (a.tail_count < 0 ? qi + 1 : a.tail_count) : 0;
+    const int tail_most =
+        a.tail ? (a.tail_count < 0 ? (min(row0 + ROWS, a.rows_total) - 1) / a.G + 1 : a.tail_count) : 0;
+    __shared__ __attribute__((aligned(16))) uint4 s_v[kTailMax * (kHeadDim / 8)];  // tail values
+    // queries, a thread's 32 dims 4 floats past the last's: other banks
+    __shared__ __attribute__((aligned(16))) float s_q[ROWS][kHeadDim + 16];
+    __shared__ float s_t[ROWS][kTailMax];  // tail scores (log2 units), then weights
+
+    const int own = WorkList<kWorkUnit, false>::load_own(a.seq_lens, a.B);
+    // ---- the tail's loads ----
+    uint4 kw[kPasses][4];
+    if (tail_most > 0) {
+        const size_t t0 = (size_t)b * a.tail_stride * Hkv + h;
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) {
+            const int j = min(kTokens * p + tid / 4, tail_most - 1);
+            const uint4 *k = reinterpret_cast<const uint4 *>(a.k_new + (t0 + (size_t)j * Hkv) * kHeadDim) + 4 * (tid % 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) kw[p][e] = k[e];
+        }
+#pragma unroll
+        for (int i = 0; i < kValues; ++i) {
+            const int piece = kThreads * i + tid, j = piece / (kHeadDim / 8);
+            if (j < tail_most)
+                s_v[piece] = reinterpret_cast<const uint4 *>(
+                    a.v_new + (t0 + (size_t)j * Hkv) * kHeadDim)[piece % (kHeadDim / 8)];
+        }
+        const uint2 qw = reinterpret_cast<const uint2 *>(a.q + qrow * kHeadDim)[d4];
+        *reinterpret_cast<float4 *>(&s_q[r][4 * d4 + 4 * (d4 / 8)]) =
+            make_float4(bf16_lo(qw.x), bf16_hi(qw.x), bf16_lo(qw.y), bf16_hi(qw.y));
+    }
+    // ---- the row's partials (work_list.h): n of them from seg0 on ----
+    const WorkList<kWorkUnit, false> list(a.seq_lens, a.B, a.max_seq_len, a.workers, own);
+    const int first = a.B == 1 ? 0 : list.first_unit(b);
+    const int w0 = list.owner(first);
+    const int n = list.owner(first + list.units(list.tokens_of(b)) - 1) - w0 + 1;
+    const size_t base = ((size_t)h * a.rows_total + gr) * a.n_seg + (w0 + b);
+    const float4 *o4 = reinterpret_cast<const float4 *>(a.ws_o) + base * (kHeadDim / 4) + d4;
+    float M = -INFINITY, L = 0.0f;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = 0; s0 < n; s0 += kBatch) {
+        float4 v[kBatch];
+        float2 ml[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int s = min(s0 + u, n - 1);
+            v[u] = o4[(size_t)s * (kHeadDim / 4)];
+            ml[u] = a.ws_ml[base + s];
+        }
+        float mb = M;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (s0 + u >= n) ml[u] = make_float2(-INFINITY, 0.0f);
+            mb = fmaxf(mb, ml[u].x);
+        }
+        const float sc = M == -INFINITY ? 0.0f : exp2f(M - mb);
+        acc.x *= sc;
+        acc.y *= sc;
+        acc.z *= sc;
+        acc.w *= sc;
+        L *= sc;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const float e = ml[u].x == -INFINITY ? 0.0f : exp2f(ml[u].x - mb);
+            L = fmaf(ml[u].y, e, L);  // a NaN sum (bad block id) stays NaN
+            // a partial of weight 0 may hold no output at all
+            const float4 x = e != 0.0f ? v[u] : make_float4(0.f, 0.f, 0.f, 0.f);
+            acc.x = fmaf(x.x, e, acc.x);
+            acc.y = fmaf(x.y, e, acc.y);
+            acc.z = fmaf(x.z, e, acc.z);
+            acc.w = fmaf(x.w, e, acc.w);
+        }
+        M = mb;
+    }
+    // ---- the tail ----
+    if (tail_most > 0) {  // uniform
+        __syncthreads();  // queries and values are staged
+        const float sm = kLog2e * rsqrtf((float)kHeadDim);
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) {
+            if (kTokens * p >= tail_most) break;
+            float kv[32];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) unpack8_bf16(kw[p][e], kv + 8 * e);
+#pragma unroll
+            for (int rr = 0; rr < ROWS; ++rr) {
+                const float4 *q = reinterpret_cast<const float4 *>(&s_q[rr][36 * (tid % 4)]);
+                float d = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float4 x = q[e];
+                    d = fmaf(x.x, kv[4 * e], d);
+                    d = fmaf(x.y, kv[4 * e + 1], d);
+                    d = fmaf(x.z, kv[4 * e + 2], d);
+                    d = fmaf(x.w, kv[4 * e + 3], d);
+                }
+                d += dpp<0xB1>(d);
+                d += dpp<0x4E>(d);  // over the token's four threads
+                if (tid % 4 == 0) s_t[rr][kTokens * p + tid / 4] = d * sm;
+            }
+        }
+        __syncthreads();
+        // the row's 32 threads: tokens d4 and d4 + 32
+        const float t0 = d4 < n_tail ? s_t[r][d4] : -INFINITY;
+        const float t1 = d4 + 32 < n_tail ? s_t[r][d4 + 32] : -INFINITY;
+        const float Mt = fmaxf(M, row_max<32>(fmaxf(t0, t1)));
+        const float p0 = d4 < n_tail ? exp2f(t0 - Mt) : 0.0f;
+        const float p1 = d4 + 32 < n_tail ? exp2f(t1 - Mt) : 0.0f;
+        s_t[r][d4] = p0;
+        s_t[r][d4 + 32] = p1;
+        const float sc = M == -INFINITY ? 0.0f : exp2f(M - Mt);
+        L = fmaf(L, sc, row_sum<32>(p0 + p1));
+        M = Mt;
+        __syncthreads();
+        acc.x *= sc;
+        acc.y *= sc;
+        acc.z *= sc;
+        acc.w *= sc;
+        const uint2 *v2 = reinterpret_cast<const uint2 *>(s_v) + d4;
+#pragma unroll 4
+        for (int j = 0; j < n_tail; ++j) {
+            const float p = s_t[r][j];
+            const uint2 w = v2[j * (kHeadDim / 4)];
+            acc.x = fmaf(p, bf16_lo(w.x), acc.x);
+            acc.y = fmaf(p, bf16_hi(w.x), acc.y);
+            acc.z = fmaf(p, bf16_lo(w.y), acc.z);
+            acc.w = fmaf(p, bf16_hi(w.y), acc.w);
+        }
+    }
+    if (row_live) write_row4(out, lse, qrow, d4, acc, M, L);
 }
 
 // Compute units of the current device (0 if unknown), queried once per device.
@@ -253,62 +406,82 @@ int compute_units() {
 
 }  // namespace
 
-AttnPlan plan_attention(const Geometry &g, int B, int Hq, int nq, int max_seq_len, bool tail) {
+namespace {
+
+constexpr int kPerCu = 2;  // workgroups of an attention kernel that a CU holds at once
+
+// 512-token units of a sequence of at most T tokens (work_list.h).
+long long work_units(int T) { return T > 0 ? ((long long)T + kWorkUnit * kKGroup - 1) / (kWorkUnit * kKGroup) : 1; }
+
+constexpr size_t kPartialBytes = kHeadDim * sizeof(float) + sizeof(float2);
+
+}  // namespace
+
+// One round of workgroups, whatever the batch: as many workers per (kv head,
+// row chunk) as the chip holds at once, each with an equal share of the
+// batch's units.  Against splits of up to 2048 tokens per workgroup (several
+// rounds, a combine kernel): see work_list.h.
+AttnPlan plan_attention(KvMode mode, const Geometry &g, int B, int Hq, int nq, int max_seq_len,
+                        size_t most) {
     AttnPlan p{};
-    const int G = Hq / g.Hkv;
-    p.rows_total = nq * G;
-    // Context tokens per split: 512, doubled while the launch still fills
-    // the chip (>= 1024 decode workgroups, two per CU; >= 512 verification
-    // workgroups, also two per CU), so long contexts write fewer partials
-    // and workgroups live longer: up to 2048 tokens (512 for decode when
-    // 16-head chunks leave no LDS for more groups).
-    p.split_tokens = kWaves * kKGroup;
-    const int max_split = nq == 1 && G > 8 ? 512 : 2048;
-    const int min_workgroups = nq == 1 ? 1024 : 512;
-    while (p.split_tokens < max_split) {
-        const long long next = ((long long)max_seq_len + 2 * p.split_tokens - 1) / (2 * p.split_tokens);
-        if (next * g.Hkv * B < min_workgroups) break;
-        p.split_tokens *= 2;
+    p.rows_total = nq * (Hq / g.Hkv);
+    const int tile = mode == KvMode::kCodes && p.rows_total > 16 ? 32 : 16;  // rows per workgroup
+    const long long chunks = (p.rows_total + tile - 1) / tile;
+    const int cus = compute_units();
+    const long long slots = (long long)kPerCu * (cus > 0 ? cus : 256);
+    const long long units = (long long)B * work_units(max_seq_len);
+    long long w = slots / (g.Hkv * chunks);
+    w = w < units ? w : units;
+    // fewer partials where the workspace is given (lynx_attn_anchor_decode_noalloc)
+    const size_t row_bytes = (size_t)g.Hkv * p.rows_total * kPartialBytes;
+    if (most < SIZE_MAX) {
+        const long long fit = (long long)((most - kCounterBytes) / row_bytes) - (B - 1);
+        w = w < fit ? w : fit;
     }
-    if (nq > 1 && g.max_blocks == 1) {
-        // The same for verification of a contiguous batch (its combine kernel
-        // still attends the draft tail, over fewer splits): 70B-shaped batch,
-        // k = 4, 2048 workgroups of 2048 tokens 231 us, 512 of 8192 212 us.
-        const int cus = compute_units();
-        const int rt = p.rows_total <= 16 ? 1 : 2;
-        const long long chunks = (p.rows_total + 16 * rt - 1) / (16 * rt);
-        for (int st = p.split_tokens; cus > 0 && st <= 8192; st *= 2) {
-            const long long splits = max_seq_len > 0 ? (max_seq_len + st - 1) / st : 1;
-            if (splits * g.Hkv * chunks * B <= 2LL * cus) {
-                p.split_tokens = st;
-                break;
-            }
-        }
-    }
-    if (nq == 1 && !tail && g.max_blocks == 1 && G <= 8) {
-        // A contiguous decode batch that fits one round of workgroups (two per
-        // CU) with longer splits, up to 8192 tokens, takes them: the split
-        // merge then runs in the same launch, and no workgroup waits for a
-        // second round (70B-shaped batch, 4 x 128K tokens: 2048 workgroups of
-        // 2048 tokens and the combine kernel, 112 us; 512 of 8192, 104 us).
-        const int cus = compute_units();
-        for (int st = p.split_tokens; cus > 0 && st <= 8192; st *= 2) {
-            const long long splits = max_seq_len > 0 ? (max_seq_len + st - 1) / st : 1;
-            if (splits * g.Hkv * B <= 2LL * cus) {
-                p.split_tokens = st;
-                break;
-            }
-        }
-    }
-    // at least one split, so that empty sequences still get (zero) outputs
-    p.n_ctx_splits = max_seq_len > 0 ? (max_seq_len + p.split_tokens - 1) / p.split_tokens : 1;
-    p.n_splits = p.n_ctx_splits + (tail ? 1 : 0);
-    const size_t parts = (size_t)B * g.Hkv * p.rows_total * p.n_splits;
-    p.o_bytes = parts * kHeadDim * sizeof(float);
-    p.ml_bytes = parts * sizeof(float2);
+    // the shares are found in 32-bit arithmetic (workers x units)
+    if (units * w > 0xffffffffll) w = 0xffffffffll / units;
+    p.workers = (int)(w > 1 ? w : 1);
+    p.n_seg = p.workers + (B > 0 ? B - 1 : 0);
+    p.max_live = (int)(work_units(max_seq_len) < p.workers ? work_units(max_seq_len) : p.workers);
+    p.o_bytes = (size_t)g.Hkv * p.rows_total * p.n_seg * kHeadDim * sizeof(float);
+    p.ml_bytes = (size_t)g.Hkv * p.rows_total * p.n_seg * sizeof(float2);
     p.row_chunks = (p.rows_total + 15) / 16;
     p.counters_fit = (long long)B * g.Hkv * p.row_chunks <= kCounters;
     return p;
+}
+
+// rows_total x workers is at most a row tile per resident workgroup (a row per
+// kv head where there are more of those), and at most a partial per unit; the
+// sum with a partial per sequence grows with each of the arguments, so a
+// workspace serves every smaller call too.
+size_t attention_workspace_bound(const Geometry &g, int B, int Hq, int nq, int max_seq_len) {
+    const size_t rows = (size_t)nq * (Hq / g.Hkv) * g.Hkv;
+    const int cus = compute_units();
+    const size_t resident = (size_t)kPerCu * (cus > 0 ? cus : 256) * (nq * (Hq / g.Hkv) > 16 ? 32 : 16);
+    const size_t by_slots = resident > rows ? resident : rows;
+    const size_t by_units = rows * B * (size_t)work_units(max_seq_len);
+    return kCounterBytes + ((by_slots < by_units ? by_slots : by_units) + rows * B) * kPartialBytes;
+}
+
+// The limit is the one that callers of the no-allocation decode know: a partial
+// per split of every sequence, splits of 512 tokens, longer (to 2048) while
+// 1024 workgroups remain, and to 8192 where a contiguous batch of at most 8
+// heads per kv head then fits two workgroups per CU.  The work list needs less,
+// and plan_attention makes any call within the limit fit.
+bool decode_over_scratch(const Geometry &g, int B, int Hq, int max_seq_len, size_t scratch) {
+    const int G = Hq / g.Hkv;
+    const long long heads = (long long)g.Hkv * B;
+    auto splits = [&](long long tokens) { return max_seq_len > 0 ? (max_seq_len + tokens - 1) / tokens : 1ll; };
+    long long tokens = 512;
+    while (tokens < (G > 8 ? 512 : 2048) && splits(2 * tokens) * heads >= 1024 && max_seq_len > 0) tokens *= 2;
+    const int cus = compute_units();
+    if (g.max_blocks == 1 && G <= 8 && cus > 0)
+        for (long long st = tokens; st <= 8192; st *= 2)
+            if (splits(st) * heads <= 2ll * cus) {
+                tokens = st;
+                break;
+            }
+    return kCounterBytes + (size_t)(heads * G * splits(tokens)) * kPartialBytes > scratch;
 }
 
 hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan, int B, int Hq,
@@ -318,7 +491,7 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
                             const uint16_t *k_new, const uint16_t *v_new, int tail_count,
                             uint16_t *out,
                             float *lse, void *workspace, hipStream_t stream, int anchor_bits) {
-    if (B == 0 || plan.n_splits == 0) return hipSuccess;
+    if (B == 0) return hipSuccess;
     AttnArgs a;
     a.geo = g;
     a.B = B;
@@ -327,14 +500,10 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
     a.G = Hq / g.Hkv;
     a.max_seq_len = max_seq_len;
     a.rows_total = plan.rows_total;
-    a.n_ctx_splits = plan.n_ctx_splits;
-    a.n_splits = plan.n_splits;
-    a.split_tokens = plan.split_tokens;
-    a.split_base = 0;
-    // the matrix-core paths leave the BF16 tail to the combine kernel:
-    // causal drafts in verification, tail_count generated tokens in decode
-    const bool mfma_path = mode == KvMode::kCodes || nq == 1;
-    a.tail_in_combine = (mfma_path && k_new != nullptr) ? 1 : 0;
+    a.workers = plan.workers;
+    a.n_seg = plan.n_seg;
+    a.max_live = plan.max_live;
+    a.tail = k_new != nullptr ? 1 : 0;
     a.tail_count = mode == KvMode::kCodes ? -1 : tail_count;
     a.tail_stride = mode == KvMode::kCodes ? nq : tail_count;
     a.seq_lens = seq_lens;
@@ -356,13 +525,11 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
         d.Hq = Hq;
         d.G = a.G;
         d.max_seq_len = max_seq_len;
-        d.n_splits = plan.n_ctx_splits;
-        d.groups_per_split = plan.split_tokens / kKGroup;
+        d.workers = plan.workers;
         d.chunk_heads = a.G < 16 ? a.G : 16;
         d.bt_shift = -1;
         for (int sh = 0; sh < 31; ++sh)
             if ((1 << sh) == g.bt) d.bt_shift = sh;
-        d.meta_vec4 = (g.max_tokens % 4 == 0) ? 1 : 0;
         d.seq_lens = seq_lens;
         d.block_table = block_table;
         d.k_anc = k_plane;
@@ -372,23 +539,13 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
         d.ws_o = a.ws_o;
         d.ws_ml = a.ws_ml;
         d.rows_total = plan.rows_total;
-        d.ws_splits = plan.n_splits;
-        // without a tail the last workgroup of each (sequence, kv head, head
-        // chunk) merges the splits itself: no second launch
-        // The in-kernel merge costs every workgroup a wait for its partial's
-        // stores and an atomic (about 1.2 us), during which it holds its CU
-        // slot: a win when the whole grid runs in one round (two workgroups
-        // per CU), a loss over several rounds, where the combine kernel
-        // merges instead (70B batch: 126 us per step with the combine, 133
-        // fused; 32K layer: 17.7 us with the combine, 15.9 fused).  The merge
-        // holds up to two splits' (max, sum) per thread: 256 / GP threads per
+        d.n_seg = plan.n_seg;
+        // Without a tail the last workgroup of each (sequence, kv head, head
+        // chunk) merges its partials itself: no second launch.  The merge
+        // holds up to two partials' (max, sum) per thread: 256 / GP threads per
         // row, GP = 4, 8 or 16 rows padded.
         const int gp = d.chunk_heads <= 4 ? 4 : d.chunk_heads <= 8 ? 8 : 16;
-        const int chunks_ = (a.G + d.chunk_heads - 1) / d.chunk_heads;
-        const long long wgs = (long long)plan.n_ctx_splits * g.Hkv * chunks_ * B;
-        const bool one_round = wgs <= 2LL * compute_units();
-        d.fused = (k_new == nullptr && plan.counters_fit && plan.n_ctx_splits <= 2 * (256 / gp) &&
-                   one_round) ? 1 : 0;
+        d.fused = (k_new == nullptr && plan.counters_fit && plan.max_live <= 2 * (256 / gp)) ? 1 : 0;
         d.row_chunks = plan.row_chunks;
         d.counters = reinterpret_cast<unsigned *>(workspace);
         d.out = out;
@@ -407,13 +564,12 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
         d.G = a.G;
         d.max_seq_len = max_seq_len;
         d.anchor_bits = anchor_bits;
-        d.n_splits = plan.n_ctx_splits;
-        d.groups_per_split = plan.split_tokens / kKGroup;
+        d.workers = plan.workers;
         d.bt_shift = -1;
         for (int sh = 0; sh < 31; ++sh)
             if ((1 << sh) == g.bt) d.bt_shift = sh;
         d.rows_total = plan.rows_total;
-        d.ws_splits = plan.n_splits;
+        d.n_seg = plan.n_seg;
         d.seq_lens = seq_lens;
         d.block_table = block_table;
         d.k_anc = k_plane;
@@ -422,13 +578,9 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
         d.q = q;
         d.ws_o = a.ws_o;
         d.ws_ml = a.ws_ml;
-        // the split merge in the same launch, under the rule of the 4-bit
-        // decode: one round of workgroups, and at most 2 * 256 / GP splits
-        // for the merging workgroup (GP: the chunk's rows, padded)
+        // the merge in the same launch, under the 4-bit decode's rule
         const int gp = a.G <= 4 ? 4 : a.G <= 8 ? 8 : 16;
-        const long long wgs = (long long)plan.n_ctx_splits * g.Hkv * plan.row_chunks * B;
-        d.fused = (plan.counters_fit && plan.n_ctx_splits <= 2 * (256 / gp) &&
-                   wgs <= 2LL * compute_units()) ? 1 : 0;
+        d.fused = (plan.counters_fit && plan.max_live <= 2 * (256 / gp)) ? 1 : 0;
         d.row_chunks = plan.row_chunks;
         d.counters = reinterpret_cast<unsigned *>(workspace);
         d.out = out;
@@ -437,7 +589,7 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
         if (e != hipSuccess) return e;
         if (d.fused) return hipSuccess;
     } else if (mode == KvMode::kCodes) {
-        // matrix-core verification over the context splits ...
+        // matrix-core verification over the context ...
         VerifyArgs v;
         v.geo = g;
         v.B = B;
@@ -446,8 +598,8 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
         v.nq = nq;
         v.max_seq_len = max_seq_len;
         v.rows_total = plan.rows_total;
-        v.n_ctx_splits = plan.n_ctx_splits;
-        v.ws_splits = plan.n_splits;
+        v.workers = plan.workers;
+        v.n_seg = plan.n_seg;
         v.bt_shift = -1;
         for (int sh = 0; sh < 31; ++sh)
             if ((1 << sh) == g.bt) v.bt_shift = sh;
@@ -459,19 +611,28 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
         v.q = q;
         v.ws_o = a.ws_o;
         v.ws_ml = a.ws_ml;
-        hipError_t e = launch_verify_mfma(v, plan.split_tokens / kKGroup, stream);
+        hipError_t e = launch_verify_mfma(v, stream);
         if (e != hipSuccess) return e;
         // the BF16 draft tail is attended by the combine kernel below
     } else {
         return hipErrorInvalidValue;  // anchor attention with several queries: no entry point asks for it
     }
-    const int n_merged = a.tail_in_combine ? a.n_ctx_splits : a.n_splits;
-    if (n_merged <= 64)
+    // A single sequence of many partials is merged a row per workgroup, 8 or 16
+    // threads deep in its partials; else the rows share workgroups.
+    if (B > 1 || plan.max_live <= 16) {
+        const int rows = plan.rows_total <= 4 ? 4 : 8;
+        const dim3 grid((plan.rows_total + rows - 1) / rows, g.Hkv, B);
+        if (rows == 4)
+            hipLaunchKernelGGL(attn_combine_rows_kernel<4>, grid, dim3(128), 0, stream, a, out, lse);
+        else
+            hipLaunchKernelGGL(attn_combine_rows_kernel<8>, grid, dim3(256), 0, stream, a, out, lse);
+    } else if (plan.max_live <= 64) {
         hipLaunchKernelGGL(attn_combine_kernel<8>, dim3(plan.rows_total, g.Hkv, B), dim3(kCombineThreads),
                            0, stream, a, out, lse);
-    else
+    } else {
         hipLaunchKernelGGL(attn_combine_kernel<16>, dim3(plan.rows_total, g.Hkv, B), dim3(kCombineThreads),
                            0, stream, a, out, lse);
+    }
     return hipGetLastError();
 }
 

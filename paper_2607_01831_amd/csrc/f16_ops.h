@@ -18,14 +18,14 @@ __device__ __forceinline__ f32x4_t mfma_f16(u32x4_t a, u32x4_t b, f32x4_t c) {
 }
 
 // Eight code bytes (two words, byte e = element e) -> eight fp16 values
-// 1024 + c in element order.
+// c 2^-24 in element order: the byte alone is the subnormal, which the matrix
+// cores take exactly, so there is no offset to remove from the products.
 __device__ __forceinline__ u32x4_t codes_to_f16(uint32_t w0, uint32_t w1) {
-    const uint32_t c = 0x64646464u;
     u32x4_t r;
-    r[0] = __builtin_amdgcn_perm(c, w0, 0x04010400u);
-    r[1] = __builtin_amdgcn_perm(c, w0, 0x04030402u);
-    r[2] = __builtin_amdgcn_perm(c, w1, 0x04010400u);
-    r[3] = __builtin_amdgcn_perm(c, w1, 0x04030402u);
+    r[0] = __builtin_amdgcn_perm(0u, w0, 0x0c010c00u);
+    r[1] = __builtin_amdgcn_perm(0u, w0, 0x0c030c02u);
+    r[2] = __builtin_amdgcn_perm(0u, w1, 0x0c010c00u);
+    r[3] = __builtin_amdgcn_perm(0u, w1, 0x0c030c02u);
     return r;
 }
 
@@ -59,8 +59,36 @@ __device__ __forceinline__ float less_f16_hi(float y, uint32_t w) {
     asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(y));
     return r;
 }
+// x times the fp16 in the low / high half of w, plus c, rounded once.
+__device__ __forceinline__ float fma_f16_lo(uint32_t w, float x, float c) {
+    float r;
+    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(x), "v"(c));
+    return r;
+}
+__device__ __forceinline__ float fma_f16_hi(uint32_t w, float x, float c) {
+    float r;
+    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(x), "v"(c));
+    return r;
+}
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// Eight BF16 values of a row that 16 neighbouring threads hold together
+// -> fp16 values q' = q 2^-E, E the exponent of the row's largest magnitude
+// (|q'| < 1; 0 for a row of zeros).
+__device__ __forceinline__ uint4 rows_to_f16(const uint4 &u, int &E) {
+    const uint32_t wv[4] = {u.x, u.y, u.z, u.w};
+    float mx = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) mx = fmax3(mx, fabsf(bf16_lo(wv[e])), fabsf(bf16_hi(wv[e])));
+    mx = row16_max(mx);
+    E = 0;
+    if (mx > 0.0f) frexpf(mx, &E);
+    uint32_t h[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = pack_f16_rne(ldexpf(bf16_lo(wv[e]), -E), ldexpf(bf16_hi(wv[e]), -E));
+    return make_uint4(h[0], h[1], h[2], h[3]);
+}
 
 // Byte offset of 16-byte chunk q of V-tile row t (rows of 128 code bytes) in
 // an LDS tile.  The XOR swizzle spreads the 8 rows one transposed read

@@ -13,6 +13,22 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4_t;
 typedef __attribute__((__vector_size__(2 * sizeof(int)))) int intx2_t;
 
+// threadIdx.x as a value of its own: what follows from it is computed where it
+// is used.  A kernel that loops over segments would otherwise compute every
+// lane constant of its body once, before the loop, and spill them (anchor
+// decode: 51 to 314 registers).
+__device__ __forceinline__ int fresh_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+// A uniform value likewise, in a scalar register.
+__device__ __forceinline__ int fresh_uniform(int v) {
+    v = __builtin_amdgcn_readfirstlane(v);
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));

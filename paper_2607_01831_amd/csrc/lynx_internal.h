@@ -105,11 +105,15 @@ constexpr int kCounterStride = 64;  // uint32 slots between counters
 constexpr int kCounters = (int)(kCounterBytes / (kCounterStride * sizeof(unsigned)));
 enum class KvMode : int { kAnchor = 0, kCodes = 1, kAnchorSplit = 2 };
 
+// 128-token groups per unit of the attention kernels' work list (work_list.h):
+// one per wavefront of a workgroup.
+constexpr int kWorkUnit = 4;
+
 struct AttnPlan {
     int rows_total;   // nq * G query rows per (sequence, kv head)
-    int split_tokens; // context tokens per split
-    int n_ctx_splits; // ceil(max_seq_len / split_tokens)
-    int n_splits;     // n_ctx_splits (+1 when a BF16 draft tail is attended)
+    int workers;      // workgroups per (kv head, row chunk)
+    int n_seg;        // partials per query row: workers + B - 1
+    int max_live;     // partials of one sequence at most
     int row_chunks;   // ceil(rows_total / 16): arrival counters per (sequence, kv head)
     bool counters_fit;  // B * Hkv * row_chunks <= kCounters
     size_t o_bytes;   // workspace bytes for the partial outputs
@@ -124,20 +128,19 @@ struct AttnPlan {
 struct DecodeArgs {
     Geometry geo;
     int B, Hq, G, max_seq_len;
-    int n_splits, groups_per_split, chunk_heads;
+    int workers, chunk_heads;
     int bt_shift;   // log2(block_tokens) when it is a power of two, else -1
-    int meta_vec4;  // max_tokens % 4 == 0: V metadata loads may be 16 bytes
     const int32_t *seq_lens;
     const int32_t *block_table;
     const uint8_t *k_anc;
     const uint8_t *v_anc;
     MetaPtrs meta;
     const uint16_t *q;
-    float *ws_o;    // split partials, same layout as the attention workspace
-    float2 *ws_ml;
-    int rows_total, ws_splits;
-    // Fused split merge: the last workgroup of a (sequence, kv head, head
-    // chunk) to finish merges its splits' partials and writes out / lse.
+    float *ws_o;    // partials [Hkv][rows_total][n_seg][128]
+    float2 *ws_ml;  // [Hkv][rows_total][n_seg]
+    int rows_total, n_seg;
+    // Fused merge: the last workgroup of a (sequence, kv head, head chunk) to
+    // finish merges its partials and writes out / lse.
     // Arrival counters uint32 [B][Hkv][row_chunks], zero on entry, left zero.
     int fused;
     int row_chunks;
@@ -148,14 +151,14 @@ struct DecodeArgs {
 
 hipError_t launch_anchor_decode_mfma(const DecodeArgs &args, int chunks, hipStream_t stream);
 
-// Arguments of the matrix-core verification kernel (verify.hip): context
-// splits only; the combine kernel attends the BF16 draft tail.
+// Arguments of the matrix-core verification kernel (verify.hip): the context
+// only; the combine kernel attends the BF16 draft tail.
 struct VerifyArgs {
     Geometry geo;
     int B, Hq, G, nq, max_seq_len;
     int rows_total;    // nq * G query rows per (sequence, kv head)
-    int n_ctx_splits;  // grid.x
-    int ws_splits;     // partial-row stride (context splits + tail)
+    int workers;       // workgroups per (kv head, row chunk)
+    int n_seg;         // partials per row
     int bt_shift;      // log2(block_tokens) when it is a power of two, else -1
     const int32_t *seq_lens;
     const int32_t *block_table;
@@ -167,20 +170,18 @@ struct VerifyArgs {
     float2 *ws_ml;
 };
 
-hipError_t launch_verify_mfma(const VerifyArgs &args, int split_groups, hipStream_t stream);
+hipError_t launch_verify_mfma(const VerifyArgs &args, hipStream_t stream);
 
 // Arguments of the anchor decode over split-width anchors (anchor_split.hip):
-// one query per sequence over A-bit anchor planes (rows of 16 A bytes);
-// context splits only, merged by the combine kernel.
+// one query per sequence over A-bit anchor planes (rows of 16 A bytes).
 struct SplitDecodeArgs {
     Geometry geo;
     int B, Hq, G, max_seq_len;
     int anchor_bits;      // A: 2, 4 or 6
-    int n_splits;         // grid.x
-    int groups_per_split; // 128-token groups per split; at most 16 when paged
+    int workers;          // workgroups per (kv head, row chunk)
     int bt_shift;         // log2(block_tokens) when it is a power of two, else -1
     int rows_total;       // G query rows per (sequence, kv head)
-    int ws_splits;        // partial-row stride
+    int n_seg;            // partials per row
     const int32_t *seq_lens;
     const int32_t *block_table;
     const uint8_t *k_anc;
@@ -189,7 +190,7 @@ struct SplitDecodeArgs {
     const uint16_t *q;    // BF16 [B][Hq][128]
     float *ws_o;
     float2 *ws_ml;
-    // split merge in the same launch (as DecodeArgs): arrival counters
+    // merge in the same launch (as DecodeArgs): arrival counters
     // uint32 [B][Hkv][row_chunks], zero on entry, left zero
     int fused;
     int row_chunks;
@@ -200,7 +201,16 @@ struct SplitDecodeArgs {
 
 hipError_t launch_anchor_split_decode(const SplitDecodeArgs &args, hipStream_t stream);
 
-AttnPlan plan_attention(const Geometry &g, int B, int Hq, int nq, int max_seq_len, bool tail);
+// The plan of a call; its workspace is at most `most` bytes where fewer workers
+// can make it so.
+AttnPlan plan_attention(KvMode mode, const Geometry &g, int B, int Hq, int nq, int max_seq_len,
+                        size_t most = SIZE_MAX);
+// Workspace bytes that suffice for every kind of call of at most B sequences,
+// nq queries each, and max_seq_len tokens.
+size_t attention_workspace_bound(const Geometry &g, int B, int Hq, int nq, int max_seq_len);
+// Whether lynx_attn_anchor_decode_noalloc refuses a call as larger than its
+// scratch of `scratch` bytes.
+bool decode_over_scratch(const Geometry &g, int B, int Hq, int max_seq_len, size_t scratch);
 
 // k_new / v_new: the BF16 tail, or nullptr.  Verification (kCodes): k drafts
 // per sequence, causal among the drafts.  Decode (kAnchor, nq == 1):

@@ -26,6 +26,19 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
     return (uint16_t)(u >> 16);
 }
 
+// Four outputs of a row (o unnormalised, sum L, maximum M in log2 units; a NaN
+// sum marks a bad block id) to BF16, and with the first four the lse.
+__device__ __forceinline__ void write_row4(uint16_t *out, float *lse, size_t row, int d4, float4 o, float M, float L) {
+    const bool nan = isnan(L);
+    float res[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) res[i] = nan ? NAN : (L > 0.0f ? res[i] / L : 0.0f);
+    const uint32_t lo = f32_to_bf16_rne(res[0]) | ((uint32_t)f32_to_bf16_rne(res[1]) << 16);
+    const uint32_t hi = f32_to_bf16_rne(res[2]) | ((uint32_t)f32_to_bf16_rne(res[3]) << 16);
+    *reinterpret_cast<uint2 *>(out + row * kHeadDim + 4 * d4) = make_uint2(lo, hi);
+    if (lse && d4 == 0) lse[row] = nan ? NAN : (L > 0.0f ? (M + log2f(L)) * 0.6931471805599453f : -INFINITY);
+}
+
 // Reductions over the kP lanes of one row (kP = 64, 32 or 16 lanes aligned
 // in the wavefront), on the permute paths (DPP, permlane swaps).
 template <int kP>
@@ -56,8 +69,8 @@ __device__ __forceinline__ float row_sum(float v) {
 }
 
 // Merge of the `live` split partials of `heads` query rows by one workgroup.
-// ro / rml: buffer resources over the pair's partial outputs [heads][ws_splits]
-// [128] and (max, sum) pairs [heads][ws_splits]; output row orow0 + r.
+// ro / rml: buffer resources over the pair's partial outputs and (max, sum)
+// pairs from its first on, rows n_seg partials apart; output row orow0 + r.
 // Threads (row r, u < kP): thread u holds the (max, sum) of splits u and
 // u + kP (live <= 2 kP), and as (split group sg, float4 column d4) the partial
 // outputs of splits sg, sg + groups, ...  Every load of the first round is
@@ -74,11 +87,11 @@ __device__ void merge_pair(const Args &a, __amdgpu_buffer_rsrc_t ro, __amdgpu_bu
     constexpr int kCols = kP >= 32 ? 1 : 32 / kP;    // float4 columns per thread
     constexpr int kRound = 32 / kCols;               // partial outputs per column and round
     constexpr uint32_t kPast = 0x80000000u;          // an offset past any resource
-    const int tid = threadIdx.x;
+    const int tid = fresh_tid();
     const int r = tid / kP, u = tid % kP;
     const int sg = kP >= 32 ? u / 32 : 0;
     const bool row_live = r < heads;
-    const uint32_t prow = (uint32_t)r * a.ws_splits;
+    const uint32_t prow = (uint32_t)r * a.n_seg;
     float *s_f = reinterpret_cast<float *>(lds);                     // [GP][2 kP] split weights
     float4 *s_acc = reinterpret_cast<float4 *>(s_f + GP * 2 * kP);   // [GP][kGroups][32]
     auto o_off = [&](int sp, int d4) {
@@ -151,15 +164,7 @@ __device__ void merge_pair(const Args &a, __amdgpu_buffer_rsrc_t ro, __amdgpu_bu
                 O.z += o.z;
                 O.w += o.w;
             }
-            const bool nan = isnan(L);
-            float res[4] = {O.x, O.y, O.z, O.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) res[i] = nan ? NAN : (L > 0.0f ? res[i] / L : 0.0f);
-            const uint32_t lo = f32_to_bf16_rne(res[0]) | ((uint32_t)f32_to_bf16_rne(res[1]) << 16);
-            const uint32_t hi = f32_to_bf16_rne(res[2]) | ((uint32_t)f32_to_bf16_rne(res[3]) << 16);
-            *reinterpret_cast<uint2 *>(a.out + (orow0 + r) * kHeadDim + 4 * d4) = make_uint2(lo, hi);
-            if (a.lse && d4 == 0)
-                a.lse[orow0 + r] = nan ? NAN : (L > 0.0f ? (M + log2f(L)) * 0.6931471805599453f : -INFINITY);
+            write_row4(a.out, a.lse, orow0 + r, d4, O, M, L);
         }
     }
 }

@@ -12,24 +12,29 @@
 // contraction is dense, so Q K^T and P V run as v_mfma_f32_16x16x32_f16.
 //
 // Exactness of the operands:
-//  * a code byte c becomes the fp16 value 1024 + c (bit pattern 0x6400 | c),
-//    one v_perm per two values; the 1024 offset is removed after the product.
-//  * per 128-token group the K scale is folded into the query rows:
-//    q''_d = q_d s_d 2^-E (E per group and row, so |q''| < 1), carried as fp16
-//    hi + lo through two MFMAs; zero and offset enter a per-(group, row) bias
-//    sum_d q_d (z_d - 1024 s_d).
+//  * a code byte c stands as the fp16 subnormal c 2^-24, one v_perm per two
+//    values; the 2^24 goes into the scales below.
+//  * the query rows are scaled once to fp16, q = 2^Eq q' with |q'| < 1 (8 bits
+//    of a BF16 value fit; a value below 2^-16 of its row's largest rounds at
+//    2^-25 of that).  Per 128-token group the K scale is folded into them:
+//    y_d = q'_d s_d 2^(15 - Es), Es the exponent of the group's largest scale,
+//    |y| < 2^15, as fp16 hi + lo through two MFMAs; the zeros enter a
+//    per-(group, row) bias sum_d q_d z_d.  An exponent per group instead of
+//    one per (group, row), and mixed-precision multiply-adds that read q' as
+//    fp16, halve the fold's instructions (800 -> 350 for 32 rows).
 //  * the V scale is folded into the softmax weight, pw_t = p_t s_t 2^-Ev
-//    (fp16, rounded to nearest; Ev per wavefront from the largest V scale of
-//    its tokens, so pw <= 1 while p <= 1, and a weight beyond the fp16 range
-//    becomes infinite and sends the wavefront to the running-maximum path);
-//    sum_t p_t z_t is summed in fp32 and the offset is measured by one MFMA
-//    against the constant 1024.  The 2^-Ev factor rides on the softmax
-//    reference, so l, sum p z and the products all carry it and one multiply
-//    restores it when the wavefronts are merged.
+//    (fp16, rounded to nearest; Ev per wavefront, so that pw <= 1 while p <= 1,
+//    and a weight beyond the fp16 range becomes infinite and sends the
+//    wavefront to the running-maximum path); sum_t p_t z_t is summed in fp32.
+//    The 2^-Ev factor rides on the softmax reference, so l, sum p z and the
+//    products all carry it and one multiply restores it when the wavefronts
+//    are merged.
 //
-// Work split: grid = (context split of SG 128-token groups, kv head x chunk
-// of 16 RT query rows, sequence); 4 wavefronts per workgroup, two
-// workgroups per CU.  Wavefront w owns the groups w, w + 4, ... of the split
+// Work split: grid = (worker, kv head x chunk of 16 RT query rows), as many
+// workers as the chip holds at once (two workgroups of 4 wavefronts per CU),
+// each with an equal share of the batch's 512-token units (work_list.h), a
+// segment per sequence it touches.  Wavefront w owns a segment's groups w,
+// w + 4, ...
 // and serves all RT row tiles from each of their 32-token tiles, so every
 // K/V byte is fetched once per workgroup and the query fold of a group
 // (q'' for the wavefront's own MFMA operand lanes) lives in its registers:
@@ -38,10 +43,11 @@
 // of the one being attended (no registers held by loads in flight); a
 // group's K metadata rides with its first tile, and the query rows are
 // copied into LDS once.  At the end the four wavefronts merge through LDS
-// into one partial per row and split.
+// into one partial per row and segment.
 #include "f16_ops.h"
 #include "lane_ops.h"
 #include "lynx_internal.h"
+#include "work_list.h"
 
 #include <math.h>
 
@@ -69,41 +75,30 @@ __device__ __forceinline__ uint32_t k_slot(int t, int q) {
 
 // LAYOUT 0: one block per sequence; 1: paged, block_tokens a multiple of 16;
 // 2: any other paging.  RT: 16-row query tiles per workgroup (1 or 2), all
-// served by every wavefront.  SG: 128-token groups per split (4, 8 or 16).
-template <int RT, int LAYOUT, int SG>
-__global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
+// served by every wavefront.  UNIT: 128-token groups per unit of the work list.
+// One segment of a worker's share, for kv head h and a chunk of 16 RT rows.
+template <int RT, int LAYOUT, int UNIT>
+__device__ __forceinline__ void verify_segment(const VerifyArgs &a, const Segment<UNIT> &seg, int h, int chunk,
+                                               const int tid) {
     constexpr int kRows = RT * 16;
     constexpr int NQ = kWaves;             // wavefront w takes groups w, w + 4, ...
-    constexpr int kMaxGroups = SG / NQ;    // groups per wavefront
-    static_assert(SG % NQ == 0, "groups must split evenly over the wavefronts");
+    static_assert(UNIT == NQ, "a group per wavefront and unit");
     const int Hkv = a.geo.Hkv;
-    // Grid (split, kv head x chunk, sequence) for the contiguous layout.  A
-    // paged block holds the rows of every kv head for its tokens side by side,
-    // so paged layouts make the kv head the fastest grid index: workgroups
-    // reading the same blocks run together and share DRAM pages.
-    const int split = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
-    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
-    const int h = hc % Hkv;
-    const int chunk = hc / Hkv;
-    const int b = blockIdx.z;
-    const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = tid >> 6;
     const int col = lane & 15;
     const int kg = lane >> 4;
     const int gq = w;  // this wavefront's groups: gq, gq + NQ, ...
-    const int T = max(0, min(a.seq_lens[b], a.max_seq_len));
-    const int g0 = split * SG;
-    const int n_groups = max(0, min(SG, (T - g0 * kKGroup + kKGroup - 1) / kKGroup));
+    const int b = seg.b, T = seg.T, g0 = seg.g0, n_groups = seg.n_groups;
     const int row_base = chunk * kRows;  // first query row of the workgroup
     const float kscore = kLog2e * rsqrtf((float)kHeadDim);
 
     // query row r <-> (draft r / G, head r % G); its partial-output row
     auto partial_index = [&](int r) {
-        return (((size_t)b * Hkv + h) * a.rows_total + r) * a.ws_splits + split;
+        return ((size_t)h * a.rows_total + r) * a.n_seg + seg.number;
     };
 
-    if (n_groups == 0) {  // a split past the context: (max, sum) = (-inf, 0)
+    if (n_groups == 0) {  // an empty sequence: (max, sum) = (-inf, 0)
         for (int r = tid; r < kRows; r += kThreads)
             if (row_base + r < a.rows_total) a.ws_ml[partial_index(row_base + r)] = make_float2(-INFINITY, 0.0f);
         return;
@@ -113,11 +108,15 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
     // epilogue reuses the ring
     __shared__ __attribute__((aligned(16))) uint8_t s_ring[kWaves * kDepth * kSlotBytes];
     __shared__ __attribute__((aligned(16))) uint8_t s_km[kWaves][kKMetaBytes];
-    __shared__ __attribute__((aligned(16))) uint8_t s_q[kRows * kHeadDim * 2];  // BF16 query rows
+    // query rows: BF16, then fp16 q' (and Eq)
+    __shared__ __attribute__((aligned(16))) uint8_t s_q[kRows * kHeadDim * 2];
+    __shared__ int s_eq[kRows];
     __shared__ int s_ev[kWaves];
     __shared__ float s_ML[kRows][2];
     static_assert(kWaves * kRows * (kHeadDim + 4) * 4 <= kWaves * kDepth * kSlotBytes,
                   "the epilogue's arrays must fit in the ring");
+    // LAYOUT 1: the blocks of a group's eight 16-token runs, for two groups
+    __shared__ int32_t s_ids[LAYOUT == 1 ? kWaves : 1][2][8];
 
     bool bad = false;
     const int32_t *bt_row = a.block_table + (size_t)b * a.geo.max_blocks;
@@ -146,42 +145,34 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
     auto tile_t0 = [&](int j) { return (g0 + group_of(j)) * kKGroup + kTile * (j & 3); };
     auto tile_valid = [&](int j) { return (j >> 2) < n_mine && tile_t0(j) < T; };
 
-    // ---- the largest V scale of the wavefront's tokens (plain loads, all
-    // consumed before the first copy) ----
+    // ---- the exponent of the largest V scale, from the wavefront's first
+    // group (plain loads, consumed before the first copy): a later, larger one
+    // gives weights above 1, and past the fp16 range an infinity that sends the
+    // wavefront to the slow path, which looks at all of its scales, as does a
+    // first group without any ----
     int Ev = 0;
-    {
-        float vm = 0.0f;
-#pragma unroll 4
-        for (int u = 0; u < kMaxGroups; ++u) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int t = (g0 + gq + NQ * u) * kKGroup + 64 * k + lane;
-                if (u < n_mine && t < T) vm = fmax2(vm, a.meta.v_scale[vmeta + t]);
-            }
-        }
+    auto v_scale_at = [&](int u, int k) {
+        const int t = (g0 + gq + NQ * u) * kKGroup + 64 * k + lane;
+        return u < n_mine && t < T ? a.meta.v_scale[vmeta + t] : 0.0f;
+    };
+    auto set_ev = [&](float vm) {
         vm = max_kg(row16_max(vm));
+        Ev = 0;
         if (vm > 0.0f) frexpf(vm, &Ev);
         // V scales below 2^-100 contribute below 255 * 2^-100 per token; the
         // clamp keeps 2^-Ev, and so the weights p 2^-Ev, finite
         Ev = max(Ev, -100);
-    }
-    // LAYOUT 1: the block of every 16-token run the wavefront attends (lane
-    // 8 u + r: run r of its group u), looked up here so that a full tile's
-    // copies take their blocks by readlane instead of waiting on a
-    // block-table load each.  Lanes past the wavefront's groups read a
-    // clamped, unused entry.
-    int run_blk = 0;
-    if (LAYOUT == 1) {
-        const int u = lane >> 3;
-        if (u < kMaxGroups) {
-            const int tr = (g0 + gq + NQ * u) * kKGroup + 16 * (lane & 7);
-            const int bi = a.bt_shift >= 0 ? (tr >> a.bt_shift) : tr / a.geo.bt;
-            run_blk = bt_row[min(bi, a.geo.max_blocks - 1)];
-        }
-    }
-    // every plain load has been consumed (Ev and run_blk depend on all of
-    // them): nothing of the compiler's own is in flight once the copies start
-    asm volatile("" ::"v"(Ev), "v"(run_blk) : "memory");
+        return vm > 0.0f;
+    };
+    auto set_ev_all = [&]() {
+        float vm = 0.0f;
+        for (int u = 0; u < n_mine; ++u) vm = fmax2(vm, fmax2(v_scale_at(u, 0), v_scale_at(u, 1)));
+        set_ev(vm);
+    };
+    if (!set_ev(fmax2(v_scale_at(0, 0), v_scale_at(0, 1)))) set_ev_all();
+    // every plain load has been consumed (Ev depends on all of them): nothing
+    // of the compiler's own is in flight once the copies start
+    asm volatile("" ::"v"(Ev) : "memory");
     wait_vmcnt<0>();
 
     // ---- copies into the ring ----
@@ -191,13 +182,28 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
     const int kq = (lane & 7) ^ crow;  // K, and V rows 0..15
     const uint32_t ring = lds_addr(s_ring) + (uint32_t)w * kDepth * kSlotBytes;
     const uint8_t *ring_p = s_ring + (size_t)w * kDepth * kSlotBytes;
-    // copies per tile: 4 K + 4 V + 1 V metadata, + 1 K metadata (into the
-    // wavefront's K-metadata buffer) for a group's first tile
+    // copies per tile: 4 K + 4 V + 1 V metadata; with a group's first tile
+    // also its K metadata (into the wavefront's K-metadata buffer) and, for
+    // LAYOUT 1, the next group's block ids
     const uint32_t km = lds_addr(&s_km[w][0]);
+    constexpr int kFirst = LAYOUT == 1 ? 11 : 10;  // copies of a group's first tile
+
+    // LAYOUT 1: the blocks of the wavefront's group u, run r in lane r, into
+    // s_ids, one group ahead of its tiles, whose copies then take them by readlane
+    // instead of waiting on a block-table load each.  Past the
+    // wavefront's groups the entries are clamped and unused.
+    auto issue_ids = [&](int u) {
+        if (LAYOUT != 1) return;
+        const int tr = (g0 + gq + NQ * u) * kKGroup + 16 * lane;
+        const int bi = a.bt_shift >= 0 ? (tr >> a.bt_shift) : tr / a.geo.bt;
+        if (lane < 8) lds_copy4(bt_row + min(bi, a.geo.max_blocks - 1), lds_addr(&s_ids[LAYOUT == 1 ? w : 0][u & 1][0]));
+    };
 
     // Tile j of this wavefront into ring slot j % kDepth.
+    int ids = 0;  // LAYOUT 1: block ids of the group being issued, run r in lane r
     auto issue_tile = [&](int j) {
         const int t0 = __builtin_amdgcn_readfirstlane(tile_t0(j));
+        if (LAYOUT == 1 && (j & 3) == 0) ids = s_ids[LAYOUT == 1 ? w : 0][(j >> 2) & 1][lane & 7];
         const uint32_t slot = ring + (uint32_t)(j % kDepth) * kSlotBytes;
         if (LAYOUT != 2 && t0 + kTile <= T) {
             // two 16-token runs, each inside one block
@@ -210,7 +216,7 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
                     const int tr = t0 + 16 * run;
                     const int bi = a.bt_shift >= 0 ? (tr >> a.bt_shift) : tr / a.geo.bt;
                     // run 2 (j % 4) + run of the wavefront's group j / 4
-                    int blk = __builtin_amdgcn_readlane(run_blk, 8 * (j >> 2) + 2 * (j & 3) + run);
+                    int blk = __builtin_amdgcn_readlane(ids, 2 * (j & 3) + run);
                     if (blk < 0 || blk >= a.geo.num_blocks) {
                         bad = true;
                         blk = 0;
@@ -249,6 +255,7 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
             const int g = g0 + min(group_of(j), n_groups - 1);
             const float *src = (lane < 32 ? a.meta.k_scale : a.meta.k_zero) + kmeta + (size_t)g * kHeadDim;
             lds_copy16(src + 4 * (lane & 31), km);
+            if (n_mine > 1) issue_ids((j >> 2) + 1);  // (a wavefront's only group has no next)
         }
     };
 
@@ -258,14 +265,15 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
     for (int k = 0; k < RT; ++k) {
         const int m = w + 4 * k;
         const int r = min(row_base + 4 * m + (lane >> 4), a.rows_total - 1);
-        const size_t qrow = ((size_t)b * a.nq + r / a.G) * a.Hq + (size_t)h * a.G + r % a.G;
+        const int G = fresh_uniform(a.G);
+        const size_t qrow = ((size_t)b * a.nq + r / G) * a.Hq + (size_t)h * G + r % G;
         lds_copy16(a.q + qrow * kHeadDim + 8 * (lane & 15), lds_addr(s_q) + 1024u * m);
     }
 
     // ---- per-wavefront online-softmax state: lane (col = query row of the
     // row tile, kg); the reference carries the 2^-Ev factor of the V weights ----
     float m_run[RT], m_ref[RT], l_part[RT], ob_part[RT];
-    f32x4_t acc[RT][8], acc_off[RT];
+    f32x4_t acc[RT][8];
     auto reset_state = [&]() {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
@@ -273,78 +281,69 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
             l_part[rt] = ob_part[rt] = 0.0f;
 #pragma unroll
             for (int n = 0; n < 8; ++n) acc[rt][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            acc_off[rt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         }
     };
     reset_state();
-    const u32x4_t c1024 = {0x64006400u, 0x64006400u, 0x64006400u, 0x64006400u};
 
     // Fold of a group (K scales and zeros from the wavefront's K-metadata
-    // buffer, query rows from LDS), per row tile: q''_d = q_d s_d 2^-E as fp16
-    // hi + lo MFMA operands, score scale 2^E kscore and bias
-    // kscore sum_d q_d (z_d - 1024 s_d), E per row.  Lane (col, kg) holds
-    // dims 32 kg .. + 31 of row col, the dims of its MFMA operand pieces.
+    // buffer, query rows from LDS): the operands y_d = q'_d s_d 2^(15 - Es), hi
+    // and lo, and per row the products' scale bsc = kscore 2^(Eq + Es + 9) and
+    // the bias bb = kscore 2^Eq sum_d q'_d z_d.  Lane (col, kg) holds dims
+    // 32 kg .. + 31 of row col of each row tile, the dims of its operand pieces.
     u32x4_t bq[RT][8];
     float bsc[RT], bb[RT];
     auto fold = [&]() {
-        const float *ks = reinterpret_cast<const float *>(&s_km[w][0]) + 32 * kg;
-        const float *kz = ks + kHeadDim;
+        const float4 *ks = reinterpret_cast<const float4 *>(&s_km[w][0]) + 8 * kg;
+        const float4 *kz = ks + kHeadDim / 4;
+        float mx = 0.0f;
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const int rl = rt * 16 + col;
-            const bool row_live = row_base + rl < a.rows_total;
-            const uint4 *qp = reinterpret_cast<const uint4 *>(s_q + rl * (kHeadDim * 2) + 64 * kg);
-            // pass 1: row maximum of |q s| and the bias
-            float mx = 0.0f, bias = 0.0f;
+        for (int k = 0; k < 8; ++k) {
+            const float4 u = ks[k];
+            mx = fmax3(mx, fmax2(u.x, u.y), fmax2(u.z, u.w));
+        }
+        mx = max_kg(mx);
+        int Es = 0;
+        if (mx > 0.0f) frexpf(mx, &Es);
+        float bias[RT];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint4 u = qp[k];
-                const float qv[8] = {bf16_lo(u.x), bf16_hi(u.x), bf16_lo(u.y), bf16_hi(u.y),
-                                     bf16_lo(u.z), bf16_hi(u.z), bf16_lo(u.w), bf16_hi(u.w)};
-                const float4 s0 = reinterpret_cast<const float4 *>(ks)[2 * k];
-                const float4 s1 = reinterpret_cast<const float4 *>(ks)[2 * k + 1];
-                const float4 z0 = reinterpret_cast<const float4 *>(kz)[2 * k];
-                const float4 z1 = reinterpret_cast<const float4 *>(kz)[2 * k + 1];
-                const float sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
-                const float zv[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
+        for (int rt = 0; rt < RT; ++rt) bias[rt] = 0.0f;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    mx = fmax2(mx, fabsf(qv[e] * sv[e]));
-                    bias = fmaf(qv[e], fmaf(-1024.0f, sv[e], zv[e]), bias);
-                }
-            }
-            mx = max_kg(mx);
-            bias = sum_kg(bias);
-            int E = 0;
-            if (mx > 0.0f) frexpf(mx, &E);  // mx = f 2^E, f in [0.5, 1)
-            // pass 2: the scaled products (the same roundings as pass 1)
+        for (int kk = 0; kk < 4; ++kk) {
+            const float4 s0 = ks[2 * kk], s1 = ks[2 * kk + 1], z0 = kz[2 * kk], z1 = kz[2 * kk + 1];
+            const float sv[8] = {ldexpf(s0.x, 15 - Es), ldexpf(s0.y, 15 - Es), ldexpf(s0.z, 15 - Es),
+                                 ldexpf(s0.w, 15 - Es), ldexpf(s1.x, 15 - Es), ldexpf(s1.y, 15 - Es),
+                                 ldexpf(s1.z, 15 - Es), ldexpf(s1.w, 15 - Es)};
+            const float zv[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const uint4 u = qp[kk];
-                const float qv[8] = {bf16_lo(u.x), bf16_hi(u.x), bf16_lo(u.y), bf16_hi(u.y),
-                                     bf16_lo(u.z), bf16_hi(u.z), bf16_lo(u.w), bf16_hi(u.w)};
-                const float4 s0 = reinterpret_cast<const float4 *>(ks)[2 * kk];
-                const float4 s1 = reinterpret_cast<const float4 *>(ks)[2 * kk + 1];
-                const float sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+            for (int rt = 0; rt < RT; ++rt) {
+                const uint4 u =
+                    reinterpret_cast<const uint4 *>(s_q + (rt * 16 + col) * (kHeadDim * 2) + 64 * kg)[kk];
+                const uint32_t qw[4] = {u.x, u.y, u.z, u.w};
                 u32x4_t hi, lo;
 #pragma unroll
-                for (int e = 0; e < 8; e += 2) {
-                    const float y0 = row_live ? ldexpf(qv[e] * sv[e], -E) : 0.0f;
-                    const float y1 = row_live ? ldexpf(qv[e + 1] * sv[e + 1], -E) : 0.0f;
+                for (int e = 0; e < 4; ++e) {
+                    const float y0 = fma_f16_lo(qw[e], sv[2 * e], 0.0f), y1 = fma_f16_hi(qw[e], sv[2 * e + 1], 0.0f);
+                    bias[rt] = fma_f16_lo(qw[e], zv[2 * e], bias[rt]);
+                    bias[rt] = fma_f16_hi(qw[e], zv[2 * e + 1], bias[rt]);
                     const uint32_t hp = pack_f16(y0, y1);
-                    hi[e / 2] = hp;
-                    lo[e / 2] = pack_f16(y0 - f16_lo(hp), y1 - f16_hi(hp));
+                    hi[e] = hp;
+                    lo[e] = pack_f16(less_f16_lo(y0, hp), less_f16_hi(y1, hp));
                 }
                 bq[rt][2 * kk] = hi;
                 bq[rt][2 * kk + 1] = lo;
             }
-            bsc[rt] = ldexpf(kscore, E);
-            bb[rt] = row_live ? bias * kscore : 0.0f;
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            const int eq = s_eq[rt * 16 + col];
+            bsc[rt] = ldexpf(kscore, eq + Es + 9);
+            bb[rt] = ldexpf(kscore * sum_kg(bias[rt]), eq);
         }
     };
-    // Scores of tile j in log2 units: lane (col, kg) gets token
-    // t0 + 16 r + 4 kg + i in x[4 r + i]; tokens past the context get -inf.
-    auto tile_scores = [&](const uint8_t *slot_p, int j, float (&x)[RT][8]) {
+    // Products of tile j (scores in log2 units are bsc times them, plus bb):
+    // lane (col, kg) gets token t0 + 16 r + 4 kg + i in x[4 r + i]; tokens past
+    // the context get -inf.
+    auto tile_products = [&](const uint8_t *slot_p, int j, float (&x)[RT][8]) {
         f32x4_t sc[RT][2];
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
@@ -367,7 +366,7 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) x[rt][i] = fmaf(sc[rt][i >> 2][i & 3], bsc[rt], bb[rt]);
+            for (int i = 0; i < 8; ++i) x[rt][i] = sc[rt][i >> 2][i & 3];
         const int t0 = tile_t0(j);
         if (t0 + kTile > T) {
             asm volatile("" ::: "memory");
@@ -379,8 +378,10 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
             }
         }
     };
-    auto tile_max = [&](const float (&x)[8]) {
-        return max_kg(fmax3(fmax3(x[0], x[1], x[2]), fmax3(x[3], x[4], x[5]), fmax2(x[6], x[7])));
+    // the row's largest score of a tile (bsc >= 0)
+    auto tile_max = [&](const float (&x)[8], int rt) {
+        const float mx = max_kg(fmax3(fmax3(x[0], x[1], x[2]), fmax3(x[3], x[4], x[5]), fmax2(x[6], x[7])));
+        return fmaf(mx, bsc[rt], bb[rt]);
     };
     // Weights against m_ref, then P V for the tile (V rows from the slot,
     // transposed on read).
@@ -396,9 +397,10 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             float pw[8];
+            const float c0 = bb[rt] - m_ref[rt];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const float p = __builtin_amdgcn_exp2f(x[rt][i] - m_ref[rt]);
+                const float p = __builtin_amdgcn_exp2f(fmaf(x[rt][i], bsc[rt], c0));
                 l_part[rt] += p;
                 ob_part[rt] = fmaf(p, vzv[i], ob_part[rt]);
                 pw[i] = p * vsv[i];
@@ -419,24 +421,37 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) acc[rt][c] = mfma_f16(pa[rt], bv, acc[rt][c]);
         }
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) acc_off[rt] = mfma_f16(pa[rt], c1024, acc_off[rt]);
     };
 
     // Fast path: the softmax reference of each row is the maximum of the
     // wavefront's first tile and stays fixed.  If any sum leaves the safe
     // range the wavefront redoes its tiles below with a running maximum.
     // Tile j + 1 is in flight while tile j is attended; no barriers.
-    if (n_mine > 0) issue_tile(0);
-    // the query rows are in once only tile 0's copies may remain in flight
-    if (n_mine > 0) {
-        wait_vmcnt<10>();
-    } else {
+    if (LAYOUT == 1) {
+        issue_ids(0);
         wait_vmcnt<0>();
     }
+    if (n_mine > 0) issue_tile(0);
+    // the query rows are in once only tile 0's copies may remain in flight
+    // (LAYOUT 1 waited for them above)
+    if (LAYOUT != 1) {
+        if (n_mine > 0) {
+            wait_vmcnt<kFirst>();
+        } else {
+            wait_vmcnt<0>();
+        }
+    }
     __syncthreads();
-    for (int u = 0; u < kMaxGroups; ++u) {
-        if (u >= n_mine) break;  // wavefront-uniform
+    // BF16 rows -> fp16 q' in place: 16 neighbouring threads hold a row
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        uint4 *qp = reinterpret_cast<uint4 *>(s_q) + kThreads * r + tid;
+        int eq;
+        *qp = rows_to_f16(*qp, eq);
+        if ((tid & 15) == 0) s_eq[16 * r + (tid >> 4)] = eq;
+    }
+    __syncthreads();
+    for (int u = 0; u < n_mine; ++u) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int j = 4 * u + c;
@@ -447,7 +462,7 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
             if (!more) {
                 wait_vmcnt<0>();
             } else if (c == 3) {
-                wait_vmcnt<10>();
+                wait_vmcnt<kFirst>();
             } else {
                 wait_vmcnt<9>();
             }
@@ -455,11 +470,11 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
             if (c == 0) fold();
             if (tile_valid(j)) {
                 float x[RT][8];
-                tile_scores(slot_p, j, x);
+                tile_products(slot_p, j, x);
                 if (j == 0) {
 #pragma unroll
                     for (int rt = 0; rt < RT; ++rt) {
-                        m_run[rt] = tile_max(x[rt]);
+                        m_run[rt] = tile_max(x[rt], rt);
                         m_ref[rt] = m_run[rt] + (float)Ev;
                     }
                 }
@@ -478,13 +493,14 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
         for (int n = 0; n < 8; ++n)
 #pragma unroll
             for (int i = 0; i < 4; ++i) unsafe |= !(fabsf(acc[rt][n][i]) < 1e30f);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) unsafe |= !(fabsf(acc_off[rt][i]) < 1e30f);
     }
     if (__any(unsafe)) {
         // Slow path (this wavefront only): running maximum with rescaling,
         // one tile fetched and waited for at a time.
         reset_state();
+        set_ev_all();
+        issue_ids(0);
+        wait_vmcnt<0>();
         for (int j = 0; j < 4 * n_mine; ++j) {
             issue_tile(j);
             wait_vmcnt<0>();
@@ -492,10 +508,10 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
             if ((j & 3) == 0) fold();
             if (tile_valid(j)) {
                 float x[RT][8];
-                tile_scores(slot_p, j, x);
+                tile_products(slot_p, j, x);
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
-                    const float mx = tile_max(x[rt]);
+                    const float mx = tile_max(x[rt], rt);
                     if (__any(mx > m_run[rt])) {
                         const float m_new = fmaxf(mx, m_run[rt]);
                         const float alpha = (m_run[rt] == -INFINITY) ? 0.0f : exp2f(m_run[rt] - m_new);
@@ -510,8 +526,6 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
                         for (int n = 0; n < 8; ++n)
 #pragma unroll
                             for (int i = 0; i < 4; ++i) acc[rt][n][i] *= af[i];
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) acc_off[rt][i] *= af[i];
                     }
                 }
                 tile_accumulate(slot_p, x);
@@ -521,8 +535,12 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
     }
     wait_vmcnt<0>();  // no copy may land in the ring once it is reused below
 
+    // The epilogue's lane numbers are its own: kept through the loop they would
+    // take registers that it has none of.
+    [&](const int tid) {
+    const int lane = tid & 63, w = tid >> 6, col = lane & 15, kg = lane >> 4;
     // ---- per-wavefront totals -> LDS (still scaled by 2^-Ev) ----
-    // o' = sum p' z + sum pw (1024 + c) - 1024 sum pw
+    // o' = sum p' z + 2^24 sum pw c 2^-24
     __syncthreads();  // every wavefront is done with its ring
     // ring reused: o [wave][kRows][128], then max, sum, sum p z and merge
     // factors [wave][kRows]
@@ -544,12 +562,12 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int c = 0; c < 8; ++c)
-                s_o[(w * kRows + rt * 16 + 4 * kg + i) * kHeadDim + 16 * c + col] = acc[rt][c][i] - acc_off[rt][i];
+                s_o[(w * kRows + rt * 16 + 4 * kg + i) * kHeadDim + 16 * c + col] = acc[rt][c][i] * 16777216.0f;
     }
     if (lane == 0) s_ev[w] = Ev;
     const bool any_bad = __syncthreads_or(bad);
 
-    // ---- merge the four wavefronts, write this split's partial: per-row
+    // ---- merge the four wavefronts, write this segment's partial: per-row
     // factors first, then float4 multiply-adds ----
     if (tid < kRows) {
         float M = -INFINITY;
@@ -596,49 +614,70 @@ __global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
             __builtin_nontemporal_store(mlv, reinterpret_cast<f32x2_t *>(a.ws_ml + pi));
         }
     }
+    }(fresh_tid());
+}
+
+// Grid (worker, kv head x chunk) for the contiguous layout.  A paged block
+// holds the rows of every kv head for its tokens side by side, so paged
+// layouts make the kv head the fastest grid index: workgroups reading the
+// same blocks run together and share DRAM pages.
+template <int RT, int LAYOUT, int UNIT>
+__global__ __launch_bounds__(kThreads, 2) void verify_batch_kernel(VerifyArgs a) {
+    const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
+    const WorkList<UNIT, true> list(a.seq_lens, a.B, a.max_seq_len, a.workers);
+    if (worker >= list.workers) return;
+    Segment<UNIT> seg;
+    seg.start(list, worker);
+    for (;;) {
+        verify_segment<RT, LAYOUT, UNIT>(a, seg, fresh_uniform(hc % a.geo.Hkv), fresh_uniform(hc / a.geo.Hkv), fresh_tid());
+        if (!seg.next(list, worker)) return;
+        __syncthreads();  // the segment's LDS is free again
+    }
+}
+
+// A single sequence: one segment per worker, no walk.
+template <int RT, int LAYOUT, int UNIT>
+__global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
+    const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
+    const WorkList<UNIT, false> list(a.seq_lens, 1, a.max_seq_len, a.workers);
+    if (worker >= list.workers) return;
+    Segment<UNIT> seg;
+    seg.start(list, worker);
+    verify_segment<RT, LAYOUT, UNIT>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
 }
 
 template <int RT, int LAYOUT>
-void launch_rt(const VerifyArgs &args, int split_groups, dim3 grid, hipStream_t stream) {
-    if (split_groups == 4)
-        hipLaunchKernelGGL((verify_kernel<RT, LAYOUT, 4>), grid, dim3(kThreads), 0, stream, args);
-    else if (LAYOUT == 0 && split_groups == 32)
-        hipLaunchKernelGGL((verify_kernel<RT, 0, 32>), grid, dim3(kThreads), 0, stream, args);
-    else if (LAYOUT == 0 && split_groups == 64)
-        hipLaunchKernelGGL((verify_kernel<RT, 0, 64>), grid, dim3(kThreads), 0, stream, args);
-    else if (split_groups == 8)
-        hipLaunchKernelGGL((verify_kernel<RT, LAYOUT, 8>), grid, dim3(kThreads), 0, stream, args);
+void launch_rt(const VerifyArgs &args, dim3 grid, hipStream_t stream) {
+    if (args.B == 1)
+        hipLaunchKernelGGL((verify_kernel<RT, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
     else
-        hipLaunchKernelGGL((verify_kernel<RT, LAYOUT, 16>), grid, dim3(kThreads), 0, stream, args);
+        hipLaunchKernelGGL((verify_batch_kernel<RT, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
 }
 
 template <int RT>
-void launch_layout(const VerifyArgs &args, int split_groups, dim3 grid, hipStream_t stream) {
+void launch_layout(const VerifyArgs &args, dim3 grid, hipStream_t stream) {
     if (args.geo.max_blocks == 1)
-        launch_rt<RT, 0>(args, split_groups, grid, stream);
+        launch_rt<RT, 0>(args, grid, stream);
     else if (args.geo.bt % 16 == 0)
-        launch_rt<RT, 1>(args, split_groups, grid, stream);
+        launch_rt<RT, 1>(args, grid, stream);
     else
-        launch_rt<RT, 2>(args, split_groups, grid, stream);
+        launch_rt<RT, 2>(args, grid, stream);
 }
 
 }  // namespace
 
-hipError_t launch_verify_mfma(const VerifyArgs &args, int split_groups, hipStream_t stream) {
-    if (split_groups != 4 && split_groups != 8 && split_groups != 16 &&
-        !(args.geo.max_blocks == 1 && (split_groups == 32 || split_groups == 64)))
-        return hipErrorInvalidValue;
-    if (args.rows_total < 1) return hipErrorInvalidValue;
+hipError_t launch_verify_mfma(const VerifyArgs &args, hipStream_t stream) {
+    if (args.rows_total < 1 || args.workers < 1 || args.workers > 65535) return hipErrorInvalidValue;
     const int rt = args.rows_total <= 16 ? 1 : 2;
-    const int chunks = (args.rows_total + 16 * rt - 1) / (16 * rt);
+    const unsigned hc = (unsigned)(args.geo.Hkv * ((args.rows_total + 16 * rt - 1) / (16 * rt)));
     // kv head fastest for paged layouts (the kernel reads the grid the same way)
-    if (args.geo.max_blocks != 1 && args.n_ctx_splits > 65535) return hipErrorInvalidValue;
-    const unsigned hc = (unsigned)(args.geo.Hkv * chunks);
-    const dim3 grid = args.geo.max_blocks == 1 ? dim3(args.n_ctx_splits, hc, args.B) : dim3(hc, args.n_ctx_splits, args.B);
+    const dim3 grid = args.geo.max_blocks == 1 ? dim3(args.workers, hc) : dim3(hc, args.workers);
     if (rt == 1)
-        launch_layout<1>(args, split_groups, grid, stream);
+        launch_layout<1>(args, grid, stream);
     else
-        launch_layout<2>(args, split_groups, grid, stream);
+        launch_layout<2>(args, grid, stream);
     return hipGetLastError();
 }
 

@@ -343,6 +343,48 @@ def test_anchor_decode_ragged_batch_stale_workspace():
     np.testing.assert_allclose(lse.cpu().numpy(), ref_lse, rtol=LSE_RTOL, atol=LSE_ATOL)
 
 
+@pytest.mark.parametrize("lens,Hkv,bt", [
+    ([0, 5000, 1, 0, 513, 512, 3000, 511], 2, 16),      # shares that straddle sequences, empty ones between
+    ([30000, 40, 9000], 8, 16),                         # one sequence over many workers, others inside one
+    ([30000, 40, 9000], 8, None),
+    ([700 + 37 * i % 900 for i in range(70)], 1, 16),   # more sequences than a wavefront's lanes
+    ([1 + 13 * i % 600 for i in range(130)], 8, 24),    # more (sequence, kv head) pairs than counters; blocks of 24
+    ([2048] * 40, 8, None),                             # whole units only, several a worker
+])
+def test_attention_work_list(lens, Hkv, bt):
+    """The attention kernels' work list: equal shares of a ragged batch's units,
+    whichever sequences they fall in, through every merge of their partials
+    (one worker's own, the last workgroup's, the combine kernels') for the
+    decode, the decode with a tail and the verification."""
+    G, nq = 2, 5
+    B = len(lens)
+    kv = [random_kv(T, Hkv, seed=2600 + T) for T in lens]
+    c = build_cache([a for a, _ in kv], [b for _, b in kv], Hkv, bt=bt, seed=4, max_tokens=max(lens))
+    q = random_bf16((B, Hkv * G, 128), seed=2601)
+    qv = random_bf16((B, nq, Hkv * G, 128), seed=2602)
+    kt, vt = random_bf16((B, nq, Hkv, 128), seed=2603), random_bf16((B, nq, Hkv, 128), seed=2604)
+    larr = np.array(lens, np.int32)
+    out, lse = gpu_anchor_decode(c, q)
+    ref, ref_lse = oracle.anchor_decode(c.OL, Hkv * G, larr, c.table.numpy(), c.planes["k_anc"], c.planes["v_anc"],
+                                        c.meta, bits(q))
+    assert_close(out, ref, what="decode")
+    fin = np.isfinite(ref_lse)
+    assert np.array_equal(fin, np.isfinite(lse))
+    np.testing.assert_allclose(lse[fin], ref_lse[fin], rtol=LSE_RTOL, atol=LSE_ATOL)
+    out, lse = gpu_anchor_decode_tail(c, q, kt, vt)
+    ref, ref_lse = oracle.anchor_decode(c.OL, Hkv * G, larr, c.table.numpy(), c.planes["k_anc"], c.planes["v_anc"],
+                                        c.meta, bits(q), k_tail_bits=bits(kt), v_tail_bits=bits(vt))
+    assert_close(out, ref, what="decode with a tail")
+    np.testing.assert_allclose(lse, ref_lse, rtol=LSE_RTOL, atol=LSE_ATOL)
+    kc = oracle.merge(c.planes["k_anc"], c.planes["k_res"])
+    vc = oracle.merge(c.planes["v_anc"], c.planes["v_res"])
+    for tail in (True, False):
+        got = gpu_verify(c, qv, kt if tail else None, vt if tail else None)
+        ref, _ = oracle.verify(c.OL, Hkv * G, larr, c.table.numpy(), kc, vc, c.meta, bits(qv),
+                               bits(kt) if tail else None, bits(vt) if tail else None)
+        assert_close(got, ref, what=f"verification, tail {tail}")
+
+
 def test_attention_calls_share_one_workspace():
     """Decode calls of different batch shapes, a decode with a BF16 tail (the
     combine kernel) and a verification pass take turns on one workspace: each
