@@ -42,9 +42,11 @@ class lynx_meta(ctypes.Structure):
 _lib = None
 
 
+_HMETA_NAMES = ("k_gmin", "k_gscale", "k_mu", "k_sigma", "v_gmin", "v_gscale", "v_mu", "v_sigma")
+
+
 class lynx_hmeta(ctypes.Structure):
-    _fields_ = [(name, ctypes.c_void_p) for name in
-                ("k_gmin", "k_gscale", "k_mu", "k_sigma", "v_gmin", "v_gscale", "v_mu", "v_sigma")]
+    _fields_ = [(name, ctypes.c_void_p) for name in _HMETA_NAMES]
 
 
 def load():
@@ -114,6 +116,9 @@ def _ptr(t):
 
 def _stream(stream):
     if stream is None:
+        if torch.cuda.is_initialized():
+            # the same handle without a Stream object around it (1.4 us a call)
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
@@ -127,34 +132,54 @@ def _check(fn: str, status: int):
 
 # Size checks of the tensors a call reads or writes.  The C ABI sees only
 # pointers, so a short tensor would become an out-of-bounds device access:
-# the binding rejects it first.
-def _nbytes(t) -> int:
-    return t.numel() * t.element_size()
+# the binding rejects it first.  A call makes a dozen of these, and a short
+# kernel waits for them (the checks and the pointers in one function each,
+# sizes computed once a call: an anchor decode 14.2 -> 10.5 us on the host).
+def _arg(fn: str, what: str, t, nbytes: int):
+    """The device pointer of tensor `t`, which holds at least nbytes bytes; an
+    int is a pointer already, None is NULL."""
+    if t is None:
+        return None
+    if isinstance(t, int):
+        return t
+    if t.nbytes < nbytes:
+        raise ValueError(f"{fn}: {what} holds {t.nbytes} bytes; the call uses {nbytes}")
+    if not t.is_cuda:
+        raise ValueError("liblynx takes device tensors")
+    if not t.is_contiguous():
+        raise ValueError("liblynx takes contiguous tensors")
+    return t.data_ptr()
 
 
-def _need(fn: str, what: str, t, nbytes: int) -> None:
-    if isinstance(t, torch.Tensor) and _nbytes(t) < nbytes:
-        raise ValueError(f"{fn}: {what} holds {_nbytes(t)} bytes; the call uses {nbytes}")
-
-
-def _need_meta(fn: str, L: "Layout", meta: "Meta", rows: int) -> None:
+def _meta_arg(fn: str, L: "Layout", meta: "Meta", rows: int) -> lynx_meta:
     """fp32 metadata rows 0 .. rows - 1 (sequences) of the layout."""
-    k = rows * L.num_kv_heads * L.n_groups * HEAD_DIM * 4
-    v = rows * L.num_kv_heads * L.max_tokens * 4
-    for name, nbytes in (("k_scale", k), ("k_zero", k), ("v_scale", v), ("v_zero", v)):
-        _need(fn, f"meta.{name}", getattr(meta, name), nbytes)
+    heads = rows * L.num_kv_heads
+    k = heads * -(-L.max_tokens // K_GROUP) * HEAD_DIM * 4
+    v = heads * L.max_tokens * 4
+    return lynx_meta(_arg(fn, "meta.k_scale", meta.k_scale, k), _arg(fn, "meta.k_zero", meta.k_zero, k),
+                     _arg(fn, "meta.v_scale", meta.v_scale, v), _arg(fn, "meta.v_zero", meta.v_zero, v))
 
 
-def _need_attn(fn: str, L: "Layout", B: int, seq_lens, block_table, planes, row_bytes: int,
-               meta: "Meta") -> None:
-    """The per-batch arguments every attention call reads."""
+def _hmeta_arg(fn: str, L: "Layout", hmeta: "HMeta", rows: int) -> lynx_hmeta:
+    heads = rows * L.num_kv_heads
+    page = heads * -(-L.max_tokens // 256) * HEAD_DIM * 4
+    chunk = heads * -(-L.max_tokens // 32) * HEAD_DIM * 4
+    return lynx_hmeta(*(_arg(fn, f"hmeta.{name}", getattr(hmeta, name), page if name[2] == "g" else chunk)
+                        for name in _HMETA_NAMES))
+
+
+def _attn_args(fn: str, L: "Layout", B: int, Hq: int, seq_lens, block_table, k_plane, v_plane, row_bytes: int,
+               meta: "Meta", q, nq: int = 1):
+    """The arguments every attention call starts with, up to q."""
     if B <= 0:
-        return
-    _need(fn, "seq_lens", seq_lens, B * 4)
-    _need(fn, "block_table", block_table, B * L.max_blocks_per_seq * 4)
-    for i, t in enumerate(planes):
-        _need(fn, f"plane {i}", t, L.plane_bytes(row_bytes))
-    _need_meta(fn, L, meta, B)
+        return (ctypes.byref(L.c()),), (_ptr(seq_lens), _ptr(block_table), _ptr(k_plane), _ptr(v_plane),
+                                        ctypes.byref(meta.c()), _ptr(q))
+    plane = L.plane_bytes(row_bytes)
+    return (ctypes.byref(L.c()),), (
+        _arg(fn, "seq_lens", seq_lens, B * 4),
+        _arg(fn, "block_table", block_table, B * L.max_blocks_per_seq * 4),
+        _arg(fn, "plane 0", k_plane, plane), _arg(fn, "plane 1", v_plane, plane),
+        ctypes.byref(_meta_arg(fn, L, meta, B)), _arg(fn, "q", q, B * nq * Hq * HEAD_DIM * 2))
 
 
 @dataclass
@@ -205,16 +230,12 @@ class Meta:
 def lynx_kv_encode(L: Layout, b: int, T: int, block_table, k, v, k_anc, v_anc, k_res, v_res,
                    meta: Meta, stream=None) -> None:
     fn = "lynx_kv_encode"
-    _need(fn, "k", k, T * L.num_kv_heads * HEAD_DIM * 2)
-    _need(fn, "v", v, T * L.num_kv_heads * HEAD_DIM * 2)
-    _need(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4)
-    for name, t in (("k_anc", k_anc), ("v_anc", v_anc), ("k_res", k_res), ("v_res", v_res)):
-        _need(fn, name, t, L.plane_bytes(64))
-    _need_meta(fn, L, meta, b + 1)
-    lay, met = L.c(), meta.c()
-    _check("lynx_kv_encode", load().lynx_kv_encode(
-        ctypes.byref(lay), b, T, _ptr(block_table), _ptr(k), _ptr(v), _ptr(k_anc), _ptr(v_anc),
-        _ptr(k_res), _ptr(v_res), ctypes.byref(met), _stream(stream)))
+    n, plane = T * L.num_kv_heads * HEAD_DIM * 2, L.plane_bytes(64)
+    _check(fn, load().lynx_kv_encode(
+        ctypes.byref(L.c()), b, T, _arg(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4),
+        _arg(fn, "k", k, n), _arg(fn, "v", v, n), _arg(fn, "k_anc", k_anc, plane), _arg(fn, "v_anc", v_anc, plane),
+        _arg(fn, "k_res", k_res, plane), _arg(fn, "v_res", v_res, plane),
+        ctypes.byref(_meta_arg(fn, L, meta, b + 1)), _stream(stream)))
 
 
 def lynx_kv_merge(anc, res, codes, n_packed_bytes: int | None = None, stream=None) -> None:
@@ -248,16 +269,11 @@ def lynx_attn_anchor_decode(L: Layout, B: int, Hq: int, max_seq_len: int, seq_le
                             block_table, k_anc, v_anc, meta: Meta, q, out, lse=None,
                             workspace_buf=None, stream=None) -> None:
     fn = "lynx_attn_anchor_decode"
-    _need_attn(fn, L, B, seq_lens, block_table, (k_anc, v_anc), 64, meta)
-    _need(fn, "q", q, B * Hq * HEAD_DIM * 2)
-    _need(fn, "out", out, B * Hq * HEAD_DIM * 2)
-    _need(fn, "lse", lse, B * Hq * 4)
-    lay, met = L.c(), meta.c()
+    lay, args = _attn_args(fn, L, B, Hq, seq_lens, block_table, k_anc, v_anc, 64, meta, q)
     ws = workspace_buf
-    _check("lynx_attn_anchor_decode", load().lynx_attn_anchor_decode(
-        ctypes.byref(lay), B, Hq, max_seq_len, _ptr(seq_lens), _ptr(block_table), _ptr(k_anc),
-        _ptr(v_anc), ctypes.byref(met), _ptr(q), _ptr(out), _ptr(lse), _ptr(ws),
-        0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)))
+    _check(fn, load().lynx_attn_anchor_decode(
+        *lay, B, Hq, max_seq_len, *args, _arg(fn, "out", out, B * Hq * HEAD_DIM * 2), _arg(fn, "lse", lse, B * Hq * 4),
+        _ptr(ws), 0 if ws is None else ws.nbytes, _stream(stream)))
 
 
 def lynx_attn_anchor_decode_split(anchor_bits: int, L: Layout, B: int, Hq: int, max_seq_len: int,
@@ -267,16 +283,11 @@ def lynx_attn_anchor_decode_split(anchor_bits: int, L: Layout, B: int, Hq: int, 
     fn = "lynx_attn_anchor_decode_split"
     if anchor_bits not in (2, 4, 6):
         raise LynxError(fn, LYNX_EINVAL)
-    _need_attn(fn, L, B, seq_lens, block_table, (k_anc, v_anc), 16 * anchor_bits, meta)
-    _need(fn, "q", q, B * Hq * HEAD_DIM * 2)
-    _need(fn, "out", out, B * Hq * HEAD_DIM * 2)
-    _need(fn, "lse", lse, B * Hq * 4)
-    lay, met = L.c(), meta.c()
+    lay, args = _attn_args(fn, L, B, Hq, seq_lens, block_table, k_anc, v_anc, 16 * anchor_bits, meta, q)
     ws = workspace_buf
     _check(fn, load().lynx_attn_anchor_decode_split(
-        anchor_bits, ctypes.byref(lay), B, Hq, max_seq_len, _ptr(seq_lens), _ptr(block_table),
-        _ptr(k_anc), _ptr(v_anc), ctypes.byref(met), _ptr(q), _ptr(out), _ptr(lse), _ptr(ws),
-        0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)))
+        anchor_bits, *lay, B, Hq, max_seq_len, *args, _arg(fn, "out", out, B * Hq * HEAD_DIM * 2),
+        _arg(fn, "lse", lse, B * Hq * 4), _ptr(ws), 0 if ws is None else ws.nbytes, _stream(stream)))
 
 
 # Scratch held by the library for lynx_attn_anchor_decode_noalloc (lynx.h).
@@ -289,14 +300,10 @@ def lynx_attn_anchor_decode_noalloc(L: Layout, B: int, Hq: int, max_seq_len: int
     """lynx_attn_anchor_decode without a workspace: the library's own static
     scratch (calls that overlap on one GPU race)."""
     fn = "lynx_attn_anchor_decode_noalloc"
-    _need_attn(fn, L, B, seq_lens, block_table, (k_anc, v_anc), 64, meta)
-    _need(fn, "q", q, B * Hq * HEAD_DIM * 2)
-    _need(fn, "out", out, B * Hq * HEAD_DIM * 2)
-    _need(fn, "lse", lse, B * Hq * 4)
-    lay, met = L.c(), meta.c()
-    _check("lynx_attn_anchor_decode_noalloc", load().lynx_attn_anchor_decode_noalloc(
-        ctypes.byref(lay), B, Hq, max_seq_len, _ptr(seq_lens), _ptr(block_table), _ptr(k_anc),
-        _ptr(v_anc), ctypes.byref(met), _ptr(q), _ptr(out), _ptr(lse), _stream(stream)))
+    lay, args = _attn_args(fn, L, B, Hq, seq_lens, block_table, k_anc, v_anc, 64, meta, q)
+    _check(fn, load().lynx_attn_anchor_decode_noalloc(
+        *lay, B, Hq, max_seq_len, *args, _arg(fn, "out", out, B * Hq * HEAD_DIM * 2),
+        _arg(fn, "lse", lse, B * Hq * 4), _stream(stream)))
 
 
 def lynx_attn_anchor_decode_tail(L: Layout, B: int, Hq: int, max_seq_len: int, seq_lens,
@@ -305,22 +312,14 @@ def lynx_attn_anchor_decode_tail(L: Layout, B: int, Hq: int, max_seq_len: int, s
     """Anchor decode that also attends the BF16 tail k_tail / v_tail
     ([B][n_tail][Hkv][128], or None for n_tail = 0)."""
     fn = "lynx_attn_anchor_decode_tail"
-    _need_attn(fn, L, B, seq_lens, block_table, (k_anc, v_anc), 64, meta)
-    _need(fn, "q", q, B * Hq * HEAD_DIM * 2)
-    _need(fn, "out", out, B * Hq * HEAD_DIM * 2)
-    _need(fn, "lse", lse, B * Hq * 4)
-    if k_tail is not None:
-        nt = int(k_tail.shape[1])
-        _need(fn, "k_tail", k_tail, B * nt * L.num_kv_heads * HEAD_DIM * 2)
-        _need(fn, "v_tail", v_tail, B * nt * L.num_kv_heads * HEAD_DIM * 2)
-    lay, met = L.c(), meta.c()
-    ws = workspace_buf
+    lay, args = _attn_args(fn, L, B, Hq, seq_lens, block_table, k_anc, v_anc, 64, meta, q)
     n_tail = 0 if k_tail is None else int(k_tail.shape[1])
-    _check("lynx_attn_anchor_decode_tail", load().lynx_attn_anchor_decode_tail(
-        ctypes.byref(lay), B, Hq, max_seq_len, _ptr(seq_lens), _ptr(block_table), _ptr(k_anc),
-        _ptr(v_anc), ctypes.byref(met), _ptr(q), n_tail, _ptr(k_tail), _ptr(v_tail), _ptr(out),
-        _ptr(lse), _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(),
-        _stream(stream)))
+    n = B * n_tail * L.num_kv_heads * HEAD_DIM * 2
+    ws = workspace_buf
+    _check(fn, load().lynx_attn_anchor_decode_tail(
+        *lay, B, Hq, max_seq_len, *args, n_tail, _arg(fn, "k_tail", k_tail, n),
+        _ptr(v_tail) if k_tail is None else _arg(fn, "v_tail", v_tail, n), _arg(fn, "out", out, B * Hq * HEAD_DIM * 2),
+        _arg(fn, "lse", lse, B * Hq * 4), _ptr(ws), 0 if ws is None else ws.nbytes, _stream(stream)))
 
 
 def lynx_spec_accept_workspace_bytes(B: int, k: int, vocab: int) -> int:
@@ -339,7 +338,7 @@ def lynx_spec_accept_greedy(target_logits, draft_tokens, accepted, next_token,
         ws = torch.empty(max(n, 16), dtype=torch.uint8, device=target_logits.device)
     _check("lynx_spec_accept_greedy", load().lynx_spec_accept_greedy(
         B, k1 - 1, V, _ptr(target_logits), _ptr(draft_tokens), _ptr(accepted), _ptr(next_token),
-        _ptr(ws), ws.numel() * ws.element_size(), _stream(stream)))
+        _ptr(ws), ws.nbytes, _stream(stream)))
 
 
 def lynx_spec_accept_sample(target_probs, draft_probs, draft_tokens, uniforms, accepted,
@@ -355,25 +354,19 @@ def lynx_spec_accept_sample(target_probs, draft_probs, draft_tokens, uniforms, a
         ws = torch.empty(max(n, 16), dtype=torch.uint8, device=target_probs.device)
     _check("lynx_spec_accept_sample", load().lynx_spec_accept_sample(
         B, k1 - 1, V, _ptr(target_probs), _ptr(draft_probs), _ptr(draft_tokens), _ptr(uniforms),
-        _ptr(accepted), _ptr(next_token), _ptr(ws), ws.numel() * ws.element_size(), _stream(stream)))
+        _ptr(accepted), _ptr(next_token), _ptr(ws), ws.nbytes, _stream(stream)))
 
 
 def lynx_attn_verify(L: Layout, B: int, Hq: int, k: int, max_seq_len: int, seq_lens,
                      block_table, k_codes, v_codes, meta: Meta, q, k_new, v_new, out,
                      workspace_buf=None, stream=None) -> None:
     fn = "lynx_attn_verify"
-    _need_attn(fn, L, B, seq_lens, block_table, (k_codes, v_codes), 128, meta)
-    _need(fn, "q", q, B * k * Hq * HEAD_DIM * 2)
-    _need(fn, "out", out, B * k * Hq * HEAD_DIM * 2)
-    _need(fn, "k_new", k_new, B * k * L.num_kv_heads * HEAD_DIM * 2)
-    _need(fn, "v_new", v_new, B * k * L.num_kv_heads * HEAD_DIM * 2)
-    lay, met = L.c(), meta.c()
+    lay, args = _attn_args(fn, L, B, Hq, seq_lens, block_table, k_codes, v_codes, 128, meta, q, k)
+    n = B * k * L.num_kv_heads * HEAD_DIM * 2
     ws = workspace_buf
-    _check("lynx_attn_verify", load().lynx_attn_verify(
-        ctypes.byref(lay), B, Hq, k, max_seq_len, _ptr(seq_lens), _ptr(block_table),
-        _ptr(k_codes), _ptr(v_codes), ctypes.byref(met), _ptr(q), _ptr(k_new), _ptr(v_new),
-        _ptr(out), _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(),
-        _stream(stream)))
+    _check(fn, load().lynx_attn_verify(
+        *lay, B, Hq, k, max_seq_len, *args, _arg(fn, "k_new", k_new, n), _arg(fn, "v_new", v_new, n),
+        _arg(fn, "out", out, B * k * Hq * HEAD_DIM * 2), _ptr(ws), 0 if ws is None else ws.nbytes, _stream(stream)))
 
 
 # ----------------------------------------------------------------------------
@@ -410,18 +403,16 @@ def lynx_kv_encode_split(L: Layout, anchor_bits: int, b: int, T: int, block_tabl
     """k, v: BF16 [T][Hkv][128]; planes: uint8 device tensors of rows of
     16 anchor_bits (anchor) and 16 (8 - anchor_bits) (residual) bytes."""
     fn = "lynx_kv_encode_split"
-    _need(fn, "k", k, T * L.num_kv_heads * HEAD_DIM * 2)
-    _need(fn, "v", v, T * L.num_kv_heads * HEAD_DIM * 2)
-    _need(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4)
-    if 0 < anchor_bits < 8:
-        for name, t, w in (("k_anc", k_anc, anchor_bits), ("v_anc", v_anc, anchor_bits),
-                           ("k_res", k_res, 8 - anchor_bits), ("v_res", v_res, 8 - anchor_bits)):
-            _need(fn, name, t, L.plane_bytes(16 * w))
-    _need_meta(fn, L, meta, b + 1)
-    lay, met = L.c(), meta.c()
-    _check("lynx_kv_encode_split", load().lynx_kv_encode_split(
-        ctypes.byref(lay), anchor_bits, b, T, _ptr(block_table), _ptr(k), _ptr(v), _ptr(k_anc),
-        _ptr(v_anc), _ptr(k_res), _ptr(v_res), ctypes.byref(met), _stream(stream)))
+    n = T * L.num_kv_heads * HEAD_DIM * 2
+    # (a width that the library rejects needs no plane)
+    wa, wr = (anchor_bits, 8 - anchor_bits) if 0 < anchor_bits < 8 else (0, 0)
+    anc, res = L.plane_bytes(16 * wa), L.plane_bytes(16 * wr)
+    _check(fn, load().lynx_kv_encode_split(
+        ctypes.byref(L.c()), anchor_bits, b, T,
+        _arg(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4), _arg(fn, "k", k, n),
+        _arg(fn, "v", v, n), _arg(fn, "k_anc", k_anc, anc), _arg(fn, "v_anc", v_anc, anc),
+        _arg(fn, "k_res", k_res, res), _arg(fn, "v_res", v_res, res),
+        ctypes.byref(_meta_arg(fn, L, meta, b + 1)), _stream(stream)))
 
 
 def lynx_kv_merge_split(anchor_bits: int, anc, res, codes, stream=None) -> None:
@@ -438,17 +429,13 @@ def lynx_kv_dequant_anchor_split(L: Layout, anchor_bits: int, b: int, T: int, bl
                                  meta: Meta, k_out, v_out, stream=None) -> None:
     """k_out, v_out: BF16 [T][Hkv][128] (device, written)."""
     fn = "lynx_kv_dequant_anchor_split"
-    _need(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4)
-    if 0 < anchor_bits < 8:
-        _need(fn, "k_anc", k_anc, L.plane_bytes(16 * anchor_bits))
-        _need(fn, "v_anc", v_anc, L.plane_bytes(16 * anchor_bits))
-    _need_meta(fn, L, meta, b + 1)
-    _need(fn, "k_out", k_out, T * L.num_kv_heads * HEAD_DIM * 2)
-    _need(fn, "v_out", v_out, T * L.num_kv_heads * HEAD_DIM * 2)
-    lay, met = L.c(), meta.c()
-    _check("lynx_kv_dequant_anchor_split", load().lynx_kv_dequant_anchor_split(
-        ctypes.byref(lay), anchor_bits, b, T, _ptr(block_table), _ptr(k_anc), _ptr(v_anc),
-        ctypes.byref(met), _ptr(k_out), _ptr(v_out), _stream(stream)))
+    n = T * L.num_kv_heads * HEAD_DIM * 2
+    anc = L.plane_bytes(16 * anchor_bits) if 0 < anchor_bits < 8 else 0
+    _check(fn, load().lynx_kv_dequant_anchor_split(
+        ctypes.byref(L.c()), anchor_bits, b, T,
+        _arg(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4), _arg(fn, "k_anc", k_anc, anc),
+        _arg(fn, "v_anc", v_anc, anc), ctypes.byref(_meta_arg(fn, L, meta, b + 1)), _arg(fn, "k_out", k_out, n),
+        _arg(fn, "v_out", v_out, n), _stream(stream)))
 
 
 # codec variants of the hierarchical codec (lynx.h LYNX_HQ_*)
@@ -459,44 +446,24 @@ def lynx_hkv_encode(L: Layout, b: int, T: int, block_table, k, v, alpha: float, 
                     k_anc, v_anc, k_res, v_res, hmeta: HMeta, stream=None) -> None:
     """k_res, v_res may be None for LYNX_HQ_INT4."""
     fn = "lynx_hkv_encode"
-    _need(fn, "k", k, T * L.num_kv_heads * HEAD_DIM * 2)
-    _need(fn, "v", v, T * L.num_kv_heads * HEAD_DIM * 2)
-    _need(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4)
-    for name, t in (("k_anc", k_anc), ("v_anc", v_anc), ("k_res", k_res), ("v_res", v_res)):
-        _need(fn, name, t, L.plane_bytes(64))
-    pg = (b + 1) * L.num_kv_heads * -(-L.max_tokens // 256) * HEAD_DIM * 4
-    ch = (b + 1) * L.num_kv_heads * -(-L.max_tokens // 32) * HEAD_DIM * 4
-    for t in ("k", "v"):
-        _need(fn, f"hmeta.{t}_gmin", getattr(hmeta, f"{t}_gmin"), pg)
-        _need(fn, f"hmeta.{t}_gscale", getattr(hmeta, f"{t}_gscale"), pg)
-        _need(fn, f"hmeta.{t}_mu", getattr(hmeta, f"{t}_mu"), ch)
-        _need(fn, f"hmeta.{t}_sigma", getattr(hmeta, f"{t}_sigma"), ch)
-    lay, met = L.c(), hmeta.c()
-    _check("lynx_hkv_encode", load().lynx_hkv_encode(
-        ctypes.byref(lay), b, T, _ptr(block_table), _ptr(k), _ptr(v), alpha, variant, _ptr(k_anc),
-        _ptr(v_anc), _ptr(k_res), _ptr(v_res), ctypes.byref(met), _stream(stream)))
+    n, plane = T * L.num_kv_heads * HEAD_DIM * 2, L.plane_bytes(64)
+    _check(fn, load().lynx_hkv_encode(
+        ctypes.byref(L.c()), b, T, _arg(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4),
+        _arg(fn, "k", k, n), _arg(fn, "v", v, n), alpha, variant, _arg(fn, "k_anc", k_anc, plane),
+        _arg(fn, "v_anc", v_anc, plane), _arg(fn, "k_res", k_res, plane), _arg(fn, "v_res", v_res, plane),
+        ctypes.byref(_hmeta_arg(fn, L, hmeta, b + 1)), _stream(stream)))
 
 
 def lynx_hkv_dequant(L: Layout, b: int, T: int, block_table, full: bool, k_plane, v_plane,
                      alpha: float, variant: int, hmeta: HMeta, k_out, v_out, stream=None) -> None:
     """k_out, v_out: BF16 [T][Hkv][128] (device, written)."""
     fn = "lynx_hkv_dequant"
-    _need(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4)
-    _need(fn, "k_plane", k_plane, L.plane_bytes(128 if full else 64))
-    _need(fn, "v_plane", v_plane, L.plane_bytes(128 if full else 64))
-    _need(fn, "k_out", k_out, T * L.num_kv_heads * HEAD_DIM * 2)
-    _need(fn, "v_out", v_out, T * L.num_kv_heads * HEAD_DIM * 2)
-    pg = (b + 1) * L.num_kv_heads * -(-L.max_tokens // 256) * HEAD_DIM * 4
-    ch = (b + 1) * L.num_kv_heads * -(-L.max_tokens // 32) * HEAD_DIM * 4
-    for t in ("k", "v"):
-        _need(fn, f"hmeta.{t}_gmin", getattr(hmeta, f"{t}_gmin"), pg)
-        _need(fn, f"hmeta.{t}_gscale", getattr(hmeta, f"{t}_gscale"), pg)
-        _need(fn, f"hmeta.{t}_mu", getattr(hmeta, f"{t}_mu"), ch)
-        _need(fn, f"hmeta.{t}_sigma", getattr(hmeta, f"{t}_sigma"), ch)
-    lay, met = L.c(), hmeta.c()
-    _check("lynx_hkv_dequant", load().lynx_hkv_dequant(
-        ctypes.byref(lay), b, T, _ptr(block_table), 1 if full else 0, _ptr(k_plane), _ptr(v_plane),
-        alpha, variant, ctypes.byref(met), _ptr(k_out), _ptr(v_out), _stream(stream)))
+    n, plane = T * L.num_kv_heads * HEAD_DIM * 2, L.plane_bytes(128 if full else 64)
+    _check(fn, load().lynx_hkv_dequant(
+        ctypes.byref(L.c()), b, T, _arg(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4),
+        1 if full else 0, _arg(fn, "k_plane", k_plane, plane), _arg(fn, "v_plane", v_plane, plane), alpha, variant,
+        ctypes.byref(_hmeta_arg(fn, L, hmeta, b + 1)), _arg(fn, "k_out", k_out, n), _arg(fn, "v_out", v_out, n),
+        _stream(stream)))
 
 
 def lynx_serialized_bytes(num_kv_heads: int, n_tokens: int) -> tuple[int, int]:
@@ -512,46 +479,37 @@ def lynx_kv_serialize(num_kv_heads: int, n_tokens: int, k, v, anchor_buf, residu
     """k, v: BF16 [n_tokens][Hkv][128] (an object's tokens); the buffers are
     uint8 device tensors of lynx_serialized_bytes() bytes."""
     fn = "lynx_kv_serialize"
-    _need(fn, "k", k, n_tokens * num_kv_heads * HEAD_DIM * 2)
-    _need(fn, "v", v, n_tokens * num_kv_heads * HEAD_DIM * 2)
+    n, na, nr = n_tokens * num_kv_heads * HEAD_DIM * 2, 0, 0
     if num_kv_heads > 0 and n_tokens > 0:
         na, nr = lynx_serialized_bytes(num_kv_heads, n_tokens)
-        _need(fn, "anchor_buf", anchor_buf, na)
-        _need(fn, "residual_buf", residual_buf, nr)
-    _check("lynx_kv_serialize", load().lynx_kv_serialize(
-        num_kv_heads, n_tokens, _ptr(k), _ptr(v), _ptr(anchor_buf), _ptr(residual_buf),
-        _stream(stream)))
+    _check(fn, load().lynx_kv_serialize(
+        num_kv_heads, n_tokens, _arg(fn, "k", k, n), _arg(fn, "v", v, n), _arg(fn, "anchor_buf", anchor_buf, na),
+        _arg(fn, "residual_buf", residual_buf, nr), _stream(stream)))
 
 
 def lynx_kv_deserialize_anchor(L: Layout, b: int, t0: int, n_tokens: int, block_table, anchor_buf,
                                k_anc, v_anc, meta: Meta, stream=None) -> None:
     fn = "lynx_kv_deserialize_anchor"
-    _need(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4)
-    if n_tokens > 0:
-        _need(fn, "anchor_buf", anchor_buf, lynx_serialized_bytes(L.num_kv_heads, n_tokens)[0])
-    _need(fn, "k_anc", k_anc, L.plane_bytes(64))
-    _need(fn, "v_anc", v_anc, L.plane_bytes(64))
-    _need_meta(fn, L, meta, b + 1)
-    lay, met = L.c(), meta.c()
-    _check("lynx_kv_deserialize_anchor", load().lynx_kv_deserialize_anchor(
-        ctypes.byref(lay), b, t0, n_tokens, _ptr(block_table), _ptr(anchor_buf), _ptr(k_anc),
-        _ptr(v_anc), ctypes.byref(met), _stream(stream)))
+    na = lynx_serialized_bytes(L.num_kv_heads, n_tokens)[0] if n_tokens > 0 else 0
+    plane = L.plane_bytes(64)
+    _check(fn, load().lynx_kv_deserialize_anchor(
+        ctypes.byref(L.c()), b, t0, n_tokens,
+        _arg(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4),
+        _arg(fn, "anchor_buf", anchor_buf, na), _arg(fn, "k_anc", k_anc, plane), _arg(fn, "v_anc", v_anc, plane),
+        ctypes.byref(_meta_arg(fn, L, meta, b + 1)), _stream(stream)))
 
 
 def lynx_kv_deserialize_residual(L: Layout, b: int, t0: int, n_tokens: int, block_table,
                                  residual_buf, k_anc, v_anc, k_codes, v_codes,
                                  stream=None) -> None:
     fn = "lynx_kv_deserialize_residual"
-    _need(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4)
-    if n_tokens > 0:
-        _need(fn, "residual_buf", residual_buf, lynx_serialized_bytes(L.num_kv_heads, n_tokens)[1])
-    for name, t, rb in (("k_anc", k_anc, 64), ("v_anc", v_anc, 64), ("k_codes", k_codes, 128),
-                        ("v_codes", v_codes, 128)):
-        _need(fn, name, t, L.plane_bytes(rb))
-    lay = L.c()
-    _check("lynx_kv_deserialize_residual", load().lynx_kv_deserialize_residual(
-        ctypes.byref(lay), b, t0, n_tokens, _ptr(block_table), _ptr(residual_buf), _ptr(k_anc),
-        _ptr(v_anc), _ptr(k_codes), _ptr(v_codes), _stream(stream)))
+    nr = lynx_serialized_bytes(L.num_kv_heads, n_tokens)[1] if n_tokens > 0 else 0
+    plane = L.plane_bytes(64)
+    _check(fn, load().lynx_kv_deserialize_residual(
+        ctypes.byref(L.c()), b, t0, n_tokens,
+        _arg(fn, "block_table", block_table, (b + 1) * L.max_blocks_per_seq * 4),
+        _arg(fn, "residual_buf", residual_buf, nr), _arg(fn, "k_anc", k_anc, plane), _arg(fn, "v_anc", v_anc, plane),
+        _arg(fn, "k_codes", k_codes, 2 * plane), _arg(fn, "v_codes", v_codes, 2 * plane), _stream(stream)))
 
 
 @dataclass
