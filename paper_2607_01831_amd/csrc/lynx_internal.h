@@ -66,8 +66,8 @@ struct HTables {
     float theta[128];
     float level[128];
     float alevel[8];
-    float alpha, yscale;
-    int linear, levels;
+    float alpha_h, one_h, yscale, yhalf;  // log2(one_h + alpha_h x) * yscale: the transform less half a code
+    int linear;                           // x - yhalf in the logarithm's place
 };
 void make_htables(float alpha, int variant, HTables *t);
 hipError_t launch_hencode(const Geometry &g, int b, int T, const int32_t *block_table,

@@ -102,6 +102,19 @@ def test_hier_paged(T, bt, variant):
     run_case(k, v, 255.0, bt=bt, seed=T, variant=variant)
 
 
+@pytest.mark.parametrize("T,bt", [(33, None), (255, None), (545, None), (300, 48), (513, 96), (289, 24)])
+def test_hier_chunk_edges(T, bt):
+    """One token in the last chunk and one short of a page; blocks that hold
+    whole chunks (96), whole dequantization runs only (48), or neither (24);
+    signed zeros under a zero minimum and a constant ragged chunk."""
+    k, v = random_kv(T, 3, seed=2300 + T)
+    k[:, 0, :8] = torch.where(torch.arange(T)[:, None] % 2 == 0, -0.0, 0.0).to(k.dtype)
+    k[:, 1, :8] = torch.where(torch.arange(T)[:, None] % 3 == 0, -0.0, 2.5).to(k.dtype)
+    v[T - T % 32:, 2, :8] = -1.25
+    run_case(k, v, 255.0, bt=bt, seed=T, variant="biased")
+    run_case(k, v, 5e-4, bt=bt, seed=T, variant="centred")
+
+
 def test_hier_adversarial():
     """Constant and two-valued channels, signed zeros, denormals, huge values,
     a constant chunk inside a varying page, and exact sign-of-zero cases."""
