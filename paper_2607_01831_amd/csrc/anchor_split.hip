@@ -55,6 +55,7 @@
 #include "split_merge.h"
 #include "work_list.h"
 
+#include <float.h>
 #include <math.h>
 
 namespace lynx {
@@ -432,7 +433,9 @@ __device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const S
             bq[2 * kk + 1] = lo;
         }
         const int eq = s_eq[col];
-        bsc = ldexpf(kscore, 9 + R + eq + Es);
+        // positive and finite: times the -inf of a token past the context and
+        // times a product of 0 it must not be a NaN
+        bsc = __builtin_amdgcn_fmed3f(ldexpf(kscore, 9 + R + eq + Es), FLT_MIN, FLT_MAX);
         bb = ldexpf(kscore * sum_kg(bias), eq);
     };
 

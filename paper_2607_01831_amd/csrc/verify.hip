@@ -49,6 +49,7 @@
 #include "lynx_internal.h"
 #include "work_list.h"
 
+#include <float.h>
 #include <math.h>
 
 namespace lynx {
@@ -336,7 +337,9 @@ __device__ __forceinline__ void verify_segment(const VerifyArgs &a, const Segmen
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             const int eq = s_eq[rt * 16 + col];
-            bsc[rt] = ldexpf(kscore, eq + Es + 9);
+            // positive and finite: times the -inf of a token past the context
+            // and times a product of 0 it must not be a NaN
+            bsc[rt] = __builtin_amdgcn_fmed3f(ldexpf(kscore, eq + Es + 9), FLT_MIN, FLT_MAX);
             bb[rt] = ldexpf(kscore * sum_kg(bias[rt]), eq);
         }
     };
@@ -378,7 +381,7 @@ __device__ __forceinline__ void verify_segment(const VerifyArgs &a, const Segmen
             }
         }
     };
-    // the row's largest score of a tile (bsc >= 0)
+    // the row's largest score of a tile (bsc > 0)
     auto tile_max = [&](const float (&x)[8], int rt) {
         const float mx = max_kg(fmax3(fmax3(x[0], x[1], x[2]), fmax3(x[3], x[4], x[5]), fmax2(x[6], x[7])));
         return fmaf(mx, bsc[rt], bb[rt]);

@@ -224,6 +224,19 @@ def test_verify_dominant_late_token(boost):
     assert_close(out, ref, what=f"verify dominant token x{boost}")
 
 
+def test_verify_tiny_queries_and_keys():
+    """Queries and keys of about 1e-24: the scale of the products underflows,
+    and the tokens past the context in the last tile must still weigh nothing
+    (the scores are all 0: every output is the mean of V)."""
+    T, Hkv, G, nq = 700, 2, 4, 5
+    k, v = random_kv(T, Hkv, seed=960)
+    c = build_cache([(k.float() * 1e-24).to(torch.bfloat16)], [v], Hkv)
+    q = (random_bf16((1, nq, Hkv * G, 128), seed=961).float() * 1e-24).to(torch.bfloat16)
+    out = gpu_verify(c, q)
+    ref, _ = oracle_verify(c, q)
+    assert_close(out, ref, what="verify, tiny queries and keys")
+
+
 @pytest.mark.slow
 def test_verify_eight_group_splits():
     """64K context x 8 kv heads, k = 8: the plan picks 1024-token splits (8

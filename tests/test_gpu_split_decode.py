@@ -213,3 +213,15 @@ def test_split_decode_extreme_scales(A, scale):
                                               op["v_anc"], om, bits(q))
     assert_close(out.astype(np.float64) / scale, ref.astype(np.float64) / scale, what=f"A={A} V x{scale}")
     np.testing.assert_allclose(lse, ref_lse, rtol=LSE_RTOL, atol=LSE_ATOL)
+
+
+@pytest.mark.parametrize("A", [2, 4, 6])
+def test_split_decode_tiny_queries_and_keys(A):
+    """Queries and keys of about 1e-24: the scale of the products underflows,
+    and the tokens past the context in the last tile must still weigh nothing."""
+    T, Hkv, G = 700, 2, 4
+    k, v = random_kv(T, Hkv, seed=4900)
+    lens, L, OL, table, planes, meta, op, om = encode(A, [(k.float() * 1e-24).to(torch.bfloat16)], [v], Hkv)
+    q = (random_bf16((1, Hkv * G, 128), seed=4901).float() * 1e-24).to(torch.bfloat16)
+    out, lse = decode(A, lens, L, table, planes, meta, q)
+    check(A, lens, OL, table, op, om, q, out, lse, what=f"A={A} tiny queries and keys")
