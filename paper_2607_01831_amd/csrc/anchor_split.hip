@@ -22,8 +22,9 @@
 // spread; plain values 1.0e-7).  So every field's top bit is put at bit 7 or
 // above.  The position's factor 2^sh is a
 // constant of the dimension, so on the K side it is folded into the query
-// (y_d = q'_d s_d 2^(15 - Es - sh), with the K scale; fp16 hi + lo, |y| < 2^15,
-// Es the exponent of the group's largest scale), and on the V side into the output's scale at the end.
+// with the K scale (y_d = q_d s_d 2^(15 - E - sh), fp16 hi + lo, |y| < 2^15, E
+// the exponent of the row's largest fp32 product |q_d s_d| of the group), and
+// on the V side into the output's scale at the end.
 // V is read transposed by bytes (ds_read_b64_tr_b8): a byte of the plane holds
 // the same 4 (A = 2) or 2 (A = 4) dimensions for every token.  For A = 6 a
 // byte holds the end of one field and the start of another, which part being
@@ -189,8 +190,7 @@ __device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const S
     constexpr int kRingBytes = kWaves * kDepth * RG::kSlot;
     __shared__ __attribute__((aligned(16))) uint8_t s_ring[kRingBytes];
     __shared__ __attribute__((aligned(16))) uint8_t s_km[kWaves][kKMetaBytes];
-    __shared__ __attribute__((aligned(16))) uint8_t s_q[kRows * kHeadDim * 2];  // fp16 rows q'
-    __shared__ int s_eq[kRows];                                                 // and their exponents Eq
+    __shared__ __attribute__((aligned(16))) uint8_t s_q[kRows * kHeadDim * 2];  // BF16 query rows
     __shared__ int s_ev[kWaves];
     __shared__ float s_ML[kRows][2];
     static_assert((kWaves * kRows * kCols + 4 * kWaves * kRows) * 4 <= kRingBytes,
@@ -357,13 +357,7 @@ __device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const S
         set_ev(vm);
     };
     if (!set_ev(fmax2(vs_first[0], vs_first[1]))) set_ev_all();
-    // The query rows as fp16, q = 2^Eq q' with |q'| < 1 (8 bits of a BF16 value
-    // fit; a value below 2^-16 of its row's largest rounds at 2^-25 of that).
-    {
-        int eq;
-        reinterpret_cast<uint4 *>(s_q)[tid] = rows_to_f16(q4, eq);
-        if ((tid & 15) == 0) s_eq[tid >> 4] = eq;
-    }
+    reinterpret_cast<uint4 *>(s_q)[tid] = q4;
     __syncthreads();
 
     // ---- per-wavefront online-softmax state: lane (col = query row, kg);
@@ -378,27 +372,16 @@ __device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const S
     };
     reset_state();
     // Rows past the chunk's heads repeat the last one; their results go nowhere.
-    // Fold of a group (K scales and zeros from the K-metadata buffer, query
-    // rows q' from LDS): the operands y_d, hi and lo, the products' scale
-    // bsc = kscore 2^(24 + R + Eq + Es - 15) and the bias
-    // bb = kscore 2^Eq sum_d q'_d z'_d.
+    // Fold of a group (K scales and zeros from the K-metadata buffer, BF16 query
+    // rows from LDS): the operands y_d, hi and lo, the products' scale
+    // bsc = kscore 2^(24 + R + E - 15) and the bias bb = kscore sum_d q_d z'_d.
     u32x4_t bq[8];
     float bsc = 0.0f, bb = 0.0f;
     auto fold = [&]() {
         const float4 *ks = reinterpret_cast<const float4 *>(&s_km[w][0]) + 8 * kg;
         const float4 *kz = ks + kHeadDim / 4;
-        float mx = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float4 u = ks[k];
-            mx = fmax3(mx, fmax2(u.x, u.y), fmax2(u.z, u.w));
-        }
-        mx = max_kg(mx);
-        int Es = 0;
-        if (mx > 0.0f) frexpf(mx, &Es);
         const uint4 *qp = reinterpret_cast<const uint4 *>(s_q + col * (kHeadDim * 2) + 64 * kg);
-        float y[32];
-        float bias = 0.0f;
+        float y[32], mx = 0.0f, bias = 0.0f;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const uint4 u = qp[k];
@@ -408,17 +391,19 @@ __device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const S
             const float zv[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int ex = 15 - Es - KP::shift_of(8 * k + e);
-                const float zc = fmaf(centre, sv[e], zv[e]);
-                if (e & 1) {
-                    y[8 * k + e] = fma_f16_hi(qw[e / 2], ldexpf(sv[e], ex), 0.0f);
-                    bias = fma_f16_hi(qw[e / 2], zc, bias);
-                } else {
-                    y[8 * k + e] = fma_f16_lo(qw[e / 2], ldexpf(sv[e], ex), 0.0f);
-                    bias = fma_f16_lo(qw[e / 2], zc, bias);
-                }
+                const float q = e & 1 ? bf16_hi(qw[e / 2]) : bf16_lo(qw[e / 2]);
+                y[8 * k + e] = q * sv[e];
+                bias = fmaf(q, fmaf(centre, sv[e], zv[e]), bias);
             }
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) mx = fmax3_abs(mx, y[8 * k + e], y[8 * k + e + 1]);
+            asm volatile("" : "+v"(bias));  // summed here: later, all its terms would be held in registers
         }
+        mx = max_kg(mx);
+        int E = 0;
+        if (mx > 0.0f) frexpf(mx, &E);
+#pragma unroll
+        for (int d = 0; d < 32; ++d) y[d] = ldexpf(y[d], 15 - E - KP::shift_of(d));
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
             u32x4_t hi, lo;
@@ -432,11 +417,10 @@ __device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const S
             bq[2 * kk] = hi;
             bq[2 * kk + 1] = lo;
         }
-        const int eq = s_eq[col];
         // positive and finite: times the -inf of a token past the context and
         // times a product of 0 it must not be a NaN
-        bsc = __builtin_amdgcn_fmed3f(ldexpf(kscore, 9 + R + eq + Es), FLT_MIN, FLT_MAX);
-        bb = ldexpf(kscore * sum_kg(bias), eq);
+        bsc = __builtin_amdgcn_fmed3f(ldexpf(kscore, 9 + R + E), FLT_MIN, FLT_MAX);
+        bb = kscore * sum_kg(bias);
     };
 
     // This lane's K words of a tile: dims 32 kg .. + 31 of token 16 r + col.

@@ -41,12 +41,6 @@ typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_f16_rne(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, f16x2_t));
 }
-__device__ __forceinline__ float f16_lo(uint32_t w) {
-    return (float)__builtin_bit_cast(_Float16, (uint16_t)(w & 0xffffu));
-}
-__device__ __forceinline__ float f16_hi(uint32_t w) {
-    return (float)__builtin_bit_cast(_Float16, (uint16_t)(w >> 16));
-}
 // y less the fp16 in the low / high half of w, one instruction (the compiler
 // converts first).
 __device__ __forceinline__ float less_f16_lo(float y, uint32_t w) {
@@ -59,36 +53,8 @@ __device__ __forceinline__ float less_f16_hi(float y, uint32_t w) {
     asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(y));
     return r;
 }
-// x times the fp16 in the low / high half of w, plus c, rounded once.
-__device__ __forceinline__ float fma_f16_lo(uint32_t w, float x, float c) {
-    float r;
-    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(x), "v"(c));
-    return r;
-}
-__device__ __forceinline__ float fma_f16_hi(uint32_t w, float x, float c) {
-    float r;
-    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(x), "v"(c));
-    return r;
-}
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-
-// Eight BF16 values of a row that 16 neighbouring threads hold together
-// -> fp16 values q' = q 2^-E, E the exponent of the row's largest magnitude
-// (|q'| < 1; 0 for a row of zeros).
-__device__ __forceinline__ uint4 rows_to_f16(const uint4 &u, int &E) {
-    const uint32_t wv[4] = {u.x, u.y, u.z, u.w};
-    float mx = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) mx = fmax3(mx, fabsf(bf16_lo(wv[e])), fabsf(bf16_hi(wv[e])));
-    mx = row16_max(mx);
-    E = 0;
-    if (mx > 0.0f) frexpf(mx, &E);
-    uint32_t h[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) h[e] = pack_f16_rne(ldexpf(bf16_lo(wv[e]), -E), ldexpf(bf16_hi(wv[e]), -E));
-    return make_uint4(h[0], h[1], h[2], h[3]);
-}
 
 // Byte offset of 16-byte chunk q of V-tile row t (rows of 128 code bytes) in
 // an LDS tile.  The XOR swizzle spreads the 8 rows one transposed read

@@ -14,14 +14,12 @@
 // Exactness of the operands:
 //  * a code byte c stands as the fp16 subnormal c 2^-24, one v_perm per two
 //    values; the 2^24 goes into the scales below.
-//  * the query rows are scaled once to fp16, q = 2^Eq q' with |q'| < 1 (8 bits
-//    of a BF16 value fit; a value below 2^-16 of its row's largest rounds at
-//    2^-25 of that).  Per 128-token group the K scale is folded into them:
-//    y_d = q'_d s_d 2^(15 - Es), Es the exponent of the group's largest scale,
-//    |y| < 2^15, as fp16 hi + lo through two MFMAs; the zeros enter a
-//    per-(group, row) bias sum_d q_d z_d.  An exponent per group instead of
-//    one per (group, row), and mixed-precision multiply-adds that read q' as
-//    fp16, halve the fold's instructions (800 -> 350 for 32 rows).
+//  * the K scale is folded into the query per 128-token group: the products
+//    q_d s_d in fp32, scaled by the exponent E of the row's largest one,
+//    y_d = q_d s_d 2^(15 - E), |y| < 2^15, as fp16 hi + lo through two MFMAs;
+//    the zeros enter a per-(group, row) bias sum_d q_d z_d.  E comes from the
+//    products themselves: a large query value where K is flat, or a large K
+//    channel where the query is small, leaves the others their bits.
 //  * the V scale is folded into the softmax weight, pw_t = p_t s_t 2^-Ev
 //    (fp16, rounded to nearest; Ev per wavefront, so that pw <= 1 while p <= 1,
 //    and a weight beyond the fp16 range becomes infinite and sends the
@@ -37,7 +35,7 @@
 // w + 4, ...
 // and serves all RT row tiles from each of their 32-token tiles, so every
 // K/V byte is fetched once per workgroup and the query fold of a group
-// (q'' for the wavefront's own MFMA operand lanes) lives in its registers:
+// (y for the wavefront's own MFMA operand lanes) lives in its registers:
 // no barrier inside the loop.  Tiles, each with its V metadata, stream
 // into a private 2-slot LDS ring by global-to-LDS copies, one tile ahead
 // of the one being attended (no registers held by loads in flight); a
@@ -109,9 +107,7 @@ __device__ __forceinline__ void verify_segment(const VerifyArgs &a, const Segmen
     // epilogue reuses the ring
     __shared__ __attribute__((aligned(16))) uint8_t s_ring[kWaves * kDepth * kSlotBytes];
     __shared__ __attribute__((aligned(16))) uint8_t s_km[kWaves][kKMetaBytes];
-    // query rows: BF16, then fp16 q' (and Eq)
-    __shared__ __attribute__((aligned(16))) uint8_t s_q[kRows * kHeadDim * 2];
-    __shared__ int s_eq[kRows];
+    __shared__ __attribute__((aligned(16))) uint8_t s_q[kRows * kHeadDim * 2];  // BF16 query rows
     __shared__ int s_ev[kWaves];
     __shared__ float s_ML[kRows][2];
     static_assert(kWaves * kRows * (kHeadDim + 4) * 4 <= kWaves * kDepth * kSlotBytes,
@@ -287,60 +283,58 @@ __device__ __forceinline__ void verify_segment(const VerifyArgs &a, const Segmen
     reset_state();
 
     // Fold of a group (K scales and zeros from the wavefront's K-metadata
-    // buffer, query rows from LDS): the operands y_d = q'_d s_d 2^(15 - Es), hi
-    // and lo, and per row the products' scale bsc = kscore 2^(Eq + Es + 9) and
-    // the bias bb = kscore 2^Eq sum_d q'_d z_d.  Lane (col, kg) holds dims
-    // 32 kg .. + 31 of row col of each row tile, the dims of its operand pieces.
+    // buffer, BF16 query rows from LDS), per row tile: the operands
+    // y_d = q_d s_d 2^(15 - E), hi and lo, E the exponent of the row's largest
+    // |q_d s_d|; the products' scale bsc = kscore 2^(E + 9) and the bias
+    // bb = kscore sum_d q_d z_d.  Lane (col, kg) holds dims 32 kg .. + 31 of
+    // row col of each row tile, the dims of its operand pieces.
     u32x4_t bq[RT][8];
     float bsc[RT], bb[RT];
     auto fold = [&]() {
         const float4 *ks = reinterpret_cast<const float4 *>(&s_km[w][0]) + 8 * kg;
         const float4 *kz = ks + kHeadDim / 4;
-        float mx = 0.0f;
+        float y[RT][32], mx[RT], bias[RT];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float4 u = ks[k];
-            mx = fmax3(mx, fmax2(u.x, u.y), fmax2(u.z, u.w));
-        }
-        mx = max_kg(mx);
-        int Es = 0;
-        if (mx > 0.0f) frexpf(mx, &Es);
-        float bias[RT];
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) bias[rt] = 0.0f;
+        for (int rt = 0; rt < RT; ++rt) mx[rt] = bias[rt] = 0.0f;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
             const float4 s0 = ks[2 * kk], s1 = ks[2 * kk + 1], z0 = kz[2 * kk], z1 = kz[2 * kk + 1];
-            const float sv[8] = {ldexpf(s0.x, 15 - Es), ldexpf(s0.y, 15 - Es), ldexpf(s0.z, 15 - Es),
-                                 ldexpf(s0.w, 15 - Es), ldexpf(s1.x, 15 - Es), ldexpf(s1.y, 15 - Es),
-                                 ldexpf(s1.z, 15 - Es), ldexpf(s1.w, 15 - Es)};
+            const float sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
             const float zv[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
                 const uint4 u =
                     reinterpret_cast<const uint4 *>(s_q + (rt * 16 + col) * (kHeadDim * 2) + 64 * kg)[kk];
                 const uint32_t qw[4] = {u.x, u.y, u.z, u.w};
-                u32x4_t hi, lo;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float y0 = fma_f16_lo(qw[e], sv[2 * e], 0.0f), y1 = fma_f16_hi(qw[e], sv[2 * e + 1], 0.0f);
-                    bias[rt] = fma_f16_lo(qw[e], zv[2 * e], bias[rt]);
-                    bias[rt] = fma_f16_hi(qw[e], zv[2 * e + 1], bias[rt]);
-                    const uint32_t hp = pack_f16(y0, y1);
-                    hi[e] = hp;
-                    lo[e] = pack_f16(less_f16_lo(y0, hp), less_f16_hi(y1, hp));
+                    const float q0 = bf16_lo(qw[e]), q1 = bf16_hi(qw[e]);
+                    const float y0 = q0 * sv[2 * e], y1 = q1 * sv[2 * e + 1];
+                    bias[rt] = fmaf(q0, zv[2 * e], bias[rt]);
+                    bias[rt] = fmaf(q1, zv[2 * e + 1], bias[rt]);
+                    mx[rt] = fmax3_abs(mx[rt], y0, y1);
+                    y[rt][8 * kk + 2 * e] = y0;
+                    y[rt][8 * kk + 2 * e + 1] = y1;
                 }
-                bq[rt][2 * kk] = hi;
-                bq[rt][2 * kk + 1] = lo;
+                asm volatile("" : "+v"(bias[rt]));  // summed here: later, all its terms would be held in registers
             }
         }
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-            const int eq = s_eq[rt * 16 + col];
+            mx[rt] = max_kg(mx[rt]);
+            int E = 0;
+            if (mx[rt] > 0.0f) frexpf(mx[rt], &E);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float y0 = ldexpf(y[rt][2 * e], 15 - E), y1 = ldexpf(y[rt][2 * e + 1], 15 - E);
+                const uint32_t hp = pack_f16(y0, y1);
+                bq[rt][2 * (e / 4)][e % 4] = hp;
+                bq[rt][2 * (e / 4) + 1][e % 4] = pack_f16(less_f16_lo(y0, hp), less_f16_hi(y1, hp));  // exact differences
+            }
             // positive and finite: times the -inf of a token past the context
             // and times a product of 0 it must not be a NaN
-            bsc[rt] = __builtin_amdgcn_fmed3f(ldexpf(kscore, eq + Es + 9), FLT_MIN, FLT_MAX);
-            bb[rt] = ldexpf(kscore * sum_kg(bias[rt]), eq);
+            bsc[rt] = __builtin_amdgcn_fmed3f(ldexpf(kscore, E + 9), FLT_MIN, FLT_MAX);
+            bb[rt] = kscore * sum_kg(bias[rt]);
         }
     };
     // Products of tile j (scores in log2 units are bsc times them, plus bb):
@@ -443,15 +437,6 @@ __device__ __forceinline__ void verify_segment(const VerifyArgs &a, const Segmen
         } else {
             wait_vmcnt<0>();
         }
-    }
-    __syncthreads();
-    // BF16 rows -> fp16 q' in place: 16 neighbouring threads hold a row
-#pragma unroll
-    for (int r = 0; r < RT; ++r) {
-        uint4 *qp = reinterpret_cast<uint4 *>(s_q) + kThreads * r + tid;
-        int eq;
-        *qp = rows_to_f16(*qp, eq);
-        if ((tid & 15) == 0) s_eq[16 * r + (tid >> 4)] = eq;
     }
     __syncthreads();
     for (int u = 0; u < n_mine; ++u) {

@@ -143,3 +143,18 @@ def random_kv(T: int, Hkv: int, seed: int, outlier_cols: int = 2, mult: float = 
 def random_bf16(shape, seed: int):
     g = torch.Generator().manual_seed(seed)
     return torch.randn(*shape, generator=g).to(torch.bfloat16)
+
+
+def wide_range_case(T, Hkv, shape, exp, seed):
+    """K, V and queries whose scores spread over several units although kv
+    head 0's queries are 2^exp larger on channel 5, where its K is 0, and kv
+    head 1's K is 2^exp larger on channel 5, where the queries are 0: channel 5
+    contributes nothing, and the others must keep their precision."""
+    k, v = random_kv(T, Hkv, seed=seed, outlier_cols=0)
+    q = random_bf16(shape, seed=seed + 1) * 4
+    half = shape[-2] // 2  # heads of kv head 0
+    k[:, 0, 5] = 0
+    q[..., :half, 5] *= 2.0 ** exp
+    k[:, 1, 5] *= 2.0 ** exp
+    q[..., half:, 5] = 0
+    return k, v, q

@@ -15,7 +15,7 @@ import oracle
 from paper_2607_01831_amd import inputs, lynx
 from tests._util import LSE_ATOL, LSE_RTOL, assert_close
 from tests.gpu_cases import (bits, build_cache, gpu_anchor_decode, gpu_verify, note, random_bf16,
-                             random_kv)
+                             random_kv, wide_range_case)
 
 pytestmark = pytest.mark.gpu
 
@@ -235,6 +235,17 @@ def test_verify_tiny_queries_and_keys():
     out = gpu_verify(c, q)
     ref, _ = oracle_verify(c, q)
     assert_close(out, ref, what="verify, tiny queries and keys")
+
+
+@pytest.mark.parametrize("exp", [10, 22, 30])
+@pytest.mark.parametrize("nq", [3, 8])
+def test_verify_wide_range_queries_and_keys(nq, exp):
+    T, Hkv, G = 1500, 2, 4
+    k, v, q = wide_range_case(T, Hkv, (1, nq, Hkv * G, 128), exp, seed=970)
+    c = build_cache([k], [v], Hkv)
+    out = gpu_verify(c, q)
+    ref, _ = oracle_verify(c, q)
+    assert_close(out, ref, what=f"verify, channel 5 2^{exp} larger")
 
 
 @pytest.mark.slow

@@ -12,7 +12,7 @@ import torch
 import oracle
 from paper_2607_01831_amd import inputs, lynx
 from tests._util import LSE_ATOL, LSE_RTOL, assert_close
-from tests.gpu_cases import bits, build_cache, gpu_anchor_decode, note, random_bf16, random_kv
+from tests.gpu_cases import bits, build_cache, gpu_anchor_decode, note, random_bf16, random_kv, wide_range_case
 
 pytestmark = pytest.mark.gpu
 
@@ -225,3 +225,13 @@ def test_split_decode_tiny_queries_and_keys(A):
     q = (random_bf16((1, Hkv * G, 128), seed=4901).float() * 1e-24).to(torch.bfloat16)
     out, lse = decode(A, lens, L, table, planes, meta, q)
     check(A, lens, OL, table, op, om, q, out, lse, what=f"A={A} tiny queries and keys")
+
+
+@pytest.mark.parametrize("A", [2, 4, 6])
+@pytest.mark.parametrize("exp", [10, 22, 30])
+def test_split_decode_wide_range_queries_and_keys(A, exp):
+    T, Hkv, G = 1500, 2, 4
+    k, v, q = wide_range_case(T, Hkv, (1, Hkv * G, 128), exp, seed=4950)
+    lens, L, OL, table, planes, meta, op, om = encode(A, [k], [v], Hkv)
+    out, lse = decode(A, lens, L, table, planes, meta, q)
+    check(A, lens, OL, table, op, om, q, out, lse, what=f"A={A}, channel 5 2^{exp} larger")
