@@ -364,8 +364,8 @@ __global__ __launch_bounds__(32 * ROWS) void attn_combine_rows_kernel(AttnArgs a
         const float t0 = d4 < n_tail ? s_t[r][d4] : -INFINITY;
         const float t1 = d4 + 32 < n_tail ? s_t[r][d4 + 32] : -INFINITY;
         const float Mt = fmaxf(M, row_max<32>(fmaxf(t0, t1)));
-        const float p0 = d4 < n_tail ? exp2f(t0 - Mt) : 0.0f;
-        const float p1 = d4 + 32 < n_tail ? exp2f(t1 - Mt) : 0.0f;
+        const float p0 = t0 == -INFINITY ? 0.0f : exp2f(t0 - Mt);
+        const float p1 = t1 == -INFINITY ? 0.0f : exp2f(t1 - Mt);
         s_t[r][d4] = p0;
         s_t[r][d4 + 32] = p1;
         const float sc = M == -INFINITY ? 0.0f : exp2f(M - Mt);
@@ -380,7 +380,8 @@ __global__ __launch_bounds__(32 * ROWS) void attn_combine_rows_kernel(AttnArgs a
 #pragma unroll 4
         for (int j = 0; j < n_tail; ++j) {
             const float p = s_t[r][j];
-            const uint2 w = v2[j * (kHeadDim / 4)];
+            // a token of weight 0 may hold an infinity
+            const uint2 w = p != 0.0f ? v2[j * (kHeadDim / 4)] : make_uint2(0u, 0u);
             acc.x = fmaf(p, bf16_lo(w.x), acc.x);
             acc.y = fmaf(p, bf16_hi(w.x), acc.y);
             acc.z = fmaf(p, bf16_lo(w.y), acc.z);

@@ -524,6 +524,35 @@ def gpu_anchor_decode_tail(c, q, kt, vt):
     return out.float().cpu().numpy(), lse.cpu().numpy()
 
 
+@pytest.mark.parametrize("lens", [[300], [0, 300, 5000]])
+@pytest.mark.parametrize("n_tail", [3, 40])
+def test_anchor_decode_tail_weightless_infinities(lens, n_tail):
+    """A tail token whose score is -inf, or so low that its weight is 0, counts
+    nothing, whatever its value: the result is that of the other tokens.  With
+    no other token the sequence is an empty one."""
+    Hkv, G = 2, 3
+    B = len(lens)
+    kv = [random_kv(T, Hkv, seed=1190 + T) for T in lens]
+    c = build_cache([a for a, _ in kv], [b for _, b in kv], Hkv, bt=16, seed=3, merge=False, with_oracle=False)
+    q = random_bf16((B, Hkv * G, 128), seed=1191)
+    q[:, :, 0] = 1.0
+    kt, vt = random_bf16((B, n_tail, Hkv, 128), seed=1192), random_bf16((B, n_tail, Hkv, 128), seed=1193)
+    ref, ref_lse = gpu_anchor_decode_tail(c, q, kt[:, 1:].contiguous(), vt[:, 1:].contiguous())
+    for low in (float("-inf"), -1e5):
+        kt[:, 0, :, 0] = low
+        vt[:, 0, :, ::2] = float("inf")
+        out, lse = gpu_anchor_decode_tail(c, q, kt, vt)
+        assert np.isfinite(out).all()
+        assert_close(out, ref, what=f"tail token of score {low}")
+        np.testing.assert_allclose(lse, ref_lse, rtol=LSE_RTOL, atol=LSE_ATOL)
+    kt[..., 0] = float("-inf")
+    out, lse = gpu_anchor_decode_tail(c, q, kt, vt)
+    ref, ref_lse = gpu_anchor_decode(c, q)
+    assert_close(out, ref, what="tail of scores -inf")
+    assert np.array_equal(np.isneginf(lse), np.isneginf(ref_lse))
+    assert (out[[i for i, T in enumerate(lens) if T == 0]] == 0).all()
+
+
 @pytest.mark.parametrize("n_tail,lens,bt", [(1, [300, 0], None), (8, [1500, 37, 4000], None),
                                             (64, [129, 700], 16), (5, [900, 0, 61], 8)])
 def test_anchor_decode_tail(n_tail, lens, bt):
