@@ -175,9 +175,11 @@ int lynx_attn_anchor_decode(const lynx_layout *L, int32_t B, int32_t Hq, int32_t
  * counters live in a static array of LYNX_NOALLOC_SCRATCH_BYTES that the
  * library holds on every GPU it runs on until the process ends.  The call
  * allocates nothing (no hipMalloc, no allocating library routine).
- *   LYNX_EWORKSPACE  the call needs more than LYNX_NOALLOC_SCRATCH_BYTES
- *                    (lynx_attn_workspace_bytes(L, B, Hq, 1, max_seq_len)
- *                    bounds what it needs), checked before anything runs
+ *   LYNX_EWORKSPACE  the call is past its limit for
+ *                    LYNX_NOALLOC_SCRATCH_BYTES, checked before anything
+ *                    runs; none is refused for which
+ *                    lynx_attn_workspace_bytes(L, B, Hq, 1, max_seq_len) is
+ *                    at most LYNX_NOALLOC_SCRATCH_BYTES
  *   LYNX_EHIP        the array's device address could not be obtained
  * Every call on a GPU shares that GPU's array: calls that overlap on one GPU
  * (other streams, other threads) race and give wrong results.

@@ -180,7 +180,9 @@ size_t lynx_attn_workspace_bytes(const lynx_layout *L, int32_t B, int32_t Hq,
     if (B < 0 || Hq < 1 || Hq % g.Hkv != 0 || num_queries < 1 || num_queries > 64 ||
         max_seq_len < 0)
         return 0;
-    return lynx::attention_workspace_bound(g, B, Hq, num_queries, max_seq_len);
+    const size_t bound = lynx::attention_workspace_bound(g, B, Hq, num_queries, max_seq_len);
+    const size_t limit = num_queries == 1 ? lynx::decode_limit_bytes(g, B, Hq, max_seq_len) : 0;
+    return bound > limit ? bound : limit;
 }
 
 int lynx_attn_anchor_decode(const lynx_layout *L, int32_t B, int32_t Hq, int32_t max_seq_len,
@@ -277,7 +279,7 @@ int lynx_attn_anchor_decode_noalloc(const lynx_layout *L, int32_t B, int32_t Hq,
     if (B == 0) return LYNX_OK;
     if (lse && !aligned16(lse)) return LYNX_EINVAL;
     const lynx::AttnPlan p = lynx::plan_attention(lynx::KvMode::kAnchor, g, B, Hq, 1, max_seq_len, kScratchBytes);
-    if (lynx::decode_over_scratch(g, B, Hq, max_seq_len, kScratchBytes) || p.workspace_bytes() > kScratchBytes)
+    if (lynx::decode_limit_bytes(g, B, Hq, max_seq_len) > kScratchBytes || p.workspace_bytes() > kScratchBytes)
         return LYNX_EWORKSPACE;
     void *ws = scratch_on_current_device();
     if (!ws) return LYNX_EHIP;

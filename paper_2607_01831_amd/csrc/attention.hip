@@ -464,12 +464,14 @@ size_t attention_workspace_bound(const Geometry &g, int B, int Hq, int nq, int m
     return kCounterBytes + ((by_slots < by_units ? by_slots : by_units) + rows * B) * kPartialBytes;
 }
 
-// The limit is the one that callers of the no-allocation decode know: a partial
-// per split of every sequence, splits of 512 tokens, longer (to 2048) while
-// 1024 workgroups remain, and to 8192 where a contiguous batch of at most 8
-// heads per kv head then fits two workgroups per CU.  The work list needs less,
-// and plan_attention makes any call within the limit fit.
-bool decode_over_scratch(const Geometry &g, int B, int Hq, int max_seq_len, size_t scratch) {
+// A partial per split of every sequence, splits of 512 tokens, longer (to 2048)
+// while 1024 workgroups remain, and to 8192 where a contiguous batch of at most
+// 8 heads per kv head then fits two workgroups per CU: the need of a plan of
+// fixed splits, by which the no-allocation decode has taken and refused calls.
+// The work list needs less (plan_attention makes any call within the limit fit
+// the scratch); the limit stays, so that no call changes sides, and is reported,
+// so that a caller who asks first is told the same.
+size_t decode_limit_bytes(const Geometry &g, int B, int Hq, int max_seq_len) {
     const int G = Hq / g.Hkv;
     const long long heads = (long long)g.Hkv * B;
     auto splits = [&](long long tokens) { return max_seq_len > 0 ? (max_seq_len + tokens - 1) / tokens : 1ll; };
@@ -482,7 +484,7 @@ bool decode_over_scratch(const Geometry &g, int B, int Hq, int max_seq_len, size
                 tokens = st;
                 break;
             }
-    return kCounterBytes + (size_t)(heads * G * splits(tokens)) * kPartialBytes > scratch;
+    return kCounterBytes + (size_t)(heads * G * splits(tokens)) * kPartialBytes;
 }
 
 hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan, int B, int Hq,

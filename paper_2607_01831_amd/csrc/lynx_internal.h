@@ -208,9 +208,9 @@ AttnPlan plan_attention(KvMode mode, const Geometry &g, int B, int Hq, int nq, i
 // Workspace bytes that suffice for every kind of call of at most B sequences,
 // nq queries each, and max_seq_len tokens.
 size_t attention_workspace_bound(const Geometry &g, int B, int Hq, int nq, int max_seq_len);
-// Whether lynx_attn_anchor_decode_noalloc refuses a call as larger than its
-// scratch of `scratch` bytes.
-bool decode_over_scratch(const Geometry &g, int B, int Hq, int max_seq_len, size_t scratch);
+// Bytes that lynx_attn_workspace_bytes reports at least for a decode, and that
+// lynx_attn_anchor_decode_noalloc compares with its scratch.
+size_t decode_limit_bytes(const Geometry &g, int B, int Hq, int max_seq_len);
 
 // k_new / v_new: the BF16 tail, or nullptr.  Verification (kCodes): k drafts
 // per sequence, causal among the drafts.  Decode (kAnchor, nq == 1):

@@ -7,6 +7,7 @@ import subprocess
 from pathlib import Path
 
 import pytest
+import torch
 
 ROOT = Path(__file__).resolve().parent.parent
 HEADER = ROOT / "include" / "lynx.h"
@@ -68,6 +69,36 @@ def test_workspace_bytes_host_only(lib):
     assert lynx.lynx_attn_workspace_bytes(L, 2, 30, 1, 64) == 0       # Hq % Hkv != 0
     assert lynx.lynx_attn_workspace_bytes(L, 2, 32, 65, 64) == 0      # k > 64
     assert lynx.lynx_attn_workspace_bytes(_layout(head_dim=64), 2, 32, 1, 64) == 0
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="an accepted call would launch on pointers of no memory")
+def test_noalloc_takes_what_workspace_bytes_says_fits(lib):
+    """A caller who asks lynx_attn_workspace_bytes whether a decode fits
+    LYNX_NOALLOC_SCRATCH_BYTES, and only then leaves the workspace out, is never
+    refused for its size (without a GPU an accepted call ends at its launch);
+    16 paged sequences of 64K with 64 query heads, and one of 128K with 128,
+    are past the limit."""
+    from paper_2607_01831_amd import lynx
+    meta = lynx.lynx_meta(16, 32, 48, 64)
+
+    def both(B, Hq, T, bt):
+        L = _layout(max_tokens=T, block_tokens=bt or T, max_blocks_per_seq=-(-T // bt) if bt else 1,
+                    num_blocks=1 << 20)
+        rc = lib.lynx_attn_anchor_decode_noalloc(ctypes.byref(L.c()), B, Hq, T, 16, 16, 16, 16, ctypes.byref(meta),
+                                                 16, 16, None, None)
+        return lynx.lynx_attn_workspace_bytes(L, B, Hq, 1, T), rc
+
+    refused = 0
+    for B in (1, 2, 4, 16, 64, 300):
+        for Hq in (8, 32, 64, 128):
+            for T in (1, 513, 4096, 20000, 65536, 131072):
+                for bt in (0, 16):
+                    n, rc = both(B, Hq, T, bt)
+                    assert (rc == lynx.LYNX_EWORKSPACE) == (n > lynx.NOALLOC_SCRATCH_BYTES), (B, Hq, T, bt, n, rc)
+                    refused += rc == lynx.LYNX_EWORKSPACE
+    assert 0 < refused
+    assert both(16, 64, 65536, 16)[1] == lynx.LYNX_EWORKSPACE
+    assert both(1, 128, 131072, 0)[1] == lynx.LYNX_EWORKSPACE
 
 
 def test_validation_rejects_before_launch(lib):
