@@ -626,7 +626,7 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_batch_kernel(Decode
     }
 }
 
-// A single sequence: one segment per worker, no walk.
+// A single sequence of more units than workers: one segment each, no walk.
 template <int GP, int LAYOUT, int UNIT>
 __global__ __launch_bounds__(kThreads, 2) void anchor_decode_long_kernel(DecodeArgs a) {
     const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
@@ -638,34 +638,26 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_long_kernel(DecodeA
     attend_segment<GP, LAYOUT, UNIT, false>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
 }
 
-// A single sequence of no more units than workers: unit p is worker p's.  The
+// A unit per workgroup, for sequence blockIdx.z: nothing to balance, and the
 // short call is all latency (32K layer: 14.0 us, 14.3 through the long kernel,
 // 14.7 through the batch's, whose start waits for its arguments in turn).
 template <int GP, int LAYOUT, int UNIT>
 __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a) {
-    const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int unit = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
     const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
-    const WorkList<UNIT, false> list(a.seq_lens, 1, a.max_seq_len, a.workers);
-    if (worker >= list.total) return;
     Segment<UNIT> seg;
-    seg.b = 0;
-    seg.T = list.only;
-    seg.g0 = worker * UNIT;
-    seg.n_groups = max(0, min(UNIT, (seg.T + kKGroup - 1) / kKGroup - seg.g0));
-    seg.number = worker;
-    seg.number0 = 0;
-    seg.live = list.total;
+    if (!seg.set_unit(a.seq_lens, a.max_seq_len, a.direct, blockIdx.z, unit)) return;
     attend_segment<GP, LAYOUT, UNIT, true>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
 }
 
 template <int GP, int LAYOUT>
 void launch_gp(const DecodeArgs &args, dim3 grid, hipStream_t stream) {
-    if (args.B > 1)
-        hipLaunchKernelGGL((anchor_decode_batch_kernel<GP, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
-    else if ((long long)args.workers * kWorkUnit * kKGroup < args.max_seq_len)
-        hipLaunchKernelGGL((anchor_decode_long_kernel<GP, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
-    else
+    if (args.direct)
         hipLaunchKernelGGL((anchor_decode_kernel<GP, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+    else if (args.B > 1)
+        hipLaunchKernelGGL((anchor_decode_batch_kernel<GP, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+    else
+        hipLaunchKernelGGL((anchor_decode_long_kernel<GP, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
 }
 
 template <int GP>
@@ -684,7 +676,8 @@ hipError_t launch_anchor_decode_mfma(const DecodeArgs &args, int chunks, hipStre
     // kv head fastest for paged layouts (the kernel reads the grid the same way)
     if (args.workers < 1 || args.workers > 65535) return hipErrorInvalidValue;
     const unsigned hc = (unsigned)(args.geo.Hkv * chunks);
-    const dim3 grid = args.geo.max_blocks == 1 ? dim3(args.workers, hc) : dim3(hc, args.workers);
+    const unsigned n = args.direct ? args.direct : args.workers, nz = args.direct ? args.B : 1;
+    const dim3 grid = args.geo.max_blocks == 1 ? dim3(n, hc, nz) : dim3(hc, n, nz);
     if (args.chunk_heads <= 4)
         launch_layout<4>(args, grid, stream);
     else if (args.chunk_heads <= 8)

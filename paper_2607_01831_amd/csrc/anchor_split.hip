@@ -148,7 +148,8 @@ struct Ring {
 // LAYOUT 0: one block per sequence (contiguous); 1: paged, block_tokens a
 // multiple of 16; 2: any other paging.
 // One segment of a worker's share, for kv head h and a chunk of 16 query rows.
-template <int A, int LAYOUT, int UNIT>
+// ONE: the segment is a single unit, a group per wavefront.
+template <int A, int LAYOUT, int UNIT, bool ONE>
 __device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const Segment<UNIT> &seg, int h, int chunk,
                                                const int tid) {
     static_assert(UNIT == kWaves, "a group per wavefront and unit");
@@ -220,7 +221,7 @@ __device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const S
 
     // this wavefront's tiles: tile j is tile j % 4 of its group j / 4, the
     // split's group w + 4 (j / 4)
-    const int n_mine = n_groups > w ? (n_groups - w + kWaves - 1) / kWaves : 0;
+    const int n_mine = ONE ? (n_groups > w ? 1 : 0) : n_groups > w ? (n_groups - w + kWaves - 1) / kWaves : 0;
     auto tile_t0 = [&](int j) { return (g0 + w + kWaves * (j >> 2)) * kKGroup + kTile * (j & 3); };
     auto tile_valid = [&](int j) { return (j >> 2) < n_mine && tile_t0(j) < T; };
 
@@ -321,7 +322,7 @@ __device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const S
             const int g = g0 + min(w + kWaves * (j >> 2), n_groups - 1);
             const float *src = (lane < 32 ? a.meta.k_scale : a.meta.k_zero) + kmeta + (size_t)g * kHeadDim;
             lds_copy16(src + 4 * (lane & 31), km);
-            if (n_mine > 1) issue_ids((j >> 2) + 1);  // (a wavefront's only group has no next)
+            if (!ONE && n_mine > 1) issue_ids((j >> 2) + 1);  // (a wavefront's only group has no next)
         }
     };
     static_assert(kDepth - 1 < 4, "a group's K metadata may not arrive before the last group's fold");
@@ -556,8 +557,8 @@ __device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const S
     // Fast path: a fixed softmax reference, the maximum of the wavefront's
     // first tile; the next tiles are in flight while one is attended.
     auto copies_at = [](int c) { return 2 * RG::kCopies + ((c & 3) == 0 ? (LAYOUT == 1 ? 3 : 2) : 1); };
-    for (int u = 0; u < n_mine; ++u) {
-        const bool next_group = u + 1 < n_mine;
+    for (int u = 0; u < (ONE ? min(n_mine, 1) : n_mine); ++u) {
+        const bool next_group = !ONE && u + 1 < n_mine;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int j = 4 * u + c;
@@ -759,28 +760,40 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_batch_kernel(
     Segment<UNIT> seg;
     seg.start(list, worker);
     for (;;) {
-        attend_segment<A, LAYOUT, UNIT>(a, seg, fresh_uniform(hc % a.geo.Hkv), fresh_uniform(hc / a.geo.Hkv), fresh_tid());
+        attend_segment<A, LAYOUT, UNIT, false>(a, seg, fresh_uniform(hc % a.geo.Hkv), fresh_uniform(hc / a.geo.Hkv), fresh_tid());
         if (!seg.next(list, worker)) return;
         __syncthreads();  // the segment's LDS is free again
     }
 }
 
-// A single sequence: one segment per worker, no walk.
+// A single sequence of more units than workers: one segment each, no walk.
 template <int A, int LAYOUT, int UNIT>
-__global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_kernel(SplitDecodeArgs a) {
+__global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_long_kernel(SplitDecodeArgs a) {
     const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
     const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
     const WorkList<UNIT, false> list(a.seq_lens, 1, a.max_seq_len, a.workers);
     if (worker >= list.workers) return;
     Segment<UNIT> seg;
     seg.start(list, worker);
-    attend_segment<A, LAYOUT, UNIT>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
+    attend_segment<A, LAYOUT, UNIT, false>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
+}
+
+// A unit per workgroup, for sequence blockIdx.z.
+template <int A, int LAYOUT, int UNIT>
+__global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_kernel(SplitDecodeArgs a) {
+    const int unit = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
+    Segment<UNIT> seg;
+    if (!seg.set_unit(a.seq_lens, a.max_seq_len, a.direct, blockIdx.z, unit)) return;
+    attend_segment<A, LAYOUT, UNIT, true>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
 }
 
 template <int A, int LAYOUT>
 void launch_layout(const SplitDecodeArgs &args, dim3 grid, hipStream_t stream) {
-    if (args.B == 1)
+    if (args.direct)
         hipLaunchKernelGGL((anchor_split_decode_kernel<A, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+    else if (args.B == 1)
+        hipLaunchKernelGGL((anchor_split_decode_long_kernel<A, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
     else
         hipLaunchKernelGGL((anchor_split_decode_batch_kernel<A, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream,
                            args);
@@ -803,7 +816,8 @@ hipError_t launch_anchor_split_decode(const SplitDecodeArgs &args, hipStream_t s
     if (args.workers < 1 || args.workers > 65535) return hipErrorInvalidValue;
     const unsigned hc = (unsigned)(args.geo.Hkv * ((args.rows_total + kRows - 1) / kRows));
     // kv head fastest for paged layouts (the kernel reads the grid the same way)
-    const dim3 grid = paged ? dim3(hc, args.workers) : dim3(args.workers, hc);
+    const unsigned n = args.direct ? args.direct : args.workers, nz = args.direct ? args.B : 1;
+    const dim3 grid = paged ? dim3(hc, n, nz) : dim3(n, hc, nz);
     switch (args.anchor_bits) {
         case 2:
             launch_a<2>(args, grid, stream);

@@ -23,7 +23,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 struct AttnArgs {
     Geometry geo;
     int B, Hq, nq, G, max_seq_len;
-    int rows_total, workers, n_seg, max_live;
+    int rows_total, direct, workers, n_seg, max_live;
     int tail;             // attend the BF16 tail
     int tail_count;       // tokens of the tail every query sees; -1: query i sees i + 1 (drafts)
     int tail_stride;      // tail tokens stored per sequence in k_new / v_new
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(32 * ROWS) void attn_combine_rows_kernel(AttnArgs a
     __shared__ __attribute__((aligned(16))) float s_q[ROWS][kHeadDim + 16];
     __shared__ float s_t[ROWS][kTailMax];  // tail scores (log2 units), then weights
 
-    const int own = WorkList<kWorkUnit, false>::load_own(a.seq_lens, a.B);
+    const int own = a.direct ? a.seq_lens[b] : WorkList<kWorkUnit, false>::load_own(a.seq_lens, a.B);
     // ---- the tail's loads ----
     uint4 kw[kPasses][4];
     if (tail_most > 0) {
@@ -289,12 +289,19 @@ __global__ __launch_bounds__(32 * ROWS) void attn_combine_rows_kernel(AttnArgs a
         *reinterpret_cast<float4 *>(&s_q[r][4 * d4 + 4 * (d4 / 8)]) =
             make_float4(bf16_lo(qw.x), bf16_hi(qw.x), bf16_lo(qw.y), bf16_hi(qw.y));
     }
-    // ---- the row's partials (work_list.h): n of them from seg0 on ----
-    const WorkList<kWorkUnit, false> list(a.seq_lens, a.B, a.max_seq_len, a.workers, own);
-    const int first = a.B == 1 ? 0 : list.first_unit(b);
-    const int w0 = list.owner(first);
-    const int n = list.owner(first + list.units(list.tokens_of(b)) - 1) - w0 + 1;
-    const size_t base = ((size_t)h * a.rows_total + gr) * a.n_seg + (w0 + b);
+    // ---- the row's partials (work_list.h): n of them from segment seg0 on ----
+    int n, seg0;
+    if (a.direct) {
+        n = WorkList<kWorkUnit, false>::units(max(0, min(own, a.max_seq_len)));
+        seg0 = b * a.direct;
+    } else {
+        const WorkList<kWorkUnit, false> list(a.seq_lens, a.B, a.max_seq_len, a.workers, own);
+        const int first = a.B == 1 ? 0 : list.first_unit(b);
+        const int w0 = list.owner(first);
+        n = list.owner(first + list.units(list.tokens_of(b)) - 1) - w0 + 1;
+        seg0 = w0 + b;
+    }
+    const size_t base = ((size_t)h * a.rows_total + gr) * a.n_seg + seg0;
     const float4 *o4 = reinterpret_cast<const float4 *>(a.ws_o) + base * (kHeadDim / 4) + d4;
     float M = -INFINITY, L = 0.0f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -409,7 +416,11 @@ int compute_units() {
 
 namespace {
 
-constexpr int kPerCu = 2;  // workgroups of an attention kernel that a CU holds at once
+// Workgroups of the attention kernels that the device holds at once, two per CU.
+long long resident_workgroups() {
+    const int cus = compute_units();
+    return 2ll * (cus > 0 ? cus : 256);
+}
 
 // 512-token units of a sequence of at most T tokens (work_list.h).
 long long work_units(int T) { return T > 0 ? ((long long)T + kWorkUnit * kKGroup - 1) / (kWorkUnit * kKGroup) : 1; }
@@ -428,21 +439,29 @@ AttnPlan plan_attention(KvMode mode, const Geometry &g, int B, int Hq, int nq, i
     p.rows_total = nq * (Hq / g.Hkv);
     const int tile = mode == KvMode::kCodes && p.rows_total > 16 ? 32 : 16;  // rows per workgroup
     const long long chunks = (p.rows_total + tile - 1) / tile;
-    const int cus = compute_units();
-    const long long slots = (long long)kPerCu * (cus > 0 ? cus : 256);
+    const long long slots = resident_workgroups();
     const long long units = (long long)B * work_units(max_seq_len);
-    long long w = slots / (g.Hkv * chunks);
-    w = w < units ? w : units;
-    // fewer partials where the workspace is given (lynx_attn_anchor_decode_noalloc)
     const size_t row_bytes = (size_t)g.Hkv * p.rows_total * kPartialBytes;
-    if (most < SIZE_MAX) {
+    // A workgroup per unit of the longest sequence where those of all sequences
+    // fit one round: nothing to balance, and the list's start and walk cost 1 us
+    // of a 10 us call (decode, 4 sequences of 4K: 10.7 us, by the list 11.5;
+    // verification of 2 drafts, 2 of 2K: 14.0 and 15.3; 6-bit anchors, 8 of 4K:
+    // 15.2 and 16.4).  Past one round the list balances (one sequence of 33000:
+    // 17.2 us, by direct workgroups 19.9).
+    const bool direct = units * g.Hkv * chunks <= slots &&
+                        (most == SIZE_MAX || kCounterBytes + units * row_bytes <= most);
+    p.direct = direct ? (int)work_units(max_seq_len) : 0;
+    long long w = slots / (g.Hkv * chunks);
+    w = direct || w > units ? units : w;
+    // fewer partials where the workspace is given (lynx_attn_anchor_decode_noalloc)
+    if (!direct && most < SIZE_MAX) {
         const long long fit = (long long)((most - kCounterBytes) / row_bytes) - (B - 1);
         w = w < fit ? w : fit;
     }
     // the shares are found in 32-bit arithmetic (workers x units)
     if (units * w > 0xffffffffll) w = 0xffffffffll / units;
     p.workers = (int)(w > 1 ? w : 1);
-    p.n_seg = p.workers + (B > 0 ? B - 1 : 0);
+    p.n_seg = p.workers + (B > 0 && !direct ? B - 1 : 0);
     p.max_live = (int)(work_units(max_seq_len) < p.workers ? work_units(max_seq_len) : p.workers);
     p.o_bytes = (size_t)g.Hkv * p.rows_total * p.n_seg * kHeadDim * sizeof(float);
     p.ml_bytes = (size_t)g.Hkv * p.rows_total * p.n_seg * sizeof(float2);
@@ -457,8 +476,7 @@ AttnPlan plan_attention(KvMode mode, const Geometry &g, int B, int Hq, int nq, i
 // workspace serves every smaller call too.
 size_t attention_workspace_bound(const Geometry &g, int B, int Hq, int nq, int max_seq_len) {
     const size_t rows = (size_t)nq * (Hq / g.Hkv) * g.Hkv;
-    const int cus = compute_units();
-    const size_t resident = (size_t)kPerCu * (cus > 0 ? cus : 256) * (nq * (Hq / g.Hkv) > 16 ? 32 : 16);
+    const size_t resident = (size_t)resident_workgroups() * (nq * (Hq / g.Hkv) > 16 ? 32 : 16);
     const size_t by_slots = resident > rows ? resident : rows;
     const size_t by_units = rows * B * (size_t)work_units(max_seq_len);
     return kCounterBytes + ((by_slots < by_units ? by_slots : by_units) + rows * B) * kPartialBytes;
@@ -503,6 +521,7 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
     a.G = Hq / g.Hkv;
     a.max_seq_len = max_seq_len;
     a.rows_total = plan.rows_total;
+    a.direct = plan.direct;
     a.workers = plan.workers;
     a.n_seg = plan.n_seg;
     a.max_live = plan.max_live;
@@ -528,6 +547,7 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
         d.Hq = Hq;
         d.G = a.G;
         d.max_seq_len = max_seq_len;
+        d.direct = plan.direct;
         d.workers = plan.workers;
         d.chunk_heads = a.G < 16 ? a.G : 16;
         d.bt_shift = -1;
@@ -567,6 +587,7 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
         d.G = a.G;
         d.max_seq_len = max_seq_len;
         d.anchor_bits = anchor_bits;
+        d.direct = plan.direct;
         d.workers = plan.workers;
         d.bt_shift = -1;
         for (int sh = 0; sh < 31; ++sh)
@@ -601,6 +622,7 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
         v.nq = nq;
         v.max_seq_len = max_seq_len;
         v.rows_total = plan.rows_total;
+        v.direct = plan.direct;
         v.workers = plan.workers;
         v.n_seg = plan.n_seg;
         v.bt_shift = -1;

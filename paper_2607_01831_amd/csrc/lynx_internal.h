@@ -111,8 +111,9 @@ constexpr int kWorkUnit = 4;
 
 struct AttnPlan {
     int rows_total;   // nq * G query rows per (sequence, kv head)
+    int direct;       // units of a sequence at most where each has a workgroup of its own, else 0
     int workers;      // workgroups per (kv head, row chunk)
-    int n_seg;        // partials per query row: workers + B - 1
+    int n_seg;        // partials per query row: workers + B - 1, or B direct
     int max_live;     // partials of one sequence at most
     int row_chunks;   // ceil(rows_total / 16): arrival counters per (sequence, kv head)
     bool counters_fit;  // B * Hkv * row_chunks <= kCounters
@@ -128,7 +129,7 @@ struct AttnPlan {
 struct DecodeArgs {
     Geometry geo;
     int B, Hq, G, max_seq_len;
-    int workers, chunk_heads;
+    int direct, workers, chunk_heads;
     int bt_shift;   // log2(block_tokens) when it is a power of two, else -1
     const int32_t *seq_lens;
     const int32_t *block_table;
@@ -157,6 +158,7 @@ struct VerifyArgs {
     Geometry geo;
     int B, Hq, G, nq, max_seq_len;
     int rows_total;    // nq * G query rows per (sequence, kv head)
+    int direct;        // as in AttnPlan
     int workers;       // workgroups per (kv head, row chunk)
     int n_seg;         // partials per row
     int bt_shift;      // log2(block_tokens) when it is a power of two, else -1
@@ -178,6 +180,7 @@ struct SplitDecodeArgs {
     Geometry geo;
     int B, Hq, G, max_seq_len;
     int anchor_bits;      // A: 2, 4 or 6
+    int direct;           // as in AttnPlan
     int workers;          // workgroups per (kv head, row chunk)
     int bt_shift;         // log2(block_tokens) when it is a power of two, else -1
     int rows_total;       // G query rows per (sequence, kv head)

@@ -76,7 +76,8 @@ __device__ __forceinline__ uint32_t k_slot(int t, int q) {
 // 2: any other paging.  RT: 16-row query tiles per workgroup (1 or 2), all
 // served by every wavefront.  UNIT: 128-token groups per unit of the work list.
 // One segment of a worker's share, for kv head h and a chunk of 16 RT rows.
-template <int RT, int LAYOUT, int UNIT>
+// ONE: the segment is a single unit, a group per wavefront.
+template <int RT, int LAYOUT, int UNIT, bool ONE>
 __device__ __forceinline__ void verify_segment(const VerifyArgs &a, const Segment<UNIT> &seg, int h, int chunk,
                                                const int tid) {
     constexpr int kRows = RT * 16;
@@ -137,7 +138,7 @@ __device__ __forceinline__ void verify_segment(const VerifyArgs &a, const Segmen
 
     // This wavefront's tiles: tile j is tile j % 4 of its group j / 4, the
     // split's group gq + NQ (j / 4).
-    const int n_mine = n_groups > gq ? (n_groups - gq + NQ - 1) / NQ : 0;  // its groups
+    const int n_mine = ONE ? (n_groups > gq ? 1 : 0) : n_groups > gq ? (n_groups - gq + NQ - 1) / NQ : 0;  // its groups
     auto group_of = [&](int j) { return gq + NQ * (j >> 2); };
     auto tile_t0 = [&](int j) { return (g0 + group_of(j)) * kKGroup + kTile * (j & 3); };
     auto tile_valid = [&](int j) { return (j >> 2) < n_mine && tile_t0(j) < T; };
@@ -252,7 +253,7 @@ __device__ __forceinline__ void verify_segment(const VerifyArgs &a, const Segmen
             const int g = g0 + min(group_of(j), n_groups - 1);
             const float *src = (lane < 32 ? a.meta.k_scale : a.meta.k_zero) + kmeta + (size_t)g * kHeadDim;
             lds_copy16(src + 4 * (lane & 31), km);
-            if (n_mine > 1) issue_ids((j >> 2) + 1);  // (a wavefront's only group has no next)
+            if (!ONE && n_mine > 1) issue_ids((j >> 2) + 1);  // (a wavefront's only group has no next)
         }
     };
 
@@ -439,12 +440,12 @@ __device__ __forceinline__ void verify_segment(const VerifyArgs &a, const Segmen
         }
     }
     __syncthreads();
-    for (int u = 0; u < n_mine; ++u) {
+    for (int u = 0; u < (ONE ? min(n_mine, 1) : n_mine); ++u) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int j = 4 * u + c;
             // the next tile: inside this group, or the next group's first
-            const bool more = c < 3 || u + 1 < n_mine;
+            const bool more = c < 3 || (!ONE && u + 1 < n_mine);
             if (more) issue_tile(j + 1);
             // tile j is in once only tile j + 1's copies may remain in flight
             if (!more) {
@@ -618,28 +619,40 @@ __global__ __launch_bounds__(kThreads, 2) void verify_batch_kernel(VerifyArgs a)
     Segment<UNIT> seg;
     seg.start(list, worker);
     for (;;) {
-        verify_segment<RT, LAYOUT, UNIT>(a, seg, fresh_uniform(hc % a.geo.Hkv), fresh_uniform(hc / a.geo.Hkv), fresh_tid());
+        verify_segment<RT, LAYOUT, UNIT, false>(a, seg, fresh_uniform(hc % a.geo.Hkv), fresh_uniform(hc / a.geo.Hkv), fresh_tid());
         if (!seg.next(list, worker)) return;
         __syncthreads();  // the segment's LDS is free again
     }
 }
 
-// A single sequence: one segment per worker, no walk.
+// A single sequence of more units than workers: one segment each, no walk.
 template <int RT, int LAYOUT, int UNIT>
-__global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
+__global__ __launch_bounds__(kThreads, 2) void verify_long_kernel(VerifyArgs a) {
     const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
     const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
     const WorkList<UNIT, false> list(a.seq_lens, 1, a.max_seq_len, a.workers);
     if (worker >= list.workers) return;
     Segment<UNIT> seg;
     seg.start(list, worker);
-    verify_segment<RT, LAYOUT, UNIT>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
+    verify_segment<RT, LAYOUT, UNIT, false>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
+}
+
+// A unit per workgroup, for sequence blockIdx.z.
+template <int RT, int LAYOUT, int UNIT>
+__global__ __launch_bounds__(kThreads, 2) void verify_kernel(VerifyArgs a) {
+    const int unit = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
+    Segment<UNIT> seg;
+    if (!seg.set_unit(a.seq_lens, a.max_seq_len, a.direct, blockIdx.z, unit)) return;
+    verify_segment<RT, LAYOUT, UNIT, true>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
 }
 
 template <int RT, int LAYOUT>
 void launch_rt(const VerifyArgs &args, dim3 grid, hipStream_t stream) {
-    if (args.B == 1)
+    if (args.direct)
         hipLaunchKernelGGL((verify_kernel<RT, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+    else if (args.B == 1)
+        hipLaunchKernelGGL((verify_long_kernel<RT, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
     else
         hipLaunchKernelGGL((verify_batch_kernel<RT, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
 }
@@ -661,7 +674,8 @@ hipError_t launch_verify_mfma(const VerifyArgs &args, hipStream_t stream) {
     const int rt = args.rows_total <= 16 ? 1 : 2;
     const unsigned hc = (unsigned)(args.geo.Hkv * ((args.rows_total + 16 * rt - 1) / (16 * rt)));
     // kv head fastest for paged layouts (the kernel reads the grid the same way)
-    const dim3 grid = args.geo.max_blocks == 1 ? dim3(args.workers, hc) : dim3(hc, args.workers);
+    const unsigned n = args.direct ? args.direct : args.workers, nz = args.direct ? args.B : 1;
+    const dim3 grid = args.geo.max_blocks == 1 ? dim3(n, hc, nz) : dim3(hc, n, nz);
     if (rt == 1)
         launch_layout<1>(args, grid, stream);
     else

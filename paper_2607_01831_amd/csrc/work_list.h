@@ -169,6 +169,19 @@ struct Segment {
         wl.find(pos, b, first);
         set(wl, p);
     }
+    // Without a list, where every unit has a worker (AttnPlan::direct): unit
+    // `unit` of sequence `seq`, whose partials stand from direct seq on; false
+    // past the sequence's end.
+    __device__ __forceinline__ bool set_unit(const int32_t *lens, int max_len, int direct, int seq, int unit) {
+        b = seq;
+        T = max(0, min(lens[seq], max_len));
+        live = WorkList<UNIT, false>::units(T);
+        g0 = unit * UNIT;
+        n_groups = max(0, min(UNIT, (T + kKGroup - 1) / kKGroup - g0));
+        number0 = seq * direct;
+        number = number0 + unit;
+        return unit < live;
+    }
     // The next one; false past the share's end.
     template <bool WALK>
     __device__ __forceinline__ bool next(const WorkList<UNIT, WALK> &wl, int p) {

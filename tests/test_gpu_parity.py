@@ -374,6 +374,9 @@ def test_anchor_decode_ragged_batch_stale_workspace():
     ([700 + 37 * i % 900 for i in range(70)], 1, 16),   # more sequences than a wavefront's lanes
     ([1 + 13 * i % 600 for i in range(130)], 8, 24),    # more (sequence, kv head) pairs than counters; blocks of 24
     ([2048] * 40, 8, None),                             # whole units only, several a worker
+    ([16384, 16000], 8, None),                          # a workgroup per unit, all resident workgroups used
+    ([16385, 3, 0], 8, 16),                             # one unit too many for that; an empty sequence
+    ([513, 0, 512, 1, 1024], 8, 16),                    # a workgroup per unit, sequences ending before the last
 ])
 def test_attention_work_list(lens, Hkv, bt):
     """The attention kernels' work list: equal shares of a ragged batch's units,
