@@ -13,6 +13,7 @@
 #include <float.h>
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 
 namespace lynx {
@@ -51,8 +52,9 @@ __device__ __forceinline__ void unpack8_bf16(const uint4 &u, float *x) {
 
 constexpr int kCombineThreads = 256;
 
-// One workgroup per (row, kv head, sequence): merge the sequence's partials
-// ("splits") and the BF16 tail tokens, normalise, round to BF16, write lse.
+// One workgroup per (row, kv head, sequence), for many partials and few rows:
+// merge the sequence's partials ("splits") and the BF16 tail tokens,
+// normalise, round to BF16, write lse.
 // Thread (split group sg, float4 column d4) folds every 8th split into a
 // running (max, sum, output), loading kBatch splits' partial outputs and
 // (max, sum) pairs together (8 when 64 splits or fewer, so no load is a
@@ -97,11 +99,14 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
                 a.v_new + (((size_t)b * a.tail_stride + j) * Hkv + h) * kHeadDim + 4 * d4);
         }
     }
-    // The sequence's partials stand from the row's first on (work_list.h).  The
-    // first batch is loaded, up to the most there can be, before the
-    // sequence's length is in.
-    const size_t base = ((size_t)h * a.rows_total + gr) * a.n_seg;
-    int n = a.max_live;
+    // The sequence's partials stand from the row's number seg0 on (work_list.h).
+    // Where that is known without the list, the first batch is loaded, up to
+    // the most there can be, before the sequence's length is in.
+    using List = WorkList<kWorkUnit, false>;
+    int n = a.max_live, seg0 = b * a.direct;
+    const bool listed = !a.direct && a.B > 1;
+    if (listed) List(a.seq_lens, a.B, a.max_seq_len, a.workers).partials(b, seg0, n);
+    const size_t base = ((size_t)h * a.rows_total + gr) * a.n_seg + seg0;
     // a batch of partials: splits s0, s0 + 8, ... (clamped to the last split)
     float4 v[kBatch];
     float2 ml[kBatch];
@@ -120,7 +125,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
         for (int u = 0; u < kBatch; ++u) live[u] = s0 + kGroups * u < n;
     };
     load_batch(sg);
-    n = WorkList<kWorkUnit, false>(a.seq_lens, 1, a.max_seq_len, a.workers).workers;
+    if (!listed) n = min(a.max_live, List::units(max(0, min(a.seq_lens[b], a.max_seq_len))));
     set_live(sg);
     if (n_tail > 0) {
         // tail scores, 16 tokens per pass: thread (token tid / 16, dims
@@ -218,7 +223,8 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
             const float f = s_m[g][d4] == -INFINITY ? 0.0f : exp2f(s_m[g][d4] - M);
-            const float4 o = s_acc[g][d4];
+            // (of weight 0: it may hold a weightless tail token's infinity)
+            const float4 o = f != 0.0f ? s_acc[g][d4] : make_float4(0.f, 0.f, 0.f, 0.f);
             O.x = fmaf(o.x, f, O.x);
             O.y = fmaf(o.y, f, O.y);
             O.z = fmaf(o.z, f, O.z);
@@ -230,7 +236,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
     }
 }
 
-// The same for batches, and wherever a sequence has few partials: one workgroup
+// The same for few partials or many rows: one workgroup
 // per (ROWS rows, kv head, sequence), a row per 32 threads.  Thread (row r,
 // float4 column d4) folds all of the row's partials, 8 loaded at a time, so
 // nothing meets in LDS but the tail, whose keys and values the rows share: a
@@ -296,10 +302,7 @@ __global__ __launch_bounds__(32 * ROWS) void attn_combine_rows_kernel(AttnArgs a
         seg0 = b * a.direct;
     } else {
         const WorkList<kWorkUnit, false> list(a.seq_lens, a.B, a.max_seq_len, a.workers, own);
-        const int first = a.B == 1 ? 0 : list.first_unit(b);
-        const int w0 = list.owner(first);
-        n = list.owner(first + list.units(list.tokens_of(b)) - 1) - w0 + 1;
-        seg0 = w0 + b;
+        list.partials(b, seg0, n);
     }
     const size_t base = ((size_t)h * a.rows_total + gr) * a.n_seg + seg0;
     const float4 *o4 = reinterpret_cast<const float4 *>(a.ws_o) + base * (kHeadDim / 4) + d4;
@@ -642,9 +645,17 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
     } else {
         return hipErrorInvalidValue;  // anchor attention with several queries: no entry point asks for it
     }
-    // A single sequence of many partials is merged a row per workgroup, 8 or 16
-    // threads deep in its partials; else the rows share workgroups.
-    if (B > 1 || plan.max_live <= 16) {
+    // More than 8 partials a sequence (one wait for memory of a thread that merges
+    // them all): a row per workgroup, 8 threads deep in them, while those
+    // workgroups are resident at once; else the rows share workgroups.  2
+    // sequences of 8K, 2 drafts (512 rows, 16 partials): 16.8 us, shared 18.2;
+    // 8 of 1.5K-5K, 8 drafts (2048 rows): 33.9, shared 26.4.  A single sequence
+    // of more than 16 partials also past that (32K, 20 drafts, 640 rows: 46.2,
+    // shared 47.7).
+    const int each = plan.direct ? plan.direct : std::min(plan.max_live, plan.workers / B + 1);
+    const long long rows_all = (long long)plan.rows_total * g.Hkv * B;
+    const bool deep = each > 8 && (rows_all <= resident_workgroups() || (B == 1 && each > 16));
+    if (!deep) {
         const int rows = plan.rows_total <= 4 ? 4 : 8;
         const dim3 grid((plan.rows_total + rows - 1) / rows, g.Hkv, B);
         if (rows == 4)

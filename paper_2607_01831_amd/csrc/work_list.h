@@ -123,6 +123,13 @@ struct WorkList {
             first = __builtin_amdgcn_readlane(last, 63);
         }
     }
+    // Sequence b's partials: n from number seg0 on.
+    __device__ __forceinline__ void partials(int b, int &seg0, int &n) const {
+        const int first = B == 1 ? 0 : first_unit(b);
+        seg0 = owner(first);
+        n = owner(first + units(tokens_of(b)) - 1) - seg0 + 1;
+        seg0 += b;
+    }
     // The number of sequence b's first unit.
     __device__ __forceinline__ int first_unit(int b) const {
         if (B <= 64) return __builtin_amdgcn_readlane(upto, b) - units(__builtin_amdgcn_readlane(own_T, b));
