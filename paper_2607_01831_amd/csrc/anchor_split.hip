@@ -756,9 +756,8 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_batch_kernel(
     const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
     const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
     const WorkList<UNIT, true> list(a.seq_lens, a.B, a.max_seq_len, a.workers);
-    if (worker >= list.workers) return;
     Segment<UNIT> seg;
-    seg.start(list, worker);
+    if (!seg.start(list, worker)) return;
     for (;;) {
         attend_segment<A, LAYOUT, UNIT, false>(a, seg, fresh_uniform(hc % a.geo.Hkv), fresh_uniform(hc / a.geo.Hkv), fresh_tid());
         if (!seg.next(list, worker)) return;
@@ -772,9 +771,8 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_long_kernel(S
     const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
     const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
     const WorkList<UNIT, false> list(a.seq_lens, 1, a.max_seq_len, a.workers);
-    if (worker >= list.workers) return;
     Segment<UNIT> seg;
-    seg.start(list, worker);
+    if (!seg.start(list, worker)) return;
     attend_segment<A, LAYOUT, UNIT, false>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
 }
 

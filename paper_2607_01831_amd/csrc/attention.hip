@@ -449,8 +449,9 @@ AttnPlan plan_attention(KvMode mode, const Geometry &g, int B, int Hq, int nq, i
     // fit one round: nothing to balance, and the list's start and walk cost 1 us
     // of a 10 us call (decode, 4 sequences of 4K: 10.7 us, by the list 11.5;
     // verification of 2 drafts, 2 of 2K: 14.0 and 15.3; 6-bit anchors, 8 of 4K:
-    // 15.2 and 16.4).  Past one round the list balances (one sequence of 33000:
-    // 17.2 us, by direct workgroups 19.9).
+    // 15.2 and 16.4).  Past one round the list balances (decodes of one
+    // sequence of 33000: 17.2 us, by direct workgroups 19.9; 5 of 8K: 18.5 and 19.7;
+    // 5 ragged ones of up to 8K, not all units there: 13.7 and 12.9).
     const bool direct = units * g.Hkv * chunks <= slots &&
                         (most == SIZE_MAX || kCounterBytes + units * row_bytes <= most);
     p.direct = direct ? (int)work_units(max_seq_len) : 0;
@@ -648,7 +649,7 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
     // More than 8 partials a sequence (one wait for memory of a thread that merges
     // them all): a row per workgroup, 8 threads deep in them, while those
     // workgroups are resident at once; else the rows share workgroups.  2
-    // sequences of 8K, 2 drafts (512 rows, 16 partials): 16.8 us, shared 18.2;
+    // sequences of 8K, 2 drafts (128 rows, 16 partials): 16.8 us, shared 18.2;
     // 8 of 1.5K-5K, 8 drafts (2048 rows): 33.9, shared 26.4.  A single sequence
     // of more than 16 partials also past that (32K, 20 drafts, 640 rows: 46.2,
     // shared 47.7).

@@ -615,9 +615,8 @@ __global__ __launch_bounds__(kThreads, 2) void verify_batch_kernel(VerifyArgs a)
     const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
     const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
     const WorkList<UNIT, true> list(a.seq_lens, a.B, a.max_seq_len, a.workers);
-    if (worker >= list.workers) return;
     Segment<UNIT> seg;
-    seg.start(list, worker);
+    if (!seg.start(list, worker)) return;
     for (;;) {
         verify_segment<RT, LAYOUT, UNIT, false>(a, seg, fresh_uniform(hc % a.geo.Hkv), fresh_uniform(hc / a.geo.Hkv), fresh_tid());
         if (!seg.next(list, worker)) return;
@@ -631,9 +630,8 @@ __global__ __launch_bounds__(kThreads, 2) void verify_long_kernel(VerifyArgs a) 
     const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
     const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
     const WorkList<UNIT, false> list(a.seq_lens, 1, a.max_seq_len, a.workers);
-    if (worker >= list.workers) return;
     Segment<UNIT> seg;
-    seg.start(list, worker);
+    if (!seg.start(list, worker)) return;
     verify_segment<RT, LAYOUT, UNIT, false>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
 }
 

@@ -5,12 +5,12 @@
 // one round (plan_attention).  The sequences' units of UNIT 128-token groups
 // (at least one unit each, so that an empty sequence has an owner) stand in
 // one list, and worker p of W takes the units [p total / W, (p + 1) total / W)
-// of it, whichever sequences they belong to: one segment per sequence that it
-// touches, one partial per segment.  A grid of fixed splits per sequence
-// leaves a ragged batch's last round partly empty and pays a prologue and an
-// epilogue per split (16 paged sequences of 16K-64K tokens: 166 us for the
-// decode and its combine in splits of 2048 tokens, 154 us so; 32 of 1K-8K with a
-// tail 58.5 -> 45.6 us).
+// of it, whichever sequences they belong to (or a share inside one sequence, see
+// inner_share): one segment per sequence that it touches, one partial per
+// segment.  A grid of fixed splits per sequence leaves a ragged batch's last
+// round partly empty and pays a prologue and an epilogue per split (16 paged
+// sequences of 16K-64K tokens: 166 us for the decode and its combine in splits
+// of 2048 tokens, 154 us so; 32 of 1K-8K with a tail 58.5 -> 45.6 us).
 // The worker that owns unit x is floor(((x + 1) W - 1) / total), so each side
 // finds the others' shares without tables.  Segment (p, b) is number p + b of
 // its (kv head, row): the two never go down along the list and one of them
@@ -123,11 +123,29 @@ struct WorkList {
             first = __builtin_amdgcn_readlane(last, 63);
         }
     }
+    // A share across a boundary costs a second prologue, epilogue and merge, as
+    // long as a unit itself.  So shares stay inside their sequences, of `s`
+    // units at most (0: the shares of begin() and owner()), where that takes no
+    // more workers and no larger share than the equal ones (decode of 15
+    // sequences of 2500 tokens: 18.4 us, by equal shares 24.5; 16 of 1K-5K:
+    // 18.7 and 22.2).  segs: the shares of the sequences up to the lane's.
+    __device__ __forceinline__ int inner_share(int &segs) const {
+        if (B == 1 || B > 64 || workers == total) return 0;
+        const uint32_t s = ((uint32_t)total + workers - 1) / (uint32_t)opaque(workers);
+        segs = scan((int)(((uint32_t)units_at(0) + s - 1) / s));
+        return __builtin_amdgcn_readlane(segs, 63) <= workers ? (int)s : 0;
+    }
     // Sequence b's partials: n from number seg0 on.
     __device__ __forceinline__ void partials(int b, int &seg0, int &n) const {
-        const int first = B == 1 ? 0 : first_unit(b);
-        seg0 = owner(first);
-        n = owner(first + units(tokens_of(b)) - 1) - seg0 + 1;
+        int segs;
+        if (inner_share(segs)) {
+            seg0 = b > 0 ? __builtin_amdgcn_readlane(segs, b - 1) : 0;
+            n = __builtin_amdgcn_readlane(segs, b) - seg0;
+        } else {
+            const int first = B == 1 ? 0 : first_unit(b);
+            seg0 = owner(first);
+            n = owner(first + units(tokens_of(b)) - 1) - seg0 + 1;
+        }
         seg0 += b;
     }
     // The number of sequence b's first unit.
@@ -168,13 +186,32 @@ struct Segment {
         number0 = w0 + b;
         live = w1 - w0 + 1;
     }
-    // The first segment of worker p (which has a share).
+    // The first segment of worker p; false where it has none.
     template <bool WALK>
-    __device__ __forceinline__ void start(const WorkList<UNIT, WALK> &wl, int p) {
+    __device__ __forceinline__ bool start(const WorkList<UNIT, WALK> &wl, int p) {
+        if (p >= wl.workers) return false;
+        int segs;
+        if (const int s = wl.inner_share(segs)) {
+            const uint64_t past = __ballot(segs > p);
+            if (!past) return false;
+            b = __ffsll((long long)past) - 1;
+            const int w0 = b > 0 ? __builtin_amdgcn_readlane(segs, b - 1) : 0;
+            T = wl.tokens_of(b);
+            const int u0 = (p - w0) * s;
+            n_units = min(s, wl.units(T) - u0);
+            g0 = u0 * UNIT;
+            n_groups = max(0, min(n_units * UNIT, (T + kKGroup - 1) / kKGroup - g0));
+            number = p + b;
+            number0 = w0 + b;
+            live = __builtin_amdgcn_readlane(segs, b) - w0;
+            pos = end = first = 0;  // no second one
+            return true;
+        }
         pos = __builtin_amdgcn_readfirstlane(wl.begin(p));
         end = __builtin_amdgcn_readfirstlane(wl.begin(p + 1));
         wl.find(pos, b, first);
         set(wl, p);
+        return true;
     }
     // Without a list, where every unit has a worker (AttnPlan::direct): unit
     // `unit` of sequence `seq`, whose partials stand from direct seq on; false

@@ -368,19 +368,21 @@ def test_anchor_decode_ragged_batch_stale_workspace():
 
 
 @pytest.mark.parametrize("lens,Hkv,bt", [
-    ([0, 5000, 1, 0, 513, 512, 3000, 511], 2, 16),      # shares that straddle sequences, empty ones between
+    ([0, 5000, 1, 0, 513, 512, 3000, 511], 2, 16),      # a unit each, empty sequences between
     ([30000, 40, 9000], 8, 16),                         # one sequence over many workers, others inside one
     ([30000, 40, 9000], 8, None),
     ([700 + 37 * i % 900 for i in range(70)], 1, 16),   # more sequences than a wavefront's lanes
     ([1 + 13 * i % 600 for i in range(130)], 8, 24),    # more (sequence, kv head) pairs than counters; blocks of 24
     ([2048] * 40, 8, None),                             # whole units only, several a worker
+    ([2500, 2049, 100] * 7 + [0], 8, 16),               # shares of two units inside their sequences, odd remainders
+    ([0, 5000, 1, 0, 513, 512, 3000, 511] * 5, 8, 16),  # equal shares across sequences, empty ones between
     ([16384, 16000], 8, None),                          # a workgroup per unit, all resident workgroups used
     ([16385, 3, 0], 8, 16),                             # one unit too many for that; an empty sequence
     ([513, 0, 512, 1, 1024], 8, 16),                    # a workgroup per unit, sequences ending before the last
 ])
 def test_attention_work_list(lens, Hkv, bt):
-    """The attention kernels' work list: equal shares of a ragged batch's units,
-    whichever sequences they fall in, through every merge of their partials
+    """The attention kernels' shares of a batch's units: a unit each, several
+    inside a sequence, equal ones across sequences, through every merge of their partials
     (one worker's own, the last workgroup's, the combine kernels') for the
     decode, the decode with a tail and the verification."""
     G, nq = 2, 5

@@ -179,11 +179,25 @@ def test_split_decode_calls_share_one_workspace():
     assert int(shared[:lynx.ATTN_COUNTER_BYTES].count_nonzero()) == 0
 
 
+@pytest.mark.parametrize("A", [2, 6])
+@pytest.mark.parametrize("lens,bt", [
+    ([2500, 2049, 100] * 7 + [0], None),                # several units a share, inside the sequences
+    ([0, 5000, 1, 0, 513, 512, 3000, 511] * 5, 16),     # equal shares across sequences
+])
+def test_split_decode_shares(A, lens, bt):
+    Hkv, G = 8, 2
+    kv = [random_kv(T, Hkv, seed=4600 + T) for T in lens]
+    lens, L, OL, table, planes, meta, op, om = encode(A, [k for k, _ in kv], [v for _, v in kv], Hkv, bt=bt)
+    q = random_bf16((len(lens), Hkv * G, 128), seed=4601)
+    out, lse = decode(A, lens, L, table, planes, meta, q)
+    check(A, lens, OL, table, op, om, q, out, lse, what=f"A={A} shares of {len(lens)} sequences")
+
+
 @pytest.mark.parametrize("A", [2, 4, 6])
 def test_split_decode_long_splits(A):
-    """A contiguous batch whose plan takes splits longer than 2048 tokens (more
-    than 512 workgroups of 2048 tokens, at most 512 of 4096): every wavefront
-    attends 8 groups and the last split is ragged.  Two (sequence, kv head) units against the oracle."""
+    """Two long contiguous sequences: shares of five units on 256 CUs, so that a
+    wavefront attends five groups, the last share of each sequence shorter and
+    ragged.  Two (sequence, kv head) units against the oracle."""
     lens, Hkv, G = [70001, 69000], 8, 1
     kv = [random_kv(T, Hkv, seed=4700 + T) for T in lens]
     lens, L, OL, table, planes, meta, op, om = encode(A, [k for k, _ in kv], [v for _, v in kv], Hkv)
