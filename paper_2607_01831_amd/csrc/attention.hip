@@ -646,16 +646,18 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
     } else {
         return hipErrorInvalidValue;  // anchor attention with several queries: no entry point asks for it
     }
-    // More than 8 partials a sequence (one wait for memory of a thread that merges
-    // them all): a row per workgroup, 8 threads deep in them, while those
-    // workgroups are resident at once; else the rows share workgroups.  2
-    // sequences of 8K, 2 drafts (128 rows, 16 partials): 16.8 us, shared 18.2;
-    // 8 of 1.5K-5K, 8 drafts (2048 rows): 33.9, shared 26.4.  A single sequence
-    // of more than 16 partials also past that (32K, 20 drafts, 640 rows: 46.2,
-    // shared 47.7).
+    // Many partials a sequence: a row per workgroup, 8 threads deep in them, while
+    // those workgroups are resident at once; else the rows share workgroups.
+    // Many are more than the 8 that a thread loads together where the partials
+    // are found without the list (2 sequences of 8K, 2 drafts, 128 rows of 16
+    // partials: 16.8 us, shared 18.2; 2048 such rows: 33.9, shared 26.4), and
+    // more than 16 with it (8 of 1.5K-5K, 2 drafts, 9 partials: 20.6, shared
+    // 19.9; 2 of 19K, 33 partials: 26.1, shared 29.8).  A single sequence's rows
+    // of more than 16 go alone whatever their number (32K, 20 drafts, 640 rows:
+    // 46.2, shared 47.7).
     const int each = plan.direct ? plan.direct : std::min(plan.max_live, plan.workers / B + 1);
     const long long rows_all = (long long)plan.rows_total * g.Hkv * B;
-    const bool deep = each > 8 && (rows_all <= resident_workgroups() || (B == 1 && each > 16));
+    const bool deep = (each > (plan.direct ? 8 : 16) && rows_all <= resident_workgroups()) || (B == 1 && each > 16);
     if (!deep) {
         const int rows = plan.rows_total <= 4 ? 4 : 8;
         const dim3 grid((plan.rows_total + rows - 1) / rows, g.Hkv, B);
