@@ -29,10 +29,6 @@ struct AttnArgs {
     int tail_count;       // tokens of the tail every query sees; -1: query i sees i + 1 (drafts)
     int tail_stride;      // tail tokens stored per sequence in k_new / v_new
     const int32_t *seq_lens;
-    const int32_t *block_table;
-    const uint8_t *k_plane;
-    const uint8_t *v_plane;
-    MetaPtrs meta;
     const uint16_t *q;
     const uint16_t *k_new;
     const uint16_t *v_new;
@@ -533,10 +529,6 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
     a.tail_count = mode == KvMode::kCodes ? -1 : tail_count;
     a.tail_stride = mode == KvMode::kCodes ? nq : tail_count;
     a.seq_lens = seq_lens;
-    a.block_table = block_table;
-    a.k_plane = k_plane;
-    a.v_plane = v_plane;
-    a.meta = meta;
     a.q = q;
     a.k_new = k_new;
     a.v_new = v_new;
