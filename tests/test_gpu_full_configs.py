@@ -204,9 +204,9 @@ def test_70b_b4_128k():
 
 
 def test_one_round_long_splits():
-    """A contiguous batch large enough that one round of workgroups (two per
-    CU) needs 4096-token splits: 512K tokens, 4 kv heads, G = 4.  Decode (its
-    split merge in the same launch) and verification of k = 4 drafts with
+    """One sequence of 512K tokens, 4 kv heads, G = 4: on 256 CUs 128 workers
+    with shares of eight units, 32 groups.  Decode (the merge of 128 partials
+    in the same launch) and verification of k = 4 drafts with
     their tail (16 query rows per workgroup), 2 sampled units each against
     the oracle."""
     Hkv, G, T, nq = 4, 4, 524288, 4

@@ -250,8 +250,8 @@ def test_verify_wide_range_queries_and_keys(nq, exp):
 
 @pytest.mark.slow
 def test_verify_eight_group_splits():
-    """64K context x 8 kv heads, k = 8: the plan picks 1024-token splits (8
-    groups, two per wavefront); 2 sampled kv heads against the oracle."""
+    """64K context x 8 kv heads, k = 8: on 256 CUs shares of two units (8 groups,
+    two per wavefront); 2 sampled kv heads against the oracle."""
     T, Hkv, G, nq = 65536, 8, 4, 8
     k, v = random_kv(T, Hkv, seed=950)
     c = build_cache([k], [v], Hkv)
@@ -328,8 +328,8 @@ def test_anchor_decode_workspace_reuse():
 
 
 def test_anchor_decode_many_units():
-    """A wide batch of short sequences: 257 sequences x 64 kv heads, one
-    split each."""
+    """A wide batch of short sequences, one unit each: 257 sequences x 64 kv
+    heads, on 256 CUs some 32 sequences to a worker."""
     Hkv, B = 64, 257
     g = torch.Generator().manual_seed(11)
     lens = torch.randint(1, 40, (B,), generator=g).tolist()
@@ -343,7 +343,7 @@ def test_anchor_decode_many_units():
 
 
 def test_anchor_decode_ragged_batch_stale_workspace():
-    """A ragged batch over a workspace full of stale values: splits past a
+    """A ragged batch over a workspace full of stale values: partials past a
     short sequence's end must not contribute."""
     Hkv, G = 8, 4
     lens = [6000, 100, 3000, 20, 5999, 1, 2500, 4097]
@@ -474,9 +474,9 @@ def _decode_check_sampled(c, q, mask, what):
 
 @pytest.mark.slow
 def test_anchor_decode_two_round_splits_dominant_token():
-    """Splits of 8 groups (two rounds of the rolling fold): 2 x 32 kv heads x
-    ~20K tokens.  One unit holds a token whose score overflows the first
-    tile's reference (the workgroup redoes the split with a running maximum),
+    """2 x 32 kv heads x ~20K tokens: on 256 CUs shares of five units, five
+    groups to a wavefront.  One unit holds a token whose score overflows the first
+    tile's reference (the wavefront redoes its tiles with a running maximum),
     one a milder outlier."""
     Hkv, G, lens = 32, 4, [20000, 19000]
     q = random_bf16((2, Hkv * G, 128), seed=21)
@@ -490,14 +490,15 @@ def test_anchor_decode_two_round_splits_dominant_token():
     c = build_cache(ks, vs, Hkv, merge=False)
     mask = np.zeros((2, Hkv), np.uint8)
     mask[1, 5] = mask[0, 3] = mask[0, 17] = mask[1, 30] = 1
-    _decode_check_sampled(c, q, mask, "8-group splits")
+    _decode_check_sampled(c, q, mask, "shares of five units")
 
 
 @pytest.mark.slow
 def test_anchor_decode_sixteen_group_splits_ragged():
-    """Splits of 16 groups (four rounds of the rolling fold) over a ragged
-    batch of 8 x 16 kv heads, including a one-token sequence and lengths that
-    end inside a round; one unit forces the running-maximum path."""
+    """A ragged batch of 8 x 16 kv heads, including a one-token sequence and
+    lengths that end inside a unit: on 256 CUs 32 workers for 143 units, shares
+    of up to five inside the sequences; one sequence forces the running-maximum
+    path."""
     Hkv, G = 16, 2
     lens = [15000, 3000, 14999, 2049, 8000, 15000, 1, 12345]
     q = random_bf16((len(lens), Hkv * G, 128), seed=22)
@@ -511,7 +512,30 @@ def test_anchor_decode_sixteen_group_splits_ragged():
     mask = np.zeros((len(lens), Hkv), np.uint8)
     for b, h in [(2, 7), (0, 0), (1, 15), (3, 4), (4, 9), (6, 2), (7, 11), (5, 8)]:
         mask[b, h] = 1
-    _decode_check_sampled(c, q, mask, "16-group splits")
+    _decode_check_sampled(c, q, mask, "ragged shares of up to five units")
+
+
+@pytest.mark.parametrize("lens,bt", [([32731, 700], None), ([32731], 16), ([32731, 700], 16), ([32731], 24)])
+def test_attention_long_walks(lens, bt):
+    """Many query rows over few kv heads leave few workers (8 on 256 CUs, for
+    the decode's 16 chunks of 16 heads and the verification's 16 of 32 rows),
+    so a wavefront walks 8 groups or more of its share, with paging through
+    both halves of its block-id buffer.  A late dominant token sends one
+    wavefront through all of them again.  Two kv heads against the oracle."""
+    Hkv, G, nq = 4, 256, 2
+    B = len(lens)
+    q = random_bf16((B, Hkv * G, 128), seed=2700)
+    qv = random_bf16((B, nq, Hkv * G, 128), seed=2701)
+    kv = [random_kv(T, Hkv, seed=2702 + T) for T in lens]
+    _dominant(kv[0][0], q[0], 30000, 1, G, 400.0)
+    c = build_cache([a for a, _ in kv], [b for _, b in kv], Hkv, bt=bt, seed=6)
+    mask = np.zeros((B, Hkv), np.uint8)
+    mask[0, 1] = mask[B - 1, 3] = 1
+    _decode_check_sampled(c, q, mask, "long walks")
+    got = gpu_verify(c, qv)
+    ref, _ = oracle_verify(c, qv, unit_mask=mask)
+    for b, h in zip(*np.nonzero(mask)):
+        assert_close(got[b, :, h * G:(h + 1) * G], ref[b, :, h * G:(h + 1) * G], what=f"verification b={b} h={h}")
 
 
 def gpu_anchor_decode_tail(c, q, kt, vt):
@@ -580,7 +604,7 @@ def test_anchor_decode_tail(n_tail, lens, bt):
 
 
 def test_combine_of_more_than_64_splits():
-    """One kv head over 40,000 tokens: 79 splits of 512 tokens, merged by the
+    """One kv head over 40,000 tokens: 79 units of 512 tokens, a partial each, merged by the
     combine kernel with its larger load batch (decode with a tail, and
     verification with its causal draft tail)."""
     Hkv, G, T, nq = 1, 4, 40000, 4

@@ -209,6 +209,21 @@ def test_split_decode_long_splits(A):
     check(A, lens, OL, table, op, om, q, out, lse, unit_mask=mask, what=f"A={A} long splits")
 
 
+@pytest.mark.parametrize("A", [2, 6])
+@pytest.mark.parametrize("bt", [None, 16])
+def test_split_decode_long_walks(A, bt):
+    """256 query heads per kv head leave 8 workers on 256 CUs: a wavefront walks
+    8 groups or more, with paging through both halves of its block-id buffer."""
+    lens, Hkv, G = [32731, 700], 4, 256
+    kv = [random_kv(T, Hkv, seed=4740 + T) for T in lens]
+    lens, L, OL, table, planes, meta, op, om = encode(A, [k for k, _ in kv], [v for _, v in kv], Hkv, bt=bt)
+    q = random_bf16((2, Hkv * G, 128), seed=4741)
+    out, lse = decode(A, lens, L, table, planes, meta, q)
+    mask = np.zeros((2, Hkv), np.uint8)
+    mask[0, 2] = mask[1, 1] = 1
+    check(A, lens, OL, table, op, om, q, out, lse, unit_mask=mask, what=f"A={A} long walks")
+
+
 @pytest.mark.parametrize("A", [2, 4, 6])
 @pytest.mark.parametrize("scale", [1e-30, 1e30])
 def test_split_decode_extreme_scales(A, scale):
