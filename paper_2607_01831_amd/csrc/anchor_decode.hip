@@ -27,7 +27,8 @@
 // Work split: grid = (worker, kv head x head chunk), as many workers as the
 // chip holds at once (two workgroups of 4 wavefronts per CU), each with an
 // equal share of the batch's 512-token units (work_list.h), a segment per
-// sequence it touches.  Wavefront w owns the groups w, w + 4, ... of a
+// sequence it touches; or, where one round holds them all, (unit, kv head x
+// head chunk, sequence).  Wavefront w owns the groups w, w + 4, ... of a
 // segment: it folds each
 // group's K scales into its own MFMA operand lanes of the query (registers)
 // and attends the group's four 32-token tiles with its own online softmax,

@@ -39,7 +39,7 @@
 // per wavefront from the largest V scale of its tokens), z' is summed in fp32.
 //
 // Work split: as in the 4-bit decode, grid = (worker, kv head x chunk of 16
-// query heads), the kv head fastest for paged layouts, each worker with an
+// query heads) or (unit, the same, sequence), the kv head fastest for paged layouts, each worker with an
 // equal share of the batch's 512-token units (work_list.h); 4 wavefronts per
 // workgroup, two workgroups per CU, wavefront w owning a segment's groups w,
 // w + 4, ...  The 32-token tiles stream into a private

@@ -31,8 +31,8 @@
 // Work split: grid = (worker, kv head x chunk of 16 RT query rows), as many
 // workers as the chip holds at once (two workgroups of 4 wavefronts per CU),
 // each with an equal share of the batch's 512-token units (work_list.h), a
-// segment per sequence it touches.  Wavefront w owns a segment's groups w,
-// w + 4, ...
+// segment per sequence it touches; or, where one round holds them all, (unit,
+// kv head x chunk, sequence).  Wavefront w owns a segment's groups w, w + 4, ...
 // and serves all RT row tiles from each of their 32-token tiles, so every
 // K/V byte is fetched once per workgroup and the query fold of a group
 // (y for the wavefront's own MFMA operand lanes) lives in its registers:
