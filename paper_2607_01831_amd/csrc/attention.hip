@@ -240,8 +240,12 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
 // values are staged once.  A workgroup per row reads the tail once a row, and
 // spends a third of its time on its first wait (verification of 5 drafts for 16
 // paged sequences: 17.1 -> 8.1 us).
-template <int ROWS>
+// FIND: how the row's partials are found: 0 without the list, 1 by the list of a
+// batch whose sequences have a lane each, 2 by any list (32 sequences of 1K-8K:
+// 5.5 us, 5.7 by one kernel for all three).
+template <int ROWS, int FIND>
 __global__ __launch_bounds__(32 * ROWS) void attn_combine_rows_kernel(AttnArgs a, uint16_t *out, float *lse) {
+    if (FIND == 1) __builtin_assume(a.B > 1 && a.B <= 64);
     constexpr int kThreads = 32 * ROWS;
     constexpr int kTailMax = 64;
     constexpr int kTokens = kThreads / 4;  // tail tokens scored per pass, four threads each
@@ -268,7 +272,8 @@ __global__ __launch_bounds__(32 * ROWS) void attn_combine_rows_kernel(AttnArgs a
     __shared__ __attribute__((aligned(16))) float s_q[ROWS][kHeadDim + 16];
     __shared__ float s_t[ROWS][kTailMax];  // tail scores (log2 units), then weights
 
-    const int own = a.direct ? a.seq_lens[b] : WorkList<kWorkUnit, false>::load_own(a.seq_lens, a.B);
+    // the length of the lane's sequence for the list, else of this one
+    const int own = a.seq_lens[FIND == 0 ? b : min((int)(threadIdx.x & 63), a.B - 1)];
     // ---- the tail's loads ----
     uint4 kw[kPasses][4];
     if (tail_most > 0) {
@@ -293,7 +298,7 @@ __global__ __launch_bounds__(32 * ROWS) void attn_combine_rows_kernel(AttnArgs a
     }
     // ---- the row's partials (work_list.h): n of them from segment seg0 on ----
     int n, seg0;
-    if (a.direct) {
+    if (FIND == 0) {
         n = WorkList<kWorkUnit, false>::units(max(0, min(own, a.max_seq_len)));
         seg0 = b * a.direct;
     } else {
@@ -505,6 +510,17 @@ size_t decode_limit_bytes(const Geometry &g, int B, int Hq, int max_seq_len) {
     return kCounterBytes + (size_t)(heads * G * splits(tokens)) * kPartialBytes;
 }
 
+template <int ROWS>
+static void launch_combine_rows(int find, const AttnArgs &a, uint16_t *out, float *lse, hipStream_t stream) {
+    const dim3 grid((a.rows_total + ROWS - 1) / ROWS, a.geo.Hkv, a.B), block(32 * ROWS);
+    if (find == 0)
+        hipLaunchKernelGGL((attn_combine_rows_kernel<ROWS, 0>), grid, block, 0, stream, a, out, lse);
+    else if (find == 1)
+        hipLaunchKernelGGL((attn_combine_rows_kernel<ROWS, 1>), grid, block, 0, stream, a, out, lse);
+    else
+        hipLaunchKernelGGL((attn_combine_rows_kernel<ROWS, 2>), grid, block, 0, stream, a, out, lse);
+}
+
 hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan, int B, int Hq,
                             int nq, int max_seq_len, const int32_t *seq_lens,
                             const int32_t *block_table, const uint8_t *k_plane,
@@ -651,12 +667,11 @@ hipError_t launch_attention(KvMode mode, const Geometry &g, const AttnPlan &plan
     const long long rows_all = (long long)plan.rows_total * g.Hkv * B;
     const bool deep = (each > (plan.direct ? 8 : 16) && rows_all <= resident_workgroups()) || (B == 1 && each > 16);
     if (!deep) {
-        const int rows = plan.rows_total <= 4 ? 4 : 8;
-        const dim3 grid((plan.rows_total + rows - 1) / rows, g.Hkv, B);
-        if (rows == 4)
-            hipLaunchKernelGGL(attn_combine_rows_kernel<4>, grid, dim3(128), 0, stream, a, out, lse);
+        const int find = plan.direct ? 0 : B > 1 && B <= 64 ? 1 : 2;
+        if (plan.rows_total <= 4)
+            launch_combine_rows<4>(find, a, out, lse, stream);
         else
-            hipLaunchKernelGGL(attn_combine_rows_kernel<8>, grid, dim3(256), 0, stream, a, out, lse);
+            launch_combine_rows<8>(find, a, out, lse, stream);
     } else if (plan.max_live <= 64) {
         hipLaunchKernelGGL(attn_combine_kernel<8>, dim3(plan.rows_total, g.Hkv, B), dim3(kCombineThreads),
                            0, stream, a, out, lse);

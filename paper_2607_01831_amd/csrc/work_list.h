@@ -124,13 +124,16 @@ struct WorkList {
         }
     }
     // A share across a boundary costs a second prologue, epilogue and merge, as
-    // long as a unit itself.  So shares stay inside their sequences, of `s`
-    // units at most (0: the shares of begin() and owner()), where that takes no
-    // more workers and no larger share than the equal ones (decode of 15
-    // sequences of 2500 tokens: 18.4 us, by equal shares 24.5; 16 of 1K-5K:
-    // 18.7 and 22.2).  segs: the shares of the sequences up to the lane's.
+    // long as a unit itself.  So shares of few units stay inside their
+    // sequences, of `s` units at most (0: the shares of begin() and owner()),
+    // where that takes no more workers and no larger share than the equal ones
+    // (decode of 15 sequences of 2500 tokens: 18.4 us, by equal shares 24.5; 16
+    // of 1K-5K: 18.7 and 22.2).  Of more than four units a share hides the
+    // boundary, and the look for whole ones, mostly in vain, costs 2% (32 of
+    // 1K-8K with a tail, five units: 46.0 us, without it 45.0).  segs: the
+    // shares of the sequences up to the lane's.
     __device__ __forceinline__ int inner_share(int &segs) const {
-        if (B == 1 || B > 64 || workers == total) return 0;
+        if (B == 1 || B > 64 || workers == total || total > 4 * workers) return 0;
         const uint32_t s = ((uint32_t)total + workers - 1) / (uint32_t)opaque(workers);
         segs = scan((int)(((uint32_t)units_at(0) + s - 1) / s));
         return __builtin_amdgcn_readlane(segs, 63) <= workers ? (int)s : 0;
