@@ -198,7 +198,8 @@ def _csv(dirname, suffix):
 def _short(name: str) -> str:
     # the kernels of a batch, of a long sequence and of rows that share a
     # workgroup, with the plain ones
-    name = name.replace("_batch_kernel", "_kernel").replace("_long_kernel", "_kernel").replace("_rows_kernel", "_kernel")
+    for suffix in ("_unit_batch", "_batch", "_long", "_rows"):
+        name = name.replace(suffix + "_kernel", "_kernel")
     for key in ("anchor_split_decode_kernel", "anchor_decode_kernel", "attn_combine_kernel", "verify_kernel", "encode_kernel",
                 "merge_kernel", "copyBuffer", "hencode_kernel", "hdequant_kernel",
                 "deserialize_anchor_kernel", "deserialize_residual_kernel", "merge_split_kernel",
@@ -214,7 +215,7 @@ def _short(name: str) -> str:
 def _variant(name: str) -> str:
     """A library kernel with its template arguments (the decode of a 32K layer,
     anchor_decode_kernel<4, 0, 4>, and the 70B-shaped one,
-    anchor_decode_batch_kernel<8, 0, 4>, launch the same number of work-items);
+    anchor_decode_batch_kernel<8, 0, 4, true>, launch the same number of work-items);
     any other kernel by its short name."""
     m = re.search(r"(\w+_kernel)(<[^()]*>)\(", name)
     if m and "lynx::" in name:

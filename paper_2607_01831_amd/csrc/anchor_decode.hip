@@ -612,8 +612,10 @@ __device__ __forceinline__ void attend_segment(const DecodeArgs &a, const Segmen
 // holds the rows of every kv head for its tokens side by side, so paged
 // layouts make the kv head the fastest grid index: workgroups reading the
 // same blocks run together and share DRAM pages.
-template <int GP, int LAYOUT, int UNIT>
+// LANES: a lane for each sequence (B <= 64).
+template <int GP, int LAYOUT, int UNIT, bool LANES>
 __global__ __launch_bounds__(kThreads, 2) void anchor_decode_batch_kernel(DecodeArgs a) {
+    if (LANES) __builtin_assume(a.B > 1 && a.B <= 64);
     const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
     const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
     const WorkList<UNIT, true> list(a.seq_lens, a.B, a.max_seq_len, a.workers);
@@ -637,11 +639,22 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_long_kernel(DecodeA
     attend_segment<GP, LAYOUT, UNIT, false>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
 }
 
-// A unit per workgroup, for sequence blockIdx.z: nothing to balance, and the
-// short call is all latency (32K layer: 14.0 us, 14.3 through the long kernel,
-// 14.7 through the batch's, whose start waits for its arguments in turn).
+// A unit per workgroup: nothing to balance, and the short call is all latency
+// (32K layer: 14.0 us, 14.3 through the long kernel, 14.7 through the batch's,
+// whose start waits for its arguments in turn).  A single sequence's own kernel,
+// without b in its addresses, is 0.1 us faster still.
 template <int GP, int LAYOUT, int UNIT>
 __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a) {
+    const int unit = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
+    const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
+    Segment<UNIT> seg;
+    if (!seg.set_unit(a.seq_lens, a.max_seq_len, a.direct, 0, unit)) return;
+    attend_segment<GP, LAYOUT, UNIT, true>(a, seg, hc % a.geo.Hkv, hc / a.geo.Hkv, threadIdx.x);
+}
+
+// The same for a batch, sequence blockIdx.z.
+template <int GP, int LAYOUT, int UNIT>
+__global__ __launch_bounds__(kThreads, 2) void anchor_decode_unit_batch_kernel(DecodeArgs a) {
     const int unit = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
     const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
     Segment<UNIT> seg;
@@ -651,12 +664,17 @@ __global__ __launch_bounds__(kThreads, 2) void anchor_decode_kernel(DecodeArgs a
 
 template <int GP, int LAYOUT>
 void launch_gp(const DecodeArgs &args, dim3 grid, hipStream_t stream) {
-    if (args.direct)
-        hipLaunchKernelGGL((anchor_decode_kernel<GP, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
-    else if (args.B > 1)
-        hipLaunchKernelGGL((anchor_decode_batch_kernel<GP, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+    const dim3 block(kThreads);
+    if (args.direct && args.B == 1)
+        hipLaunchKernelGGL((anchor_decode_kernel<GP, LAYOUT, kWorkUnit>), grid, block, 0, stream, args);
+    else if (args.direct)
+        hipLaunchKernelGGL((anchor_decode_unit_batch_kernel<GP, LAYOUT, kWorkUnit>), grid, block, 0, stream, args);
+    else if (args.B == 1)
+        hipLaunchKernelGGL((anchor_decode_long_kernel<GP, LAYOUT, kWorkUnit>), grid, block, 0, stream, args);
+    else if (args.B <= 64)
+        hipLaunchKernelGGL((anchor_decode_batch_kernel<GP, LAYOUT, kWorkUnit, true>), grid, block, 0, stream, args);
     else
-        hipLaunchKernelGGL((anchor_decode_long_kernel<GP, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+        hipLaunchKernelGGL((anchor_decode_batch_kernel<GP, LAYOUT, kWorkUnit, false>), grid, block, 0, stream, args);
 }
 
 template <int GP>

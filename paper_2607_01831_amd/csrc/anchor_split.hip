@@ -751,8 +751,10 @@ __device__ __forceinline__ void attend_segment(const SplitDecodeArgs &a, const S
         merge_pair<16>(a, pair_o, pair_ml, orow0, heads, live, s_ring);
 }
 
-template <int A, int LAYOUT, int UNIT>
+// LANES: a lane for each sequence (B <= 64).
+template <int A, int LAYOUT, int UNIT, bool LANES>
 __global__ __launch_bounds__(kThreads, 2) void anchor_split_decode_batch_kernel(SplitDecodeArgs a) {
+    if (LANES) __builtin_assume(a.B > 1 && a.B <= 64);
     const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
     const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
     const WorkList<UNIT, true> list(a.seq_lens, a.B, a.max_seq_len, a.workers);
@@ -792,9 +794,12 @@ void launch_layout(const SplitDecodeArgs &args, dim3 grid, hipStream_t stream) {
         hipLaunchKernelGGL((anchor_split_decode_kernel<A, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
     else if (args.B == 1)
         hipLaunchKernelGGL((anchor_split_decode_long_kernel<A, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+    else if (args.B <= 64)
+        hipLaunchKernelGGL((anchor_split_decode_batch_kernel<A, LAYOUT, kWorkUnit, true>), grid, dim3(kThreads), 0,
+                           stream, args);
     else
-        hipLaunchKernelGGL((anchor_split_decode_batch_kernel<A, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream,
-                           args);
+        hipLaunchKernelGGL((anchor_split_decode_batch_kernel<A, LAYOUT, kWorkUnit, false>), grid, dim3(kThreads), 0,
+                           stream, args);
 }
 
 template <int A>

@@ -610,8 +610,10 @@ __device__ __forceinline__ void verify_segment(const VerifyArgs &a, const Segmen
 // holds the rows of every kv head for its tokens side by side, so paged
 // layouts make the kv head the fastest grid index: workgroups reading the
 // same blocks run together and share DRAM pages.
-template <int RT, int LAYOUT, int UNIT>
+// LANES: a lane for each sequence (B <= 64).
+template <int RT, int LAYOUT, int UNIT, bool LANES>
 __global__ __launch_bounds__(kThreads, 2) void verify_batch_kernel(VerifyArgs a) {
+    if (LANES) __builtin_assume(a.B > 1 && a.B <= 64);
     const int worker = LAYOUT == 0 ? blockIdx.x : blockIdx.y;
     const int hc = LAYOUT == 0 ? blockIdx.y : blockIdx.x;
     const WorkList<UNIT, true> list(a.seq_lens, a.B, a.max_seq_len, a.workers);
@@ -651,8 +653,10 @@ void launch_rt(const VerifyArgs &args, dim3 grid, hipStream_t stream) {
         hipLaunchKernelGGL((verify_kernel<RT, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
     else if (args.B == 1)
         hipLaunchKernelGGL((verify_long_kernel<RT, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+    else if (args.B <= 64)
+        hipLaunchKernelGGL((verify_batch_kernel<RT, LAYOUT, kWorkUnit, true>), grid, dim3(kThreads), 0, stream, args);
     else
-        hipLaunchKernelGGL((verify_batch_kernel<RT, LAYOUT, kWorkUnit>), grid, dim3(kThreads), 0, stream, args);
+        hipLaunchKernelGGL((verify_batch_kernel<RT, LAYOUT, kWorkUnit, false>), grid, dim3(kThreads), 0, stream, args);
 }
 
 template <int RT>
